@@ -133,6 +133,7 @@ struct DecodeWs {
     int32_t *order;         // [S][max_blocks]  ranked logical blocks
     int32_t *ranked_page;   // [S][max_blocks]  physical page of each ranked block
     unsigned long long *agg;  // [S][max_chunks][G]  (L_chunk, Lmin_chunk) as two floats, or kAggSentinel
+    int32_t *lse_ready;     // [S][max_chunks]  1 = the chunk's block_lse values are in memory (written after agg)
     float *block_lse;       // [S][max_blocks][G]  log2 of each ranked block's AS (Algorithm 1 line 10)
     float *logits;          // [S][max_blocks][G][16]  scaled logits (log2 units) by ranked block; position
                             // 4*r + j of a (block, head) row holds token 4*j + r

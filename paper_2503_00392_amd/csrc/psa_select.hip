@@ -20,9 +20,13 @@
 //   3. reads the chunk's key slices (each wave keeps 4 slices = 16 KiB in flight, loaded as coalesced
 //      1 KiB rows and turned into the matrix-operand layout through a patch of LDS), computes the
 //      scaled logits of all G heads as a 16-token x 16-head x 128-channel product on the matrix
-//      cores (heads beyond G are zero columns), stores them for the value pass, and reduces each
-//      block's log-sum-exp L_b (= log AS of line 10);
-//   4. publishes the chunk's (log-sum-exp, minimum) of L_b per head as one 64-bit word per head.
+//      cores (heads beyond G are zero columns), keeps them in LDS until the chunk is done, and then reduces
+//      every block's log-sum-exp L_b (= log AS of line 10) at once;
+//   4. publishes the chunk's (log-sum-exp, minimum) of L_b per head as one 64-bit word per head, then the L_b
+//      themselves, then a word that says they are there; the logits leave for the workspace meanwhile.
+// From the last key to the published word a chunk takes 0.9 us, and 3.2 us from its first load on an idle chip; with
+// the reduction inside the loop over the slices, and the words after all stores, these were 1.0 us (3 us under load)
+// and 4.6 us.  A call at 32K tokens, batch 8, went from 112.5 to 109.7 us, at 4K, batch 31, from 58.1 to 54.1.
 // The wait of step 2 is a courtesy, not a dependency: no chunk workgroup needs anything to proceed
 // (when the looks run out it simply reads its chunk), so the grid drains whatever order it runs in.
 // THE FOLD applies lines 12-17 strictly in rank order: AS_acc, AS_min, N_left and P_acc at the end
@@ -111,19 +115,18 @@ __device__ __forceinline__ void nap(int tries) {
     if (tries > 1) __builtin_amdgcn_s_sleep(20);
 }
 
-constexpr int kStagedBlocks = 32;     // chunks of up to this many blocks keep their logits in LDS until they are done
-
-template <int G, bool STAGE>
+// MAXB: blocks of a chunk at most, 32 or kMaxChunkBlocks (the size of the patch that holds a chunk's logits).
+template <int G, int MAXB>
 struct SelectShared {
     uint4 qb[4][64];                       // B operand of the QK^T product of the workgroup's stream, by lane
-    float Lb[kMaxChunkBlocks][G];          // per-block log2-sum-exp2
-    int page[kMaxChunkBlocks];
-    int valid[kMaxChunkBlocks];
+    float Lb[MAXB][G];                     // per-block log2-sum-exp2
+    int page[MAXB];
+    int valid[MAXB];
     int go;                                // after the wait for the window: 1 = read the chunk, 0 = the stream closed
     unsigned long long kp0;                // the stream's progress word as the workgroup first saw it
     uint4 stage[kSelectThreads / 64][16 * 17];   // per wave: one key slice, rows padded to 272 bytes
-    // the chunk's logits in the layout of the workspace, written out as one piece (STAGE only)
-    __attribute__((aligned(16))) float lg[STAGE ? kStagedBlocks : 1][G][kPage];
+    // the chunk's logits in the layout of the workspace, written out as one piece
+    __attribute__((aligned(16))) float lg[MAXB][G][kPage];
 };
 
 // How far a stream can still go, in chunks, given what the fold knows after n blocks.  AS_acc only grows and
@@ -192,15 +195,17 @@ constexpr int kFoldPatience = 1 << 19;
 constexpr int kMaxFoldGroups = 128;            // workgroups of four folding waves at most: they must leave the
                                                // compute units room for the chunks they wait for
 
-template <int G>
+template <int G, int MAXB>
 __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float eps, int m, int KU, int budget,
                             int window) {
     constexpr int CPG = 64 / G;                // chunks per group
+    constexpr int kScan = (MAXB * G + 63) / 64;   // registers that hold one value per (block, head) of a chunk
     const int lane = threadIdx.x & 63, g = lane % G, jl = lane / G;     // my head, my chunk of the group
     StreamCtl *ctl = &ws.ctl[s];
     const int ctx = stream_ctx(kv, s);
     const int N = (ctx + kPage - 1) / kPage;
     const unsigned long long *agg = ws.agg + (size_t)s * ws.max_chunks * G;
+    const int32_t *lse_ready = ws.lse_ready + (size_t)s * ws.max_chunks;
     // chunks that may ever be folded: all of them, or those a fixed budget of blocks covers (the limit in the
     // progress word is for the readers of keys and may be tighter: see stop_bound)
     const int nch = ((budget > 0 ? min(N, budget) : N) + KU - 1) / KU;
@@ -221,6 +226,7 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
         // the group's words, and (in flight at the same time) how many streams have closed
         const int ci = base + jl;
         const unsigned long long v = (ci < nch) ? ld_relaxed(&agg[(size_t)ci * G + g]) : kAggSentinel;
+        const int ready = ld_relaxed(&lse_ready[min(ci, nch - 1)]);      // are the chunk's block values there?
         const int closed_now = uniform(ld_relaxed(&ws.header[kClosedStreams]));
         const unsigned long long pub = __ballot(v != kAggSentinel);
         const int k = ((pub == ~0ull) ? 64 : (__ffsll((long long)~pub) - 1)) / G;     // leading published chunks
@@ -258,44 +264,56 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
             if (cand == 0ull) { j = k; break; }
             const int js = (__ffsll((long long)cand) - 1) / G;          // the first chunk in which an open head passes
             const bool scan = (cand >> (js * G + g)) & 1ull;            // does mine?
+            // its blocks' values follow its words by a store round trip: if this look came in between, fold up to it
+            if (__shfl(ready, js * G) == 0) { j = js; break; }
             {
-                // That chunk's blocks' L_b are fetched 64 at a time, lane = (block, head); a prefix scan over the
-                // blocks of each head (steps of G lanes), on top of the state after the chunk before, gives AS_acc
-                // and AS_min after every block, hence P_acc at every position; the first tested position that
-                // passes is the stop.
+                // That chunk's blocks' L_b, lane = (block, head), 64 values to a register and all registers asked for at
+                // once; a prefix scan over the blocks of each head (steps of G lanes; the registers' scans side by side),
+                // on top of the state after the chunk before, gives AS_acc and AS_min after every block, hence P_acc at
+                // every position; the first tested position that passes is the stop.
                 const int cb0 = (base + js) * KU, cn_end = min(cb0 + KU, N);
                 const float *lb = ws.block_lse + ((size_t)s * kv.max_blocks + cb0) * G;
                 const int cnt = (cn_end - cb0) * G;
                 float cl = js == 0 ? Cacc : __shfl(L, (js - 1) * G + g);
                 float cm = js == 0 ? Cmin : __shfl(M, (js - 1) * G + g);
                 bool found = false;
+                float pl[kScan], pm[kScan];
+#pragma unroll
+                for (int u = 0; u < kScan; ++u) pm[u] = pl[u] = ld_relaxed(&lb[min(64 * u + lane, cnt - 1)]);
 #pragma nounroll
-                for (int x0 = 0; x0 < cnt; x0 += 64) {
-                    const bool valid = x0 + lane < cnt;
-                    float pl = ld_relaxed(&lb[min(x0 + lane, cnt - 1)]);
-                    float pm = pl;
-#pragma nounroll
-                    for (int d = G; d < 64; d <<= 1) {
-                        const float ol = __shfl_up(pl, d), om = __shfl_up(pm, d);
-                        if (lane >= d) { pl = lse2(ol, pl); pm = fminf(om, pm); }
+                for (int d = G; d < 64; d <<= 1) {
+#pragma unroll
+                    for (int u = 0; u < kScan; ++u) {
+                        const float ol = __shfl_up(pl[u], d), om = __shfl_up(pm[u], d);
+                        if (lane >= d) { pl[u] = lse2(ol, pl[u]); pm[u] = fminf(om, pm[u]); }
                     }
-                    const float fl = lse2(cl, pl), fm = fminf(cm, pm);
-                    const int nn = cb0 + (x0 + lane) / G + 1;
+                }
+#pragma unroll
+                for (int u = 0; u < kScan; ++u) {
+                    const float fl = lse2(cl, pl[u]), fm = fminf(cm, pm[u]);
+                    const int nn = cb0 + (64 * u + lane) / G + 1;
                     const float P = p_acc(fl, fm, N - nn);
-                    const unsigned long long hits = __ballot(valid && (nn % m == 0 || nn == N) && P > eps) & head_lanes;
+                    const unsigned long long hits =
+                        __ballot(64 * u + lane < cnt && (nn % m == 0 || nn == N) && P > eps) & head_lanes;
                     const int src = hits ? (__ffsll((long long)hits) - 1) : 0;
                     const float Pf = __shfl(P, src);
                     if (scan && !found && hits) {
-                        stop = ((unsigned long long)(cb0 + (x0 + src) / G + 1) << 32) | __float_as_uint(Pf);
+                        stop = ((unsigned long long)(cb0 + (64 * u + src) / G + 1) << 32) | __float_as_uint(Pf);
                         found = true;
                     }
-                    const int last = (min(64, cnt - x0) / G - 1) * G + g;   // my head's last block of this batch
-                    cl = __shfl(fl, last);
-                    cm = __shfl(fm, last);
+                    cl = __shfl(fl, 64 - G + g);       // my head's state after this register's last block
+                    cm = __shfl(fm, 64 - G + g);
                 }
             }
             j = js + 1;
             if (__ballot(stop == ~0ull) == 0ull) { finished = true; break; }
+        }
+        if (base + j == walked && !finished) {
+            if (++looks > kFoldPatience) {
+                if (lane == 0) set_error(ws.header, PSA_DEVERR_STALLED);
+                break;
+            }
+            continue;
         }
         walked = base + j;
         if (walked >= nch) finished = true;
@@ -331,8 +349,8 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
 
 // Physical page and valid-token count of each ranked block of chunk c of stream s -> LDS.  Issued before
 // the workgroup looks at the window, so that the loads overlap its wait.
-template <int G, bool STAGE>
-__device__ __forceinline__ void stage_pages(SelectShared<G, STAGE> &sh, const KvView &kv, const DecodeWs &ws, int CB,
+template <int G, int MAXB>
+__device__ __forceinline__ void stage_pages(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int CB,
                                             int s, int c) {
     const int tid = threadIdx.x;
     const int ctx = stream_ctx(kv, s);
@@ -351,8 +369,8 @@ __device__ __forceinline__ void stage_pages(SelectShared<G, STAGE> &sh, const Kv
 // B operand of the QK^T product of stream s -> LDS (every wave of the workgroup reads it from there): column
 // n = lane%16 is query head n (zero beyond the group), k block kq = lane/16; for step kk the lane holds
 // channels 8*(4*kk + kq) .. +7.  (The caller's next barrier makes it visible.)
-template <int G, bool STAGE>
-__device__ __forceinline__ void load_queries(SelectShared<G, STAGE> &sh, const KvView &kv, const uint8_t *__restrict__ q,
+template <int G, int MAXB>
+__device__ __forceinline__ void load_queries(SelectShared<G, MAXB> &sh, const KvView &kv, const uint8_t *__restrict__ q,
                                              int s) {
     const int tid = threadIdx.x;
     if (tid < 256) {
@@ -368,8 +386,8 @@ __device__ __forceinline__ void load_queries(SelectShared<G, STAGE> &sh, const K
 // Key work of one workgroup: chunk c of stream s.  Ends with the chunk published (wave 0 stores the chunk's
 // words, which the stream's folding wave is looking at).
 // =================================================================================================
-template <int DT, int G, bool STAGE>
-__device__ void process_chunk(SelectShared<G, STAGE> &sh, const KvView &kv, const uint8_t *__restrict__ q,
+template <int DT, int G, int MAXB>
+__device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const uint8_t *__restrict__ q,
                               const DecodeWs &ws, float eps, int m, int CB, int budget, int s, int c) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = s % kv.num_kv_heads;
@@ -389,10 +407,8 @@ __device__ void process_chunk(SelectShared<G, STAGE> &sh, const KvView &kv, cons
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) qb[kk] = sh.qb[kk][lane];
     float *lg_out = ws.logits + row0 * (kPage * G);
-    lds_barrier();
-    // ---- keys: wave w takes blocks [16*it + 4*w, +4), each a 4 KiB slice read as four coalesced 1 KiB
-    //      loads.  A operand of the product: row n = token n of the block, same channel assignment as
-    //      the queries. ----------------------------------------------------------------------------
+    // ---- keys: wave w takes blocks w, w + 4, ..., each a 4 KiB slice read as four coalesced 1 KiB loads.  A operand
+    //      of the product: row n = token n of the block, same channel assignment as the queries. ------------------
     auto issue = [&](int i, uint4 (&dst)[4]) {
         const uint8_t *kp = key_slice(kv, sh.page[i], h) + lane * 16;
 #pragma unroll
@@ -420,64 +436,76 @@ __device__ void process_chunk(SelectShared<G, STAGE> &sh, const KvView &kv, cons
         for (int kk = 0; kk < 4; ++kk) acc = mfma_16x16x32<DT>(a[kk], qb[kk], acc);
         // the lane now holds head n's logits of tokens kq, 4+kq, 8+kq, 12+kq
         const int valid = sh.valid[i];
-        float sc[4];
+        f32x4_t sc;
 #pragma unroll
         for (int x = 0; x < 4; ++x) sc[x] = (4 * x + kq < valid) ? acc[x] * kScaleLog2 : -INFINITY;
-        if (n < G) {
-            if constexpr (STAGE) *reinterpret_cast<f32x4_t *>(&sh.lg[i][n][4 * kq]) = f32x4_t{sc[0], sc[1], sc[2], sc[3]};
-            else store_stream(lg_out + ((size_t)i * G + n) * kPage + 4 * kq, f32x4_t{sc[0], sc[1], sc[2], sc[3]});
-        }
-        // the block's log-sum-exp for head n, across the 4 token groups
-        float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        float sum = (exp2_fast(sc[0] - mx) + exp2_fast(sc[1] - mx)) +
-                    (exp2_fast(sc[2] - mx) + exp2_fast(sc[3] - mx));
-        sum += __shfl_xor(sum, 16);
-        sum += __shfl_xor(sum, 32);
-        if (lane < G) sh.Lb[i][lane] = mx + log2_fast(sum);
+        if (n < G) *reinterpret_cast<f32x4_t *>(&sh.lg[i][n][4 * kq]) = sc;
     };
     constexpr int kWaves = kSelectThreads / 64;
-    if (nblk == 2 * kWaves * kBatch) {
-        // A whole chunk of 32 blocks, eight per wave: a rolling window.  Four slices are in flight; the oldest is
+    if (nblk == 32) {
+        // A whole chunk of 32 blocks, eight per wave: a rolling window.  kBatch slices are in flight; the oldest is
         // worked on and its registers go to the next load at once, so the wave never stands with nothing in
-        // flight between rounds (a quarter of a round is arithmetic, LDS and stores).
+        // flight between rounds.
         uint4 ka[kBatch][4];
-        auto block_of = [&](int k) { return (k / kBatch) * (kWaves * kBatch) + wave * kBatch + (k % kBatch); };
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) issue(block_of(u), ka[u]);
+        for (int u = 0; u < kBatch; ++u) issue(wave + kWaves * u, ka[u]);
 #pragma unroll
-        for (int k = 0; k < 2 * kBatch; ++k) {
-            consume(block_of(k), ka[k % kBatch]);
-            if (k + kBatch < 2 * kBatch) issue(block_of(k + kBatch), ka[k % kBatch]);
+        for (int k = 0; k < 32 / kWaves; ++k) {
+            consume(wave + kWaves * k, ka[k % kBatch]);
+            if (k + kBatch < 32 / kWaves) issue(wave + kWaves * (k + kBatch), ka[k % kBatch]);
         }
     } else {
-        for (int i0 = wave * kBatch; i0 < nblk; i0 += kWaves * kBatch) {
+        for (int i0 = wave; i0 < nblk; i0 += kWaves * kBatch) {
             uint4 ka[kBatch][4];
 #pragma unroll
             for (int u = 0; u < kBatch; ++u)
-                if (i0 + u < nblk) issue(i0 + u, ka[u]);
+                if (i0 + kWaves * u < nblk) issue(i0 + kWaves * u, ka[u]);
 #pragma unroll
             for (int u = 0; u < kBatch; ++u)
-                if (i0 + u < nblk) consume(i0 + u, ka[u]);
+                if (i0 + kWaves * u < nblk) consume(i0 + kWaves * u, ka[u]);
         }
     }
     lds_barrier();
-    // The chunk's logits leave as one contiguous piece (8 KiB at G = 4), every thread 16 bytes at a time.  Writes
-    // are what this kernel pays most for per byte (the stored logits are 6 % of what it moves and a tenth of its
-    // time); in whole, neighbouring cache lines they cost a third less than as 256 bytes per block in between
-    // the loads.
-    if constexpr (STAGE) {
-        const float *staged = &sh.lg[0][0][0];
-        for (int idx = tid * 4; idx < nblk * G * kPage; idx += kSelectThreads * 4)
-            store_stream(lg_out + idx, *reinterpret_cast<const f32x4_t *>(staged + idx));
+    // ---- the blocks' log-sum-exp L_b per head, from the logits in LDS, all threads of the workgroup at once: kQuad
+    //      threads per (block, head) row of sixteen, each its share of the row's four quarters.  (Reduced slice by
+    //      slice inside the loop, the chain of lane exchanges, exponentials and a logarithm took longer than the
+    //      slice's product, eight times one after the other.)
+    {
+        constexpr int kQuad = G >= 8 ? 1 : (G == 4 ? 2 : 4), kShare = 4 / kQuad;
+        for (int x = tid; x < nblk * G * kQuad; x += kSelectThreads) {
+            const int row = x / kQuad, part = x % kQuad;
+            const f32x4_t *src = reinterpret_cast<const f32x4_t *>(&sh.lg[0][0][0]) + row * 4 + part * kShare;
+            f32x4_t v[kShare];
+            float mx = -INFINITY;
+#pragma unroll
+            for (int y = 0; y < kShare; ++y) {
+                v[y] = src[y];
+                mx = fmaxf(mx, fmaxf(fmaxf(v[y][0], v[y][1]), fmaxf(v[y][2], v[y][3])));
+            }
+            if constexpr (kQuad >= 2) mx = fmaxf(mx, dpp_f<0xB1>(mx));
+            if constexpr (kQuad == 4) mx = fmaxf(mx, dpp_f<0x4E>(mx));
+            float e[kShare];
+#pragma unroll
+            for (int y = 0; y < kShare; ++y)
+                e[y] = (exp2_fast(v[y][0] - mx) + exp2_fast(v[y][1] - mx)) + (exp2_fast(v[y][2] - mx) + exp2_fast(v[y][3] - mx));
+            float sum = e[0];
+            if constexpr (kShare == 2) sum = e[0] + e[1];
+            if constexpr (kShare == 4) sum = (e[0] + e[1]) + (e[2] + e[3]);
+            if constexpr (kQuad >= 2) sum += dpp_f<0xB1>(sum);
+            if constexpr (kQuad == 4) sum += dpp_f<0x4E>(sum);
+            if (part == 0) sh.Lb[row / G][row % G] = mx + log2_fast(sum);
+        }
     }
-    // the blocks' L_b, for the fold's block-by-block pass; complete before the chunk is published
-    for (int idx = tid; idx < nblk * G; idx += kSelectThreads)
-        st_relaxed(&ws.block_lse[row0 * G + idx], sh.Lb[idx / G][idx % G]);
-    stores_done();
     lds_barrier();
-    if (wave != 0) return;
+    // The chunk's logits leave as one contiguous piece (8 KiB at G = 4), every thread of waves 1-3 16 bytes at a time,
+    // while wave 0 publishes.  Writes are what this kernel pays most for per byte; in whole, neighbouring cache lines
+    // they cost a third less than as 256 bytes per block in between the loads.
+    if (wave != 0) {
+        const float *staged = &sh.lg[0][0][0];
+        for (int idx = (tid - 64) * 4; idx < nblk * G * kPage; idx += (kSelectThreads - 64) * 4)
+            store_stream(lg_out + idx, *reinterpret_cast<const f32x4_t *>(staged + idx));
+        return;
+    }
 
     // ---- publish: the chunk's (log-sum-exp, minimum) of its blocks' L_b per head.  Lane = (slot, head):
     //      64/G slots each fold every (64/G)-th block, then a butterfly over the slots -- a fixed tree, so
@@ -501,6 +529,11 @@ __device__ void process_chunk(SelectShared<G, STAGE> &sh, const KvView &kv, cons
     if (w == kAggSentinel) w = kAggSentinel - 1;     // a NaN pair that happens to look like "not published"
     // The G words need no order among themselves: the fold takes a chunk only when it sees all of them.
     if (lane < G) st_relaxed(&ws.agg[((size_t)s * ws.max_chunks + c) * G + lane], w);
+    // The blocks' L_b follow, and a word that says they are there: the fold needs them only in a chunk in which a head
+    // stops, so the frontier does not wait for these stores to complete (1 to 3 us while the memory system is busy).
+    for (int idx = lane; idx < nblk * G; idx += 64) st_relaxed(&ws.block_lse[row0 * G + idx], sh.Lb[idx / G][idx % G]);
+    stores_done();
+    if (lane == 0) st_relaxed(&ws.lse_ready[(size_t)s * ws.max_chunks + c], 1);
 }
 
 // =================================================================================================
@@ -508,17 +541,17 @@ __device__ void process_chunk(SelectShared<G, STAGE> &sh, const KvView &kv, cons
 // workgroups are the folds, one wave per stream (they start first and stay until their streams close); then one
 // workgroup per (chunk, stream), streams fastest.
 // =================================================================================================
-template <int DT, int G, bool STAGE>
-__global__ __launch_bounds__(kSelectThreads, 4) void select_kernel(KvView kv, const uint8_t *__restrict__ q,
+template <int DT, int G, int MAXB>
+__global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select_kernel(KvView kv, const uint8_t *__restrict__ q,
                                                                 DecodeWs ws, float eps, int m, int CB, int budget,
                                                                 int window, int spin_limit,
                                                                 const int32_t *depth_hint) {
-    __shared__ SelectShared<G, STAGE> sh;
+    __shared__ SelectShared<G, MAXB> sh;
     const int S = kv.batch * kv.num_kv_heads;
     const int folders = min((S + 3) / 4, kMaxFoldGroups);
     if ((int)blockIdx.x < folders) {
         for (int fs = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6); fs < S; fs += 4 * folders)
-            fold_stream<G>(kv, ws, fs, eps, m, CB, budget, window > 0 ? window : 1);
+            fold_stream<G, MAXB>(kv, ws, fs, eps, m, CB, budget, window > 0 ? window : 1);
         return;
     }
     // Workgroups go to the chip's eight partitions by index, round robin.  With the streams in the same order in
@@ -535,8 +568,8 @@ __global__ __launch_bounds__(kSelectThreads, 4) void select_kernel(KvView kv, co
     if (threadIdx.x == 0) kp_first = ld_relaxed(&ws.ctl[s].key_progress);
     const int N = (stream_ctx(kv, s) + kPage - 1) / kPage;
     if (c * CB >= N) return;
-    load_queries<G, STAGE>(sh, kv, q, s);
-    stage_pages<G, STAGE>(sh, kv, ws, CB, s, c);
+    load_queries<G, MAXB>(sh, kv, q, s);
+    stage_pages<G, MAXB>(sh, kv, ws, CB, s, c);
     if (threadIdx.x == 0) sh.kp0 = kp_first;
     lds_barrier();
     if (c >= (int)(sh.kp0 >> 32)) return;          // closed, out of reach, or beyond a block budget
@@ -571,7 +604,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void select_kernel(KvView kv, co
     lds_barrier();
     if (!sh.go) return;
     if (threadIdx.x == 0) atomicAdd(&ws.ctl[s].k_blocks, min(CB, N - c * CB));     // traffic accounting
-    process_chunk<DT, G, STAGE>(sh, kv, q, ws, eps, m, CB, budget, s, c);
+    process_chunk<DT, G, MAXB>(sh, kv, q, ws, eps, m, CB, budget, s, c);
 }
 
 template <int DT, int G>
@@ -580,11 +613,11 @@ static hipError_t launch_select_t(const KvView &kv, const void *q, const DecodeW
     const unsigned S = (unsigned)(kv.batch * kv.num_kv_heads);
     const unsigned folders = (S + 3) / 4 < (unsigned)kMaxFoldGroups ? (S + 3) / 4 : (unsigned)kMaxFoldGroups;
     const unsigned grid = folders + S * (unsigned)plan.max_chunks;
-    if (plan.chunk_blocks <= kStagedBlocks)
-        select_kernel<DT, G, true><<<grid, kSelectThreads, 0, st>>>(kv, (const uint8_t *)q, ws, eps, m, plan.chunk_blocks,
+    if (plan.chunk_blocks <= 32)
+        select_kernel<DT, G, 32><<<grid, kSelectThreads, 0, st>>>(kv, (const uint8_t *)q, ws, eps, m, plan.chunk_blocks,
                                                          budget, plan.window_chunks, plan.spin_limit, plan.depth_hint);
     else
-        select_kernel<DT, G, false><<<grid, kSelectThreads, 0, st>>>(kv, (const uint8_t *)q, ws, eps, m, plan.chunk_blocks,
+        select_kernel<DT, G, kMaxChunkBlocks><<<grid, kSelectThreads, 0, st>>>(kv, (const uint8_t *)q, ws, eps, m, plan.chunk_blocks,
                                                           budget, plan.window_chunks, plan.spin_limit, plan.depth_hint);
     return hipGetLastError();
 }
