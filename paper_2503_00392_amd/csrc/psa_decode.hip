@@ -44,7 +44,7 @@ DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t) {
 }
 
 struct WsLayout {
-    size_t header, ctl, scores, order, ranked_page, agg, lse_ready, block_lse, logits, partial, value_items, total;
+    size_t header, ctl, scores, order, ranked_page, agg, block_lse, logits, partial, value_items, total;
 };
 
 static WsLayout layout(const psa_kv_desc *d, const DecodePlan &p) {
@@ -59,7 +59,6 @@ static WsLayout layout(const psa_kv_desc *d, const DecodePlan &p) {
     L.order = at;       at = align_up(at + S * MB * 4, 256);
     L.ranked_page = at; at = align_up(at + S * MB * 4, 256);
     L.agg = at;         at = align_up(at + S * p.max_chunks * G * 8, 256);
-    L.lse_ready = at;   at = align_up(at + S * p.max_chunks * 4, 256);
     L.block_lse = at;   at = align_up(at + S * MB * G * 4, 256);
     L.logits = at;      at = align_up(at + S * MB * kPage * G * 4, 256);
     L.partial = at;     at = align_up(at + S * p.max_chunks * G * kPartialStride * 4, 256);
@@ -82,7 +81,6 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     ws.order = reinterpret_cast<int32_t *>(base + L.order);
     ws.ranked_page = reinterpret_cast<int32_t *>(base + L.ranked_page);
     ws.agg = reinterpret_cast<unsigned long long *>(base + L.agg);
-    ws.lse_ready = reinterpret_cast<int32_t *>(base + L.lse_ready);
     ws.block_lse = reinterpret_cast<float *>(base + L.block_lse);
     ws.logits = reinterpret_cast<float *>(base + L.logits);
     ws.partial = reinterpret_cast<float *>(base + L.partial);

@@ -118,11 +118,13 @@ struct alignas(128) StreamCtl {
     int32_t pad0[30];
     // line 1: counters
     int32_t k_blocks;   // key slices loaded (traffic accounting)
-    int32_t pad1[31];
+    int32_t pad1[15];
+    uint32_t lse_ready_hi[16];   // as lse_ready, chunks 512 and up (chunks of eight blocks make 1024 of them)
     // line 2: the fold's result, written when it closes the stream
     unsigned long long stop[8];  // per head: (n << 32) | float bits of P_acc at the stop; ~0 = not stopped
-    int32_t pad2[16];
+    uint32_t lse_ready[16];      // bit c: chunk c's block_lse values are in memory (set after its words in agg)
 };
+static_assert(sizeof(StreamCtl) == 384, "three cache lines");
 
 struct DecodeWs {
     int32_t *header;        // [128]: word 1 = sticky error bits; word kValueCount (a cache line of its own) =
@@ -133,7 +135,6 @@ struct DecodeWs {
     int32_t *order;         // [S][max_blocks]  ranked logical blocks
     int32_t *ranked_page;   // [S][max_blocks]  physical page of each ranked block
     unsigned long long *agg;  // [S][max_chunks][G]  (L_chunk, Lmin_chunk) as two floats, or kAggSentinel
-    int32_t *lse_ready;     // [S][max_chunks]  1 = the chunk's block_lse values are in memory (written after agg)
     float *block_lse;       // [S][max_blocks][G]  log2 of each ranked block's AS (Algorithm 1 line 10)
     float *logits;          // [S][max_blocks][G][16]  scaled logits (log2 units) by ranked block; position
                             // 4*r + j of a (block, head) row holds token 4*j + r
@@ -143,6 +144,10 @@ struct DecodeWs {
     int32_t max_chunks;     // chunks per stream at most
     int32_t max_units;      // = max_chunks (stride of `partial`)
 };
+// The word of a stream's control block that holds the lse_ready bit of chunk c (bit c % 32), c < 1024.
+__device__ __forceinline__ uint32_t *lse_ready_word(StreamCtl *ctl, int c) {
+    return c < 512 ? &ctl->lse_ready[c >> 5] : &ctl->lse_ready_hi[(c >> 5) & 15];
+}
 constexpr int kPartialStride = 132;  // M, l, pad, pad, acc[128]
 constexpr int kMaxWindowChunks = 256; // chunks read beyond the fold's frontier, at most
 constexpr int kValueCount = 32;      // index of the value-item counter in the workspace header

@@ -139,8 +139,7 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
     if (part == 0) {
         unsigned long long *a = ws.agg + (size_t)s * ws.max_chunks * G;
         for (int i = tid; i < ws.max_chunks * G; i += nthreads) a[i] = kAggSentinel;      // nothing published yet
-        int32_t *lr = ws.lse_ready + (size_t)s * ws.max_chunks;
-        for (int i = tid; i < ws.max_chunks; i += nthreads) lr[i] = 0;
+        if (tid < 32) *lse_ready_word(&ws.ctl[s], tid * 32) = 0u;
     }
 
     // LDS carve-up of the bucket path: 10*Np bytes + scratch

@@ -23,7 +23,7 @@
 //      cores (heads beyond G are zero columns), keeps them in LDS until the chunk is done, and then reduces
 //      every block's log-sum-exp L_b (= log AS of line 10) at once;
 //   4. publishes the chunk's (log-sum-exp, minimum) of L_b per head as one 64-bit word per head, then the L_b
-//      themselves, then a word that says they are there; the logits leave for the workspace meanwhile.
+//      themselves, then a bit that says they are there; the logits leave for the workspace meanwhile.
 // From the last key to the published word a chunk takes 0.9 us, and 3.2 us from its first load on an idle chip; with
 // the reduction inside the loop over the slices, and the words after all stores, these were 1.0 us (3 us under load)
 // and 4.6 us.  A call at 32K tokens, batch 8, went from 112.5 to 109.7 us, at 4K, batch 31, from 58.1 to 54.1.
@@ -58,6 +58,9 @@ __device__ __forceinline__ int ld_relaxed(const int32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ unsigned long long ld_relaxed(const unsigned long long *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t ld_relaxed(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ float ld_relaxed(const float *p) {
@@ -205,7 +208,6 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
     const int ctx = stream_ctx(kv, s);
     const int N = (ctx + kPage - 1) / kPage;
     const unsigned long long *agg = ws.agg + (size_t)s * ws.max_chunks * G;
-    const int32_t *lse_ready = ws.lse_ready + (size_t)s * ws.max_chunks;
     // chunks that may ever be folded: all of them, or those a fixed budget of blocks covers (the limit in the
     // progress word is for the readers of keys and may be tighter: see stop_bound)
     const int nch = ((budget > 0 ? min(N, budget) : N) + KU - 1) / KU;
@@ -226,7 +228,8 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
         // the group's words, and (in flight at the same time) how many streams have closed
         const int ci = base + jl;
         const unsigned long long v = (ci < nch) ? ld_relaxed(&agg[(size_t)ci * G + g]) : kAggSentinel;
-        const int ready = ld_relaxed(&lse_ready[min(ci, nch - 1)]);      // are the chunk's block values there?
+        const int cr = min(ci, nch - 1);
+        const uint32_t ready = (ld_relaxed(lse_ready_word(ctl, cr)) >> (cr & 31)) & 1u;   // are the chunk's block values there?
         const int closed_now = uniform(ld_relaxed(&ws.header[kClosedStreams]));
         const unsigned long long pub = __ballot(v != kAggSentinel);
         const int k = ((pub == ~0ull) ? 64 : (__ffsll((long long)~pub) - 1)) / G;     // leading published chunks
@@ -265,7 +268,7 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
             const int js = (__ffsll((long long)cand) - 1) / G;          // the first chunk in which an open head passes
             const bool scan = (cand >> (js * G + g)) & 1ull;            // does mine?
             // its blocks' values follow its words by a store round trip: if this look came in between, fold up to it
-            if (__shfl(ready, js * G) == 0) { j = js; break; }
+            if (__shfl((int)ready, js * G) == 0) { j = js; break; }
             {
                 // That chunk's blocks' L_b, lane = (block, head), 64 values to a register and all registers asked for at
                 // once; a prefix scan over the blocks of each head (steps of G lanes; the registers' scans side by side),
@@ -529,11 +532,12 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
     if (w == kAggSentinel) w = kAggSentinel - 1;     // a NaN pair that happens to look like "not published"
     // The G words need no order among themselves: the fold takes a chunk only when it sees all of them.
     if (lane < G) st_relaxed(&ws.agg[((size_t)s * ws.max_chunks + c) * G + lane], w);
-    // The blocks' L_b follow, and a word that says they are there: the fold needs them only in a chunk in which a head
+    // The blocks' L_b follow, and a bit that says they are there: the fold needs them only in a chunk in which a head
     // stops, so the frontier does not wait for these stores to complete (1 to 3 us while the memory system is busy).
     for (int idx = lane; idx < nblk * G; idx += 64) st_relaxed(&ws.block_lse[row0 * G + idx], sh.Lb[idx / G][idx % G]);
     stores_done();
-    if (lane == 0) st_relaxed(&ws.lse_ready[(size_t)s * ws.max_chunks + c], 1);
+    if (lane == 0)
+        __hip_atomic_fetch_or(lse_ready_word(&ws.ctl[s], c), 1u << (c & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // =================================================================================================
