@@ -64,4 +64,30 @@ __device__ __forceinline__ uint32_t pick_word(const uint4 &v, int w) {
     return w == 0 ? v.x : (w == 1 ? v.y : (w == 2 ? v.z : v.w));
 }
 
+// One block of the value product.  x: head cl's logits of the four tokens whose value rows the lane holds; the weights
+// p = exp(x - ref), nothing where the lane's head does not use the block (`on`; tokens beyond the request hold -inf), are
+// added to l and, as a sum of two 16-bit halves, multiplied into acc: D[head][channel] += P[head][token] V[token][channel].
+template <int DT>
+__device__ __forceinline__ void add_values(f32x4_t (&acc)[8], float &l, const Slice &v, f32x4_t x, bool on, float ref) {
+    float p[4];
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        p[j] = on ? exp2_fast(x[j] - ref) : 0.0f;
+        split16<DT>(p[j], hi[j], lo[j]);
+    }
+    l += (p[0] + p[1]) + (p[2] + p[3]);
+    const uint2 a_hi = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
+    const uint2 a_lo = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const uint32_t w0 = pick_word(v.r[0], t >> 1), w1 = pick_word(v.r[1], t >> 1);
+        const uint32_t w2 = pick_word(v.r[2], t >> 1), w3 = pick_word(v.r[3], t >> 1);
+        const uint2 b = (t & 1) ? make_uint2((w0 >> 16) | (w1 & 0xffff0000u), (w2 >> 16) | (w3 & 0xffff0000u))
+                                : make_uint2((w0 & 0xffffu) | (w1 << 16), (w2 & 0xffffu) | (w3 << 16));
+        acc[t] = mfma_16x16x16<DT>(a_hi, b, acc[t]);
+        acc[t] = mfma_16x16x16<DT>(a_lo, b, acc[t]);
+    }
+}
+
 }  // namespace psa

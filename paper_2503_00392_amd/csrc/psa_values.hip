@@ -11,22 +11,36 @@
 //   finalize_kernel  merges a head's chunks (the online-softmax merge of line 11, all at once):
 //                    out_g = sum over the chunks of the head's own prefix of the partial numerators,
 //                    over the sum of the partial exp-sums, both rescaled to one reference maximum
+#include <type_traits>
+#include <utility>
+
 #include "psa_attend.h"
 #include "psa_host.h"
 
 namespace psa {
 
-// Stop of head g of a stream: (n, P_acc) as the selection kernel left it, n = N when it never stopped.
-__device__ __forceinline__ int head_stop(const StreamCtl *ctl, int g, int N) {
-    const unsigned long long st = ctl->stop[g];
+// Blocks a head uses, from its stop (n, P_acc) as the selection kernel left it: n, or N when it never stopped.
+__device__ __forceinline__ int stop_blocks(unsigned long long st, int N) {
     return (st != ~0ull && (int)(st >> 32) <= N) ? (int)(st >> 32) : N;
 }
+
+// f(0), f(1), ... f(N - 1) with the index as a constant: arrays indexed with it stay in registers.
+template <class F, int... I>
+__device__ __forceinline__ void static_for(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) { static_for(f, std::make_integer_sequence<int, N>{}); }
 
 // =================================================================================================
 // One workgroup per entry of the work list the selection kernel left (value unit = chunk c of stream s);
 // the grid is sized for the most there can be, and a workgroup beyond the list's end returns after one
-// load.  256 threads.  The four waves stream independently: wave w takes blocks w, w+4, ... of the unit,
-// two value slices (8 KiB) in flight at a time, and nothing is shared until the final merge.
+// round trip.  256 threads.  The four waves stream independently: wave w takes blocks w, w+4, ... of the unit,
+// four value slices (16 KiB) in flight at a time, and nothing is shared until the final merge.
+// What bounds it: with many units the memory (5.8 TB/s, logits included, on 16 requests of 64K tokens whose blocks are
+// nearly all selected, 374 us before and after), with few the chain of loads before the first slice: entry, then
+// everything about the unit at once, then slices.  (With the stops, the block values and the slices asked for one
+// after the other, two slices in flight, 12 requests of up to 24K tokens took 12.1 us; 9.2 now.)  Four slices need 152
+// registers, hence three workgroups per CU; three slices at four workgroups spilled and were slower throughout, as was
+// a grid of resident workgroups that walks the list (31.4 us against 26.4 at 32K tokens, batch 8).
 //   weights   p = exp(logit - L), L = per head the largest log-sum-exp of a block the head uses (the selection
 //             kernel left one per block): a reference every wave knows beforehand, so nothing is rescaled
 //             on the way and the four waves' sums simply add up.  (p <= 1, and the largest weight is at least
@@ -40,109 +54,106 @@ __device__ __forceinline__ int head_stop(const StreamCtl *ctl, int g, int N) {
 //             8cl..8cl+7.
 // Output per unit and head: (L, sum of p, numerator[128]) for the final merge.
 // =================================================================================================
-constexpr int kValueDepth = 2;      // value slices a wave keeps in flight
+constexpr int kValueDepth = 4;      // value slices a wave keeps in flight
+constexpr int kUnitBlocks = 32;     // blocks of a unit in the default plan: the size with a fixed schedule
+
 template <int DT, int G>
-__global__ __launch_bounds__(256, 4) void attend_kernel(KvView kv, DecodeWs ws, int CB) {
-    __shared__ float st_acc[4][G][kHeadDim];
+__global__ __launch_bounds__(256, 3) void attend_kernel(KvView kv, DecodeWs ws, int CB) {
+    __shared__ __attribute__((aligned(16))) float st_acc[4][G][kHeadDim];
     __shared__ float st_l[4][G];
     __shared__ float st_ref[G];
-    if ((int)blockIdx.x >= ws.header[kValueCount]) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), rg = lane >> 4, cl = lane & 15;
+    // (the list's length and the entry are asked for together; an entry beyond the length is not used)
     const int item = ws.value_items[blockIdx.x];
-    const int s = item / ws.max_chunks, c = item % ws.max_chunks;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rg = lane >> 4, cl = lane & 15;
-    const int h = s % kv.num_kv_heads;
-    int ctx = kv.ctx_lens[s / kv.num_kv_heads];
-    ctx = ctx < 0 ? 0 : (ctx > kv.max_blocks * kPage ? kv.max_blocks * kPage : ctx);
-    const int N = (ctx + kPage - 1) / kPage;
-    const int start = c * CB;
-    if (start >= N) return;
-    const int nblk = min(CB, N - start);
-    const StreamCtl *ctl = &ws.ctl[s];
-    // blocks of this chunk each head uses: those before its stop
-    int maxcnt = 0, mycnt = 0;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int cg = min(nblk, max(0, head_stop(ctl, g, N) - start));
-        maxcnt = max(maxcnt, cg);
-        if (g == cl) mycnt = cg;
-    }
-    if (maxcnt == 0) return;    // no head of the group reaches this chunk
+    const int count = ws.header[kValueCount];
+    if ((int)blockIdx.x >= count) return;
+    const int s = __builtin_amdgcn_readfirstlane(item / ws.max_chunks), c = __builtin_amdgcn_readfirstlane(item % ws.max_chunks);
+    const int h = s % kv.num_kv_heads, start = c * CB;
     const size_t row0 = (size_t)s * kv.max_blocks + start;
-    // the wave's blocks are wave, wave + 4, ...: lane j fetches the page and the logical index of the j-th
-    const int jmax = (maxcnt - wave + 3) / 4;           // how many of them there are (may be <= 0)
-    int pg = 0, od = 0;
-    if (lane < jmax) {
-        pg = ws.ranked_page[row0 + wave + 4 * lane];
-        if (!(kv.slot_pool != nullptr && pg < 0)) pg = clamp_page_quiet(pg, kv.num_pages);   // (a page of the pool, or ~slot)
-        od = ws.order[row0 + wave + 4 * lane];
-    }
-    // Reference exponent per head: the largest block log-sum-exp among the blocks the head uses (log2 units; the
-    // selection kernel left one per block and head).  Lane = (block, head) pairs, 64 / G blocks per load, then a
-    // butterfly over the lanes of a head: every lane l ends with the reference of head l % G, so lane (rg, cl < G)
-    // holds head cl's.  Every wave computes the same bits.
-    float Lc = -INFINITY;
-    {
-        const float *bl = ws.block_lse + row0 * G;
-        const int g = lane % G;
-        int cg = 0;
+    const int room = min(CB, kv.max_blocks - start);          // rows of the tables that belong to the unit
+    // Everything about the unit is asked for at once: the heads' stops, the length, the wave's blocks (wave, wave + 4,
+    // ...: lane j has the page and the logical index of the j-th), the blocks' log-sum-exps.
+    const unsigned long long stop = ws.ctl[s].stop[lane % G];
+    const int mine = min(wave + 4 * (lane & 15), room - 1);
+    int pg = ws.ranked_page[row0 + mine];
+    const int od = ws.order[row0 + mine];
+    constexpr int kRef = G * kUnitBlocks / 64 > 0 ? G * kUnitBlocks / 64 : 1;     // loads for the values of 32 blocks
+    const float *bl = ws.block_lse + row0 * G;
+    float lse[kRef];
 #pragma unroll
-        for (int x = 0; x < G; ++x) cg = (x == g) ? min(nblk, max(0, head_stop(ctl, x, N) - start)) : cg;
-        for (int i = lane / G; i < maxcnt; i += 64 / G) {
-            const float v = bl[(size_t)i * G + g];
-            if (i < cg) Lc = fmaxf(Lc, v);
-        }
+    for (int k = 0; k < kRef; ++k) lse[k] = bl[min(64 * k + lane, room * G - 1)];
+    const int ctx = ctx_clamped_quiet(kv, s / kv.num_kv_heads);
+    const int N = (ctx + kPage - 1) / kPage;
+    const int nblk = min(CB, N - start);
+    // blocks of this chunk that head lane % G uses: those before its stop; and the most any head of the group uses
+    const int mycnt = min(nblk, max(0, stop_blocks(stop, N) - start));
+    int maxcnt = mycnt;
 #pragma unroll
-        for (int d = G; d < 64; d <<= 1) Lc = fmaxf(Lc, __shfl_xor(Lc, d));
-    }
-    const float *lg = ws.logits + row0 * (kPage * G) + (size_t)(cl < G ? cl : 0) * kPage + 4 * rg;
+    for (int d = 1; d < G; d <<= 1) maxcnt = max(maxcnt, __shfl_xor(maxcnt, d));
+    maxcnt = __builtin_amdgcn_readfirstlane(maxcnt);
+    if (maxcnt <= 0) return;    // no head of the group reaches this chunk
+    const int jmax = (maxcnt - wave + 3) / 4;           // blocks of this wave (may be <= 0)
+    if (!(kv.slot_pool != nullptr && pg < 0)) pg = clamp_page_quiet(pg, kv.num_pages);   // (a page of the pool, or ~slot)
+    const float *lg = ws.logits + row0 * (kPage * G);
+    const int lg_lane = (cl < G ? cl : 0) * kPage + 4 * rg;
 
+    Slice v[kValueDepth];
+    f32x4_t x[kValueDepth];
+    auto issue = [&](int j, auto slot) __attribute__((always_inline)) {
+        constexpr int u = decltype(slot)::value;
+        v[u] = load_slice(value_slice(kv, __builtin_amdgcn_readlane(pg, j), h), lane);
+        x[u] = load_stream(lg + (wave + 4 * j) * (kPage * G) + lg_lane);
+    };
     f32x4_t acc[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    float l = 0.0f;
-    for (int j0 = 0; j0 < jmax; j0 += kValueDepth) {
-        Slice v[kValueDepth];
-        f32x4_t x[kValueDepth];
-        int valid[kValueDepth], blk[kValueDepth];
+    float l = 0.0f, Lc = -INFINITY;
+    // Reference exponent per head: the largest block log-sum-exp among the blocks the head uses (log2 units).  Lane =
+    // (block, head) pairs, 64 / G blocks per load, then a butterfly over the lanes of a head: every lane l ends with
+    // the reference of head l % G, so lane (rg, cl < G) holds head cl's.  Every wave computes the same bits.
+    auto reference = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < kValueDepth; ++u) {    // (index clamped, loads made anyway: no branch around a load)
-            const int j = min(j0 + u, jmax - 1);
-            blk[u] = wave + 4 * j;
-            v[u] = load_slice(value_slice(kv, __shfl(pg, j), h), lane);
-            x[u] = load_stream(lg + (size_t)blk[u] * (kPage * G));
-            valid[u] = min(kPage, ctx - __shfl(od, j) * kPage);
+        for (int k = 0; k < kRef; ++k)
+            if ((64 * k + lane) / G < mycnt && 64 * k + lane < kUnitBlocks * G) Lc = fmaxf(Lc, lse[k]);
+        for (int i = kUnitBlocks + lane / G; i < mycnt; i += 64 / G) Lc = fmaxf(Lc, bl[(size_t)i * G + lane % G]);
+#pragma unroll
+        for (int d = G; d < 64; d <<= 1) Lc = fmaxf(Lc, __shfl_xor(Lc, d));
+    };
+    auto consume = [&](int j, auto slot) __attribute__((always_inline)) {
+        constexpr int u = decltype(slot)::value;
+        const int blk = wave + 4 * j;
+        if (kv.staging != nullptr) {               // (second tier: see stage_key_slice)
+            const int loc = __builtin_amdgcn_readlane(pg, j);
+            if (loc >= 0) stage_value_slice(kv, loc, h, v[u].r, lane);
         }
-#pragma unroll
-        for (int u = 0; u < kValueDepth; ++u) {
-            if (j0 + u < jmax) {
-                if (kv.staging != nullptr) {               // (second tier: see stage_key_slice)
-                    const int loc = __shfl(pg, j0 + u);
-                    if (loc >= 0) stage_value_slice(kv, loc, h, v[u].r, lane);
+        const int valid = ctx - __builtin_amdgcn_readlane(od, j) * kPage;
+        if (valid < kPage) zero_invalid_rows(v[u], rg, valid);
+        // tokens beyond `valid` hold -inf logits; blocks beyond the head's stop, and heads beyond the
+        // group, weigh nothing
+        const bool on = cl < G && blk < mycnt;
+        add_values<DT>(acc, l, v[u], x[u], on, Lc);      // (a head that uses no block of the unit is never `on`)
+    };
+    if (maxcnt == kUnitBlocks) {
+        // Eight blocks for every wave: a rolling window, the oldest slice is worked on and its registers go to the next
+        // load at once.
+        static_for<kValueDepth>([&](auto u) { issue(u, u); });
+        reference();
+        static_for<kUnitBlocks / 4>([&](auto j) {
+            const std::integral_constant<int, j % kValueDepth> slot;
+            consume(j, slot);
+            if (j + kValueDepth < kUnitBlocks / 4) issue(j + kValueDepth, slot);
+            __builtin_amdgcn_sched_barrier(0);           // (steps that are interleaved run out of registers)
+        });
+    } else {
+        static_for<kValueDepth>([&](auto u) { if (u < jmax) issue(u, u); });      // (rows beyond jmax may hold anything)
+        reference();
+        for (int j0 = 0; j0 < jmax; j0 += kValueDepth) {
+            static_for<kValueDepth>([&](auto u) {
+                if (j0 + u < jmax) {
+                    consume(j0 + u, u);
+                    if (j0 + kValueDepth + u < jmax) issue(j0 + kValueDepth + u, u);
                 }
-                if (valid[u] < kPage) zero_invalid_rows(v[u], rg, valid[u]);
-                // tokens beyond `valid` hold -inf logits; blocks beyond the head's stop, and heads beyond the
-                // group, weigh nothing
-                const bool on = cl < G && blk[u] < mycnt;
-                float pw[4] = {x[u][0], x[u][1], x[u][2], x[u][3]};
-                uint32_t hi[4], lo[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    pw[j] = on ? exp2_fast(pw[j] - Lc) : 0.0f;      // (a head that uses no block of the unit is never `on`)
-                    split16<DT>(pw[j], hi[j], lo[j]);
-                }
-                l += (pw[0] + pw[1]) + (pw[2] + pw[3]);
-                const uint2 a_hi = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-                const uint2 a_lo = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const uint32_t w0 = pick_word(v[u].r[0], t >> 1), w1 = pick_word(v[u].r[1], t >> 1);
-                    const uint32_t w2 = pick_word(v[u].r[2], t >> 1), w3 = pick_word(v[u].r[3], t >> 1);
-                    const uint2 b = (t & 1) ? make_uint2((w0 >> 16) | (w1 & 0xffff0000u), (w2 >> 16) | (w3 & 0xffff0000u))
-                                            : make_uint2((w0 & 0xffffu) | (w1 << 16), (w2 & 0xffffu) | (w3 << 16));
-                    acc[t] = mfma_16x16x16<DT>(a_hi, b, acc[t]);
-                    acc[t] = mfma_16x16x16<DT>(a_lo, b, acc[t]);
-                }
-            }
+            });
         }
     }
     // the exp-sum over the four row groups, then the four waves through LDS (one reference: plain sums)
@@ -152,13 +163,14 @@ __global__ __launch_bounds__(256, 4) void attend_kernel(KvView kv, DecodeWs ws, 
     for (int r = 0; r < 4; ++r) {
         const int g = 4 * rg + r;
         if (g < G) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) st_acc[wave][g][cl * 8 + t] = acc[t][r];
+            f32x4_t *row = reinterpret_cast<f32x4_t *>(&st_acc[wave][g][cl * 8]);
+            row[0] = f32x4_t{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+            row[1] = f32x4_t{acc[4][r], acc[5][r], acc[6][r], acc[7][r]};
         }
     }
     if (rg == 0 && cl < G) st_l[wave][cl] = l;
     if (wave == 0 && rg == 0 && cl < G) st_ref[cl] = Lc;
-    __syncthreads();
+    lds_barrier();
     float *dst = ws.partial + ((size_t)s * ws.max_units + c) * G * kPartialStride;
     for (int idx = tid; idx < G * kHeadDim; idx += 256) {
         const int g = idx / kHeadDim, ch = idx % kHeadDim;
