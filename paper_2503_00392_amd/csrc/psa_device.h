@@ -14,6 +14,7 @@ constexpr int kRowBytes = 256;    // one token's key (or value) for one head
 constexpr int kSliceBytes = 4096; // one (page, KV head) K or V slice
 constexpr int kMetaBytes = 512;   // one (page, KV head) metadata record: min[128] | max[128]
 constexpr int kMaxBlocks = 8192;  // ranking limit per request (128K tokens)
+constexpr int kSoloBlocks = 256;  // blocks of a request the one-launch path takes (4K tokens)
 constexpr int kMaxChunkBlocks = 64;   // key chunk and value unit, in blocks, at most
 
 // 1/sqrt(128) * log2(e): logits are carried in log2 units so that exp is one v_exp_f32.
@@ -239,6 +240,41 @@ __device__ __forceinline__ float row_max16(float v) {
     return v;
 }
 
+// Unsigned minimum and maximum over a DPP row, and inclusive sums along it (row_shr feeds zeros in at the row's start).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+__device__ __forceinline__ uint32_t row_min16(uint32_t v) {
+    v = min(v, dpp_u<0xB1>(v));
+    v = min(v, dpp_u<0x4E>(v));
+    v = min(v, dpp_u<0x141>(v));
+    return min(v, dpp_u<0x140>(v));
+}
+__device__ __forceinline__ uint32_t row_max16(uint32_t v) {
+    v = max(v, dpp_u<0xB1>(v));
+    v = max(v, dpp_u<0x4E>(v));
+    v = max(v, dpp_u<0x141>(v));
+    return max(v, dpp_u<0x140>(v));
+}
+__device__ __forceinline__ uint32_t row_sum16(uint32_t v) {
+    v += dpp_u<0xB1>(v);
+    v += dpp_u<0x4E>(v);
+    v += dpp_u<0x141>(v);
+    return v + dpp_u<0x140>(v);
+}
+// Inclusive prefix sum over the wave: along the rows, then the totals of the rows before.
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
+    v += dpp_u<0x111>(v);
+    v += dpp_u<0x112>(v);
+    v += dpp_u<0x114>(v);
+    v += dpp_u<0x118>(v);
+    const int row = (threadIdx.x & 63) >> 4;
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 15), r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 31),
+                   r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
+    return v + (row > 0 ? r0 : 0u) + (row > 1 ? r1 : 0u) + (row > 2 ? r2 : 0u);
+}
+
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float log2_fast(float x) { return __builtin_amdgcn_logf(x); }
 
@@ -247,6 +283,14 @@ __device__ __forceinline__ float lse2(float a, float b) {
     float hi = fmaxf(a, b), lo = fminf(a, b);
     if (hi == -INFINITY) return -INFINITY;
     return hi + log2_fast(1.0f + exp2_fast(lo - hi));
+}
+
+// Ranking key of a score: smaller key = larger score; -0 ranks as +0.
+__device__ __forceinline__ uint32_t descending_key(float score) {
+    uint32_t u = __float_as_uint(score);
+    if (u == 0x80000000u) u = 0u;
+    const uint32_t asc = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return ~asc;
 }
 
 // Workgroup barrier that orders LDS traffic only: unlike __syncthreads() it does not wait for the

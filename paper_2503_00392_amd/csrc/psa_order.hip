@@ -2,7 +2,7 @@
 // smaller logical block.  One workgroup per stream, everything in LDS and registers.
 //
 // Main path: a monotone bucket map + exact in-bucket ranking.
-//   1. every thread holds 8 keys (order-preserving 32-bit images of the scores, inverted so that a
+//   1. every thread holds K keys (order-preserving 32-bit images of the scores, inverted so that a
 //      smaller key is a larger score) and the workgroup reduces their minimum and maximum;
 //   2. bucket = floor((largest score - score) * scale) is monotone in the score, so bucket order is
 //      rank order; an LDS counter per bucket and a workgroup scan give each bucket its output range;
@@ -14,15 +14,23 @@
 // There are as many buckets as element slots, so a bucket holds about one element.  If one bucket
 // holds more than kBucketLimit elements
 // (near-identical scores) the quadratic in-bucket count would be slow, and the workgroup falls back
-// to a bitonic network over 64-bit (key, index) words: compare distances below 8 stay in registers,
-// below 512 go through wave shuffles, the rest through LDS.  Both paths give the same total order.
+// to a bitonic network over 64-bit (key, index) words, eight to a thread: compare distances below 8 stay in
+// registers, below 512 go through wave shuffles, the rest through LDS.  Both paths give the same total order.
 //
-// With few streams several workgroups share one stream: each builds the bucket table (cheap) and
-// ranks its share of the elements (the expensive part, bound by LDS traffic).
+// With few streams several workgroups share one stream: each counts all elements (cheap) and lays out and
+// ranks its share of them (the expensive part, bound by LDS traffic).
+//
+// What bounds it is the chain of short steps between barriers, not data: hence two keys to a thread up to 2048 blocks,
+// four up to 4096, eight beyond (a workgroup has 1024 threads at most); reductions along rows of lanes; counters of
+// 16 bits, so that two workgroups of 8192 blocks fit a compute unit; and the request's row of the block table read at
+// the start, so that the gather at the end finds it in the cache.  With eight keys to a thread throughout, 32-bit
+// counters and reductions through LDS exchanges it took 12.1 us at 2048 blocks (64 streams), 7.5 now; 17.9 -> 13.9 at
+// 8192 (32 streams), 40 -> 26 with 512 streams; where the time went: scores 0.9 us, range 0.5, counters 0.6, scan 0.4,
+// shares 0.5, layout 0.4, count 0.9, gather and stores 0.4, the rest is the launch.
 //
 // The kernel also resets the stream's control block and chunk words for the progressive kernel and
 // reports out-of-range contexts and block-table entries.
-// grid (S), Np/8 threads, 10*Np + 512 bytes of dynamic LDS; Np = power of two >= max(512, max_blocks).
+// grid (workgroups per stream, S), Np / K threads, 8*Np + 512 bytes of dynamic LDS; Np = power of two >= max(512, max_blocks).
 #include <limits.h>
 
 #include "psa_host.h"
@@ -38,22 +46,17 @@ __device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v,
     return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
 }
 
-// Smaller key = larger score; -0 ranks as +0.
-__device__ __forceinline__ uint32_t descending_key(float score) {
-    uint32_t u = __float_as_uint(score);
-    if (u == 0x80000000u) u = 0u;
-    const uint32_t asc = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    return ~asc;
-}
-
 // The score a key stands for (with -0 read as +0).
 __device__ __forceinline__ float score_of_key(uint32_t key) {
     const uint32_t asc = ~key;
     return __uint_as_float((asc & 0x80000000u) ? (asc & 0x7FFFFFFFu) : ~asc);
 }
 
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
+
 __device__ void bitonic_sort(unsigned long long (&e)[8], unsigned long long *lds_keys, int Np, int tid,
                              int nthreads) {
+    // (nthreads = Np / 8 threads hold keys; the others of the workgroup only meet them at the barriers)
     for (int k = 2; k <= Np; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
             if (j >= 8) {
@@ -61,10 +64,11 @@ __device__ void bitonic_sort(unsigned long long (&e)[8], unsigned long long *lds
                 unsigned long long o[8];
                 if (tj >= 64) {
 #pragma unroll
-                    for (int x = 0; x < 8; ++x) lds_keys[x * nthreads + tid] = e[x];
+                    for (int x = 0; x < 8; ++x)
+                        if (tid < nthreads) lds_keys[x * nthreads + tid] = e[x];
                     __syncthreads();
 #pragma unroll
-                    for (int x = 0; x < 8; ++x) o[x] = lds_keys[x * nthreads + (tid ^ tj)];
+                    for (int x = 0; x < 8; ++x) o[x] = tid < nthreads ? lds_keys[x * nthreads + (tid ^ tj)] : 0ull;
                     __syncthreads();
                 } else {
 #pragma unroll
@@ -102,7 +106,9 @@ __device__ void bitonic_sort(unsigned long long (&e)[8], unsigned long long *lds
     }
 }
 
-__global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int G, int KU, int budget_blocks, int Np,
+// K: keys per thread.
+template <int K>
+__global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, int G, int KU, int budget_blocks, int Np,
                                                       int force_bitonic,
                                                       int32_t *__restrict__ order_out) {
     extern __shared__ unsigned long long lds_raw[];
@@ -114,18 +120,27 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
     // where the row's length allows)
     const float *sc = ws.scores + (size_t)s * kv.max_blocks;
     const int32_t *table = kv.block_table + (size_t)r * kv.max_blocks;
-    float scv[8];
-    if ((kv.max_blocks & 7) == 0 && kv.max_blocks >= 8) {
-        const float4 *v4 = reinterpret_cast<const float4 *>(sc + min(tid * 8, kv.max_blocks - 8));   // (clamped: no branch)
-        const float4 a = v4[0], b = v4[1];
-        scv[0] = a.x; scv[1] = a.y; scv[2] = a.z; scv[3] = a.w; scv[4] = b.x; scv[5] = b.y; scv[6] = b.z; scv[7] = b.w;
+    float scv[K];
+    if (kv.max_blocks % K == 0) {
+        typedef float vec_t __attribute__((ext_vector_type(K < 4 ? K : 4)));
+        const vec_t *v = reinterpret_cast<const vec_t *>(sc + min(tid * K, kv.max_blocks - K));   // (clamped: no branch)
+#pragma unroll
+        for (int j = 0; j < K; ++j) scv[j] = v[j / 4][j % 4];
     } else {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) scv[j] = sc[min(tid * 8 + j, max(kv.max_blocks - 1, 0))];
+        for (int j = 0; j < K; ++j) scv[j] = sc[min(tid * K + j, kv.max_blocks - 1)];
     }
+    // ... and the request's row of the block table: whoever ranks a block gathers its page at the end, from the cache then
+    bool bad_page = false;
+    int page_at[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) page_at[j] = table[min(tid + j * nthreads, kv.max_blocks - 1)];
     // the scoring kernel clamps silently (it clears the error word); out-of-range inputs are reported here
     const int ctx = (tid == 0 && blockIdx.x == 0) ? ctx_clamped(kv, r, ws.header) : ctx_clamped_quiet(kv, r);
     const int N = (ctx + kPage - 1) / kPage;
+#pragma unroll
+    for (int j = 0; j < K; ++j) bad_page |= tid + j * nthreads < N && (unsigned)page_at[j] >= (unsigned)kv.num_pages;
+    if (bad_page) set_error(ws.header, PSA_DEVERR_PAGE_RANGE);
     // ---- reset of the progressive kernel's per-stream state ------------------------------------
     if (tid == 0 && part == 0) {
         StreamCtl *c = &ws.ctl[s];
@@ -142,18 +157,19 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
         if (tid < 32) *lse_ready_word(&ws.ctl[s], tid * 32) = 0u;
     }
 
-    // LDS carve-up of the bucket path: 10*Np bytes + scratch
+    // LDS carve-up of the bucket path: 8*Np bytes + scratch
     uint32_t *skey = reinterpret_cast<uint32_t *>(lds_raw);                   // [Np] key by slot
-    uint32_t *cnt = skey + Np;                                                // [Np + 4] bucket counts, then bases
-    uint16_t *slot = reinterpret_cast<uint16_t *>(cnt + Np + 4);              // [Np] logical block by slot
+    uint32_t *cnt = skey + Np;                                                // [Np / 2 + 4] bucket counts, then bases, two to a word
+    uint16_t *base = reinterpret_cast<uint16_t *>(cnt);                       // base[b] .. base[b+1]: bucket b's slots
+    uint16_t *slot = reinterpret_cast<uint16_t *>(cnt + Np / 2 + 4);          // [Np] logical block by slot
     uint32_t *scratch = reinterpret_cast<uint32_t *>(slot + Np);              // 64 words
     const int NB = Np;                                                        // one bucket per element slot
 
-    uint32_t key[8];
+    uint32_t key[K];
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int p = tid * 8 + j;
+    for (int j = 0; j < K; ++j) {
+        const int p = tid * K + j;
         key[j] = 0xFFFFFFFFu;
         if (p < N) {
             key[j] = descending_key(scv[j]);
@@ -161,17 +177,19 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
             kmax = max(kmax, key[j]);
         }
     }
-    *reinterpret_cast<uint4 *>(cnt + tid * 8) = make_uint4(0, 0, 0, 0);
-    *reinterpret_cast<uint4 *>(cnt + tid * 8 + 4) = make_uint4(0, 0, 0, 0);
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, d));
-        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, d));
-    }
+    for (int j = 0; j < K / 2; ++j) cnt[tid * (K / 2) + j] = 0u;
+    if (tid < 16) scratch[48 + tid] = 0u;          // [48]: a bucket is too full; [56 + p]: where workgroup p's share begins
+    // smallest and largest key: along the rows of lanes, over the wave's four rows, over the waves through LDS
+    kmin = row_min16(kmin);
+    kmax = row_max16(kmax);
+    kmin = min(min(lane_value(kmin, 0), lane_value(kmin, 16)), min(lane_value(kmin, 32), lane_value(kmin, 48)));
+    kmax = max(max(lane_value(kmax, 0), lane_value(kmax, 16)), max(lane_value(kmax, 32), lane_value(kmax, 48)));
     if (lane == 0) { scratch[wave] = kmin; scratch[16 + wave] = kmax; }
     lds_barrier();
-    kmin = 0xFFFFFFFFu; kmax = 0u;
-    for (int w = 0; w < nwaves; ++w) { kmin = min(kmin, scratch[w]); kmax = max(kmax, scratch[16 + w]); }
+    const int wl = lane & 15;                      // (at most sixteen waves)
+    kmin = row_min16(wl < nwaves ? scratch[wl] : 0xFFFFFFFFu);
+    kmax = row_max16(wl < nwaves ? scratch[16 + wl] : 0u);
     // Buckets are equal steps of the SCORE between the largest and the smallest one (not of its bit
     // pattern, which would crowd scores of small magnitude or mixed sign into a few buckets).  Every
     // operation below is monotone in the score, so a block that ranks before another never lands in a
@@ -179,82 +197,66 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
     const float smax = score_of_key(kmin), span = smax - score_of_key(kmax);
     const bool span_ok = span > 0.0f && span < INFINITY;       // false also for NaN: the fallback ranks then
     const float scale = span_ok ? (float)NB / span : 0.0f;
-    int bkt[8], arrival[8];
+    int bkt[K], arrival[K];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < K; ++j) {
         bkt[j] = 0; arrival[j] = 0;
-        if (tid * 8 + j < N) {
+        if (tid * K + j < N) {
             const float fb = (smax - score_of_key(key[j])) * scale;
             int b = fb >= (float)(NB - 1) ? NB - 1 : (int)fb;     // (a NaN compares false and converts to 0)
             b = b < 0 ? 0 : b;
             bkt[j] = b;
-            arrival[j] = (int)atomicAdd(&cnt[b], 1u);
+            arrival[j] = (int)((atomicAdd(&cnt[b >> 1], 1u << (16 * (b & 1))) >> (16 * (b & 1))) & 0xffffu);
+            if (arrival[j] >= kBucketLimit) scratch[48] = 1u;
         }
     }
     lds_barrier();
-    // exclusive scan of the bucket counts (8 buckets per thread) and the largest bucket
-    uint32_t c8[8];
-    {
-        const uint4 a = *reinterpret_cast<const uint4 *>(cnt + tid * 8), b4 = *reinterpret_cast<const uint4 *>(cnt + tid * 8 + 4);
-        c8[0] = a.x; c8[1] = a.y; c8[2] = a.z; c8[3] = a.w; c8[4] = b4.x; c8[5] = b4.y; c8[6] = b4.z; c8[7] = b4.w;
-    }
-    uint32_t mine = 0, biggest = 0, e8[8];
+    // exclusive scan of the bucket counts (K buckets per thread)
+    uint32_t c8[K];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) { e8[j] = mine; mine += c8[j]; biggest = max(biggest, c8[j]); }
-    uint32_t incl = mine;
+    for (int j = 0; j < K; ++j) c8[j] = (cnt[tid * (K / 2) + j / 2] >> (16 * (j & 1))) & 0xffffu;
+    uint32_t mine = 0, e8[K];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_up((int)incl, d);
-        if (lane >= d) incl += o;
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) biggest = max(biggest, (uint32_t)__shfl_xor((int)biggest, d));
+    for (int j = 0; j < K; ++j) { e8[j] = mine; mine += c8[j]; }
+    const uint32_t incl = wave_prefix_sum(mine);
     if (lane == 63) scratch[32 + wave] = incl;
-    if (lane == 0) scratch[48 + wave] = biggest;
     lds_barrier();
-    uint32_t wave_off = 0, max_bucket = 0;
-    for (int w = 0; w < nwaves; ++w) {
-        if (w < wave) wave_off += scratch[32 + w];
-        max_bucket = max(max_bucket, scratch[48 + w]);
-    }
+    const bool too_full = scratch[48] != 0u;
+    const uint32_t t0 = row_sum16(wl < wave ? scratch[32 + wl] : 0u) + incl - mine;      // my first bucket's base
+#pragma unroll
+    for (int j = 0; j < K / 2; ++j) cnt[tid * (K / 2) + j] = (t0 + e8[2 * j]) | ((t0 + e8[2 * j + 1]) << 16);
+    if (tid == 0) base[NB] = (uint16_t)N;
     // A workgroup's share of the ranking work is a run of whole buckets (the workgroups of a stream agree on the
     // buckets' ranges, not on the arrangement inside a bucket): share p starts with the first bucket that begins at
     // or after slot p * N / nparts.  Whoever holds the bucket that slot falls into notes where the next one begins.
-    const int share = (N + nparts - 1) / nparts;
-    if (tid < 8) scratch[64 + tid] = 0u;               // (share 0 starts at slot 0; nparts <= 4)
-    {
-        const uint32_t t0 = wave_off + incl - mine;
-        *reinterpret_cast<uint4 *>(cnt + tid * 8) = make_uint4(t0 + e8[0], t0 + e8[1], t0 + e8[2], t0 + e8[3]);
-        *reinterpret_cast<uint4 *>(cnt + tid * 8 + 4) = make_uint4(t0 + e8[4], t0 + e8[5], t0 + e8[6], t0 + e8[7]);
-        if (tid == 0) cnt[NB] = (uint32_t)N;
-    }
-    lds_barrier();
-    {
-        const uint32_t t0 = wave_off + incl - mine;
+    const int share = (N + nparts - 1) / nparts;       // (share 0 starts at slot 0; nparts <= 4)
+    for (int p = 1; p < nparts; ++p) {
+        const uint32_t target = (uint32_t)min(p * share, N);
+        if (t0 < target && target <= t0 + mine) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t lo = t0 + e8[j], hi = lo + c8[j];          // bucket's slots [lo, hi)
-            for (int p = 1; p < nparts; ++p) {
-                const uint32_t target = (uint32_t)min(p * share, N);
-                if (lo < target && target <= hi) scratch[64 + p] = hi;
+            for (int j = 0; j < K; ++j) {
+                const uint32_t lo = t0 + e8[j], hi = lo + c8[j];          // bucket's slots [lo, hi)
+                if (lo < target && target <= hi) scratch[56 + p] = hi;
             }
         }
     }
     lds_barrier();
-    const uint32_t *base = cnt;                                               // base[b] .. base[b+1]: bucket b's slots
 
     int32_t *ord = ws.order + (size_t)s * kv.max_blocks;
     int32_t *rpage = ws.ranked_page + (size_t)s * kv.max_blocks;
     int32_t *oout = order_out ? order_out + (size_t)s * kv.max_blocks : nullptr;
 
-    if (max_bucket <= (uint32_t)kBucketLimit && !force_bitonic) {
-        // every workgroup of the stream builds the whole slot table: the elements of a bucket side by side, in
+    if (!too_full && !force_bitonic) {
+        // every workgroup of the stream builds its share of the slot table: the elements of a bucket side by side, in
         // arrival order (which may differ between the workgroups; the exact count below does not depend on it) ...
+        const int first = (int)scratch[56 + part];
+        const int last = part == nparts - 1 ? N : (int)scratch[56 + part + 1];
+        const int mine = last - first;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (tid * 8 + j < N) {
-                const uint32_t at = base[bkt[j]] + arrival[j];
-                slot[at] = (uint16_t)(tid * 8 + j);
+        for (int j = 0; j < K; ++j) {
+            const uint32_t at = (uint32_t)base[bkt[j]] + (uint32_t)arrival[j];
+            if (tid * K + j < N && at >= (uint32_t)first && at < (uint32_t)last) {
+                slot[at] = (uint16_t)(tid * K + j);
                 skey[at] = key[j];
             }
         }
@@ -264,9 +266,6 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
         // next, so a wave's reads of the bucket's members are mostly the same addresses.  The final rank of a
         // slot's element is its bucket's base plus the number of the bucket's members that precede it under
         // (key, block index).
-        const int first = (int)scratch[64 + part];
-        const int last = part == nparts - 1 ? N : (int)scratch[64 + part + 1];
-        const int mine = last - first;
         for (int q0 = 0; q0 < mine; q0 += 2 * nthreads) {         // two slots per thread and turn
             uint32_t mk[2], me[2], b0[2], cn[2], before[2], cmax = 0;
 #pragma unroll
@@ -280,7 +279,7 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
                     int b = fb >= (float)(NB - 1) ? NB - 1 : (int)fb;
                     b = b < 0 ? 0 : b;
                     b0[j] = base[b];
-                    cn[j] = base[b + 1] - b0[j];
+                    cn[j] = (uint32_t)base[b + 1] - b0[j];
                     cmax = max(cmax, cn[j]);
                 }
             }
@@ -303,7 +302,7 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
                 if (q0 + tid + j * nthreads < mine) {
                     const uint32_t rank = b0[j] + before[j];
                     ord[rank] = (int)me[j];
-                    rpage[rank] = clamp_page(table[me[j]], kv.num_pages, ws.header);
+                    rpage[rank] = clamp_page_quiet(table[me[j]], kv.num_pages);
                     if (oout) oout[rank] = (int)me[j];
                 }
             }
@@ -311,19 +310,20 @@ __global__ __launch_bounds__(1024) void order_kernel(KvView kv, DecodeWs ws, int
     } else if (part == 0) {     // (uniform over the workgroup) the fallback is one workgroup's work
         __syncthreads();   // everyone is done with the bucket arrays before LDS is reused
         unsigned long long e[8];
+        const int holders = Np / 8;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int p = tid * 8 + j;
-            e[j] = p < N ? (((unsigned long long)key[j] << 32) | (unsigned)p) : ~0ull;
+            e[j] = tid < holders && p < N ? (((unsigned long long)descending_key(sc[p]) << 32) | (unsigned)p) : ~0ull;
         }
-        bitonic_sort(e, lds_raw, Np, tid, nthreads);
+        bitonic_sort(e, lds_raw, Np, tid, holders);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int p = tid * 8 + j;
-            if (p < N) {
+            if (tid < holders && p < N) {
                 const int b = (int)(e[j] & 0xffffffffull);
                 ord[p] = b;
-                rpage[p] = clamp_page(table[b], kv.num_pages, ws.header);
+                rpage[p] = clamp_page_quiet(table[b], kv.num_pages);
                 if (oout) oout[p] = b;
             }
         }
@@ -337,20 +337,26 @@ hipError_t launch_order(const KvView &kv, const DecodeWs &ws, int G, const Decod
     const int S = kv.batch * kv.num_kv_heads;
     int Np = 512;
     while (Np < kv.max_blocks) Np <<= 1;
-    const size_t lds = (size_t)Np * 10 + 512;
-    static bool raised = false;       // more than 64 KiB of dynamic LDS has to be asked for once
-    if (!raised) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(order_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlocks * 10 + 512) != hipSuccess)
-            return hipErrorInvalidValue;
-        raised = true;
-    }
+    const size_t lds = (size_t)Np * 8 + 512;
     // with few streams, up to 4 workgroups share a stream's ranking
     int parts = 256 / (S > 0 ? S : 1);
     parts = parts < 1 ? 1 : (parts > 4 ? 4 : parts);
     if (Np < 2048) parts = 1;
-    order_kernel<<<dim3(parts, S), Np / 8, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget_blocks, Np, plan.force_bitonic,
-                                                      order_out);
+    const int budget = budget_blocks;
+    if (Np <= 2048) {
+        order_kernel<2><<<dim3(parts, S), Np / 2, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, order_out);
+    } else if (Np == 4096) {
+        order_kernel<4><<<dim3(parts, S), Np / 4, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, order_out);
+    } else {
+        static bool raised = false;       // more than 64 KiB of dynamic LDS has to be asked for once
+        if (!raised) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(order_kernel<8>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlocks * 8 + 512) != hipSuccess)
+                return hipErrorInvalidValue;
+            raised = true;
+        }
+        order_kernel<8><<<dim3(parts, S), Np / 8, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, order_out);
+    }
     return hipGetLastError();
 }
 
