@@ -44,19 +44,15 @@ __device__ __forceinline__ f32x4_t mfma_16x16x16(const uint2 &a, const uint2 &b,
     }
 }
 
-// p = hi + lo with both halves in the 16-bit type of the cache (round to nearest each): the bits of the two.
+// p = hi + lo with both halves in the 16-bit type of the cache (round to nearest each): the bits of the asked-for half.
 template <int DT>
-__device__ __forceinline__ void split16(float p, uint32_t &hi, uint32_t &lo) {
+__device__ __forceinline__ uint32_t half16(float p, bool low) {
     if constexpr (DT == 0) {
         const _Float16 h = (_Float16)p;
-        const _Float16 l = (_Float16)(p - (float)h);
-        hi = __builtin_bit_cast(uint16_t, h);
-        lo = __builtin_bit_cast(uint16_t, l);
+        return __builtin_bit_cast(uint16_t, low ? (_Float16)(p - (float)h) : h);
     } else {
-        const uint32_t u = __float_as_uint(p);
-        hi = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-        const uint32_t w = __float_as_uint(p - __uint_as_float(hi << 16));
-        lo = (w + 0x7fffu + ((w >> 16) & 1u)) >> 16;
+        const __bf16 h = (__bf16)p;
+        return __builtin_bit_cast(uint16_t, low ? (__bf16)(p - (float)h) : h);
     }
 }
 
@@ -64,29 +60,50 @@ __device__ __forceinline__ uint32_t pick_word(const uint4 &v, int w) {
     return w == 0 ? v.x : (w == 1 ? v.y : (w == 2 ? v.z : v.w));
 }
 
-// One block of the value product.  x: head cl's logits of the four tokens whose value rows the lane holds; the weights
-// p = exp(x - ref), nothing where the lane's head does not use the block (`on`; tokens beyond the request hold -inf), are
-// added to l and, as a sum of two 16-bit halves, multiplied into acc: D[head][channel] += P[head][token] V[token][channel].
+// One block of the value product: D[row][channel] += A[row][token] V[token][channel], eight 16x16x16 products, one per
+// channel of the lane's eight.  Row 2 g of A holds the upper 16-bit halves of head g's weights, row 2 g + 1 the lower
+// halves: the two share one product (sixteen rows are there anyway, and at most eight heads), lane (rg, *) ends up with
+// both halves of heads 2 rg and 2 rg + 1 in registers 0, 1 and 2, 3 of each accumulator, to be added at the end.
+// x: logits of head cl / 2 for the four tokens whose value rows the lane holds; the weights p = exp(x - ref), nothing
+// where the head does not use the block (`on`; tokens beyond the request hold -inf), are added to l.
 template <int DT>
-__device__ __forceinline__ void add_values(f32x4_t (&acc)[8], float &l, const Slice &v, f32x4_t x, bool on, float ref) {
-    float p[4];
-    uint32_t hi[4], lo[4];
+__device__ __forceinline__ void add_weighted(f32x4_t (&acc)[8], const Slice &v, const float (&p)[4], bool low) {
+    uint32_t w[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        p[j] = on ? exp2_fast(x[j] - ref) : 0.0f;
-        split16<DT>(p[j], hi[j], lo[j]);
-    }
-    l += (p[0] + p[1]) + (p[2] + p[3]);
-    const uint2 a_hi = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-    const uint2 a_lo = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+    for (int j = 0; j < 4; ++j) w[j] = half16<DT>(p[j], low);
+    const uint2 a = make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
         const uint32_t w0 = pick_word(v.r[0], t >> 1), w1 = pick_word(v.r[1], t >> 1);
         const uint32_t w2 = pick_word(v.r[2], t >> 1), w3 = pick_word(v.r[3], t >> 1);
         const uint2 b = (t & 1) ? make_uint2((w0 >> 16) | (w1 & 0xffff0000u), (w2 >> 16) | (w3 & 0xffff0000u))
                                 : make_uint2((w0 & 0xffffu) | (w1 << 16), (w2 & 0xffffu) | (w3 << 16));
-        acc[t] = mfma_16x16x16<DT>(a_hi, b, acc[t]);
-        acc[t] = mfma_16x16x16<DT>(a_lo, b, acc[t]);
+        acc[t] = mfma_16x16x16<DT>(a, b, acc[t]);
+    }
+}
+template <int DT>
+__device__ __forceinline__ void add_values(f32x4_t (&acc)[8], float &l, const Slice &v, f32x4_t x, bool on, float ref, bool low) {
+    float p[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[j] = on ? exp2_fast(x[j] - ref) : 0.0f;
+    l += (p[0] + p[1]) + (p[2] + p[3]);
+    add_weighted<DT>(acc, v, p, low);
+}
+// The lane's sums of heads 2 rg and 2 rg + 1 (those below G), channels 8 cl .. 8 cl + 7, to rows[head][channel].
+template <int G>
+__device__ __forceinline__ void store_heads(const f32x4_t (&acc)[8], float (*rows)[kHeadDim], int rg, int cl) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if (2 * rg + k < G) {
+            f32x4_t *row = reinterpret_cast<f32x4_t *>(&rows[2 * rg + k][cl * 8]);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                f32x4_t o;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[t] = acc[4 * y + t][2 * k] + acc[4 * y + t][2 * k + 1];
+                row[y] = o;
+            }
+        }
     }
 }
 

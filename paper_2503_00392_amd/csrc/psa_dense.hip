@@ -5,16 +5,16 @@
 
 namespace psa {
 
-constexpr int kDenseStride = 132;  // M, l, pad, pad, acc[128]
+constexpr int kDenseStride = 132;  // M, l, error bits (head 0), pad, acc[128]
 
 // grid (nsplit, S); 256 threads.  Wave w of the workgroup takes blocks b0+w, b0+w+4, ... and carries its own
 // online softmax over them, both products on the matrix cores:
 //   logits  D[token][head] = K[token][channel] Q[channel][head]: four 16x16x32 steps.  Row r of the A operand
 //           stands for token 4*(r%4) + r/4, so that lane (kq, n) = (lane/16, lane%16) ends up with the logits
-//           of head n for tokens kq, 4+kq, 8+kq, 12+kq -- the token rows its value loads fetch;
+//           of head n/2 for tokens kq, 4+kq, 8+kq, 12+kq -- the token rows its value loads fetch;
 //   values  D[head][channel] += P[head][token] V[token][channel]: eight 16x16x16 products per block (one per
-//           channel of the lane's eight), the weights split into two 16-bit halves; lane (kq, cl) accumulates
-//           heads 4kq..4kq+3 of channels 8cl..8cl+7.
+//           channel of the lane's eight), the weights split into two 16-bit halves in neighbouring rows (see
+//           add_weighted); lane (kq, cl) accumulates heads 2kq and 2kq+1 of channels 8cl..8cl+7.
 // The running maximum of a head is shared by the wave (two exchanges per block); the four waves are merged
 // once at the end.
 template <int DT, int G>
@@ -24,29 +24,41 @@ __global__ __launch_bounds__(256) void dense_split_kernel(KvView kv, const uint8
     const int s = blockIdx.y, split = blockIdx.x, nsplit = gridDim.x;
     const int r = s / kv.num_kv_heads, h = s % kv.num_kv_heads;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rg = lane >> 4, cl = lane & 15;
-    const int ctx = ctx_clamped(kv, r, header);
+    // the call's error word: cleared here, set by the merge kernel from what the workgroups found (a launch of its own for
+    // the clearing cost 5 us)
+    if (split == 0 && s == 0 && tid < 64) header[tid] = 0;
+    const int raw_ctx = kv.ctx_lens[r], ctx = ctx_clamped_quiet(kv, r);
+    int err = raw_ctx != ctx ? PSA_DEVERR_CTX_RANGE : 0;
     const int N = (ctx + kPage - 1) / kPage;
     // every request is cut into the same number of splits, each over its own length: ragged batches stay balanced
     const int bps = min(blocks_per_split, (N + nsplit - 1) / nsplit);
     const int b0 = split * bps;
     const int b1 = min(N, b0 + bps);
 
-    // B operand of the logits: column cl = head cl (zero beyond the group), channels 8*(4kk + rg) .. +7 in step kk
+    // B operand of the logits: columns 2 g and 2 g + 1 = head g (zero beyond the group), channels 8*(4kk + rg) .. +7 in
+    // step kk; the two lanes of a head supply the two halves of its weights (see add_weighted)
+    const int hd = cl >> 1;
     uint4 qb[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
         qb[kk] = make_uint4(0, 0, 0, 0);
-        if (cl < G) qb[kk] = ld16(q + ((size_t)(r * kv.num_q_heads + h * G + cl) * kHeadDim + (4 * kk + rg) * 8) * 2);
+        if (hd < G) qb[kk] = ld16(q + ((size_t)(r * kv.num_q_heads + h * G + hd) * kHeadDim + (4 * kk + rg) * 8) * 2);
     }
     const int row_token = 4 * (cl & 3) + (cl >> 2);      // the token this lane's row of the A operand stands for
-    float m = -INFINITY, l = 0.0f;                       // head cl: running maximum (whole wave), exp-sum (this row group)
+    float m = -INFINITY, l = 0.0f;                       // head hd: running maximum (whole wave), exp-sum (this row group)
     f32x4_t acc[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int32_t *table = kv.block_table + (size_t)r * kv.max_blocks;
-    for (int b = b0 + wave; b < b1; b += 4) {
-        const int page = clamp_page(table[b], kv.num_pages, header);
+    int pages = 0;                                       // lane j: page of the wave's block j of the next 64
+    for (int b = b0 + wave, i = 0; b < b1; b += 4, ++i) {
+        if ((i & 63) == 0) {
+            const int bl = b + 4 * lane, page = table[min(bl, b1 - 1)];
+            pages = clamp_page_quiet(page, kv.num_pages);
+            if (pages != page) err |= PSA_DEVERR_PAGE_RANGE;
+        }
+        const int page = __builtin_amdgcn_readlane(pages, i & 63);
         const size_t off = ((size_t)page * kv.num_kv_heads + h) * kSliceBytes;
         const uint8_t *kp = kv.k_pool + off + row_token * kRowBytes + rg * 16;
         uint4 ka[4];
@@ -72,46 +84,29 @@ __global__ __launch_bounds__(256) void dense_split_kernel(KvView kv, const uint8
         for (int j = 0; j < 4; ++j) p[j] = exp2_fast(sc[j] - mn);
         l = l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
         m = mn;
-        // the accumulators hold heads 4rg .. 4rg+3: rescale each by its head's factor (held by lane = head)
+        // the accumulators hold heads 2rg and 2rg + 1: rescale each by its head's factor, where a maximum has moved
+        if (__ballot(alpha != 1.0f)) {
+            const float a0 = __shfl(alpha, 4 * rg), a1 = __shfl(alpha, 4 * rg + 2);
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const float ax = __shfl(alpha, 4 * rg + x);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) acc[t][x] *= ax;
+            for (int t = 0; t < 8; ++t) { acc[t][0] *= a0; acc[t][1] *= a0; acc[t][2] *= a1; acc[t][3] *= a1; }
         }
-        uint32_t hi[4], lo[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) split16<DT>(p[j], hi[j], lo[j]);
-        const uint2 a_hi = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-        const uint2 a_lo = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const uint32_t w0 = pick_word(v.r[0], t >> 1), w1 = pick_word(v.r[1], t >> 1);
-            const uint32_t w2 = pick_word(v.r[2], t >> 1), w3 = pick_word(v.r[3], t >> 1);
-            const uint2 bv = (t & 1) ? make_uint2((w0 >> 16) | (w1 & 0xffff0000u), (w2 >> 16) | (w3 & 0xffff0000u))
-                                     : make_uint2((w0 & 0xffffu) | (w1 << 16), (w2 & 0xffffu) | (w3 << 16));
-            acc[t] = mfma_16x16x16<DT>(a_hi, bv, acc[t]);
-            acc[t] = mfma_16x16x16<DT>(a_lo, bv, acc[t]);
-        }
+        add_weighted<DT>(acc, v, p, cl & 1);
     }
     // the exp-sum over the four row groups
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
 
     // merge the 4 waves through LDS
-    __shared__ float st_acc[4][G][kHeadDim];
+    __shared__ __attribute__((aligned(16))) float st_acc[4][G][kHeadDim];
     __shared__ float st_m[4][G], st_l[4][G];
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const int g = 4 * rg + x;
-        if (g < G) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) st_acc[wave][g][cl * 8 + t] = acc[t][x];
-        }
-    }
-    if (rg == 0 && cl < G) { st_m[wave][cl] = m; st_l[wave][cl] = l; }
+    __shared__ int st_err[4];
+    store_heads<G>(acc, st_acc[wave], rg, cl);
+    if (rg == 0 && hd < G && !(cl & 1)) { st_m[wave][hd] = m; st_l[wave][hd] = l; }
+    const bool bad_ctx = __ballot(err & PSA_DEVERR_CTX_RANGE) != 0ull, bad_page = __ballot(err & PSA_DEVERR_PAGE_RANGE) != 0ull;
+    if (lane == 0) st_err[wave] = (bad_ctx ? PSA_DEVERR_CTX_RANGE : 0) | (bad_page ? PSA_DEVERR_PAGE_RANGE : 0);
     __syncthreads();
     float *dst = partial + ((size_t)s * nsplit + split) * G * kDenseStride;
+    if (tid == 0) dst[2] = __int_as_float(st_err[0] | st_err[1] | st_err[2] | st_err[3]);
     for (int idx = tid; idx < G * kHeadDim; idx += 256) {
         const int g = idx / kHeadDim, ch = idx % kHeadDim;
         float M = fmaxf(fmaxf(st_m[0][g], st_m[1][g]), fmaxf(st_m[2][g], st_m[3][g]));
@@ -134,7 +129,7 @@ __global__ __launch_bounds__(256) void dense_split_kernel(KvView kv, const uint8
 __global__ __launch_bounds__(512) void dense_combine_kernel(const float *__restrict__ partial, int nsplit,
                                                             int G, int num_kv_heads, int num_q_heads,
                                                             float *__restrict__ out,
-                                                            float *__restrict__ lse) {
+                                                            float *__restrict__ lse, int32_t *header) {
     __shared__ float red[8];
     __shared__ float wgt[1024];                 // rescale factor of every split (nsplit <= 1024)
     __shared__ float num_part[4][kHeadDim];
@@ -145,7 +140,14 @@ __global__ __launch_bounds__(512) void dense_combine_kernel(const float *__restr
     const float *src = partial + ((size_t)s * nsplit * G + g) * kDenseStride;
     const size_t stride = (size_t)G * kDenseStride;
     float M = -INFINITY;
-    for (int i = tid; i < nsplit; i += 512) { const float mi = src[i * stride]; wgt[i] = mi; M = fmaxf(M, mi); }
+    int err = 0;
+    for (int i = tid; i < nsplit; i += 512) {
+        const float mi = src[i * stride];
+        wgt[i] = mi;
+        M = fmaxf(M, mi);
+        if (g == 0) err |= __float_as_int(src[i * stride + 2]);
+    }
+    if (err) set_error(header, err);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) M = fmaxf(M, __shfl_xor(M, d));
     if ((tid & 63) == 0) red[tid >> 6] = M;
@@ -207,9 +209,8 @@ static hipError_t launch_dense_t(const KvView &kv, const void *q, float *out, fl
     float *partial = reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(ws) + 256);
     const int S = kv.batch * kv.num_kv_heads;
     const int bps = (kv.max_blocks + nsplit - 1) / nsplit;
-    clear_words_kernel<<<1, 64, 0, st>>>(header, 64);
     dense_split_kernel<DT, G><<<dim3(nsplit, S), 256, 0, st>>>(kv, (const uint8_t *)q, partial, bps, header);
-    dense_combine_kernel<<<S * G, 512, 0, st>>>(partial, nsplit, G, kv.num_kv_heads, kv.num_q_heads, out, lse);
+    dense_combine_kernel<<<S * G, 512, 0, st>>>(partial, nsplit, G, kv.num_kv_heads, kv.num_q_heads, out, lse, header);
     return hipGetLastError();
 }
 

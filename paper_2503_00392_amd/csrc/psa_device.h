@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "../../include/psa.h"
 
 namespace psa {
@@ -215,6 +218,12 @@ __device__ __forceinline__ float cvt_hi(uint32_t w) {
         return __builtin_bit_cast(float, w & 0xffff0000u);
     }
 }
+
+// f(0), f(1), ... f(N - 1) with the index as a constant: arrays indexed with it stay in registers.
+template <class F, int... I>
+__device__ __forceinline__ void static_for(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) { static_for(f, std::make_integer_sequence<int, N>{}); }
 
 // ---- cross-lane helpers ----------------------------------------------------------------------
 template <int CTRL>

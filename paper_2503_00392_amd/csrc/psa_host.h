@@ -35,11 +35,6 @@ inline KvView make_view(const psa_kv_desc *d) {
     return kv;
 }
 
-// Zero-fill by kernel (kept out of hipMemsetAsync so that callers may capture the calls in a graph).
-static __global__ void clear_words_kernel(int32_t *p, int n) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
-}
-
 // psa_dense.hip
 int dense_num_splits(const psa_kv_desc *d);
 size_t dense_workspace_bytes(const psa_kv_desc *d);
@@ -66,6 +61,7 @@ struct DecodePlan {
     int force_bitonic;
     const int32_t *depth_hint;   // NULL or [S] expected blocks per stream (device)
     hipEvent_t *events;   // NULL or 6 events recorded between the kernels
+    bool solo;            // the whole step in one launch (see psa_solo.hip)
 };
 DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t);
 int compute_units();      // of the current device (256 on MI355X); read once
@@ -107,6 +103,8 @@ hipError_t launch_select(const KvView &kv, int dtype, int G, const void *q, cons
                          int m, int budget_blocks, const DecodePlan &plan, hipStream_t st);
 hipError_t launch_attend(const KvView &kv, int dtype, int G, const DecodeWs &ws, const DecodePlan &plan,
                          hipStream_t st);
+// psa_solo.hip: all of the above in one kernel
+hipError_t launch_solo(const KvView &kv, int dtype, int G, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st);
 hipError_t launch_finalize(const KvView &kv, const DecodeWs &ws, int G, int VU, float *out,
                            int32_t *n_selected, float *mass_est, int32_t *blocks_read, float *lse_out,
                            int32_t *traffic_out, hipStream_t st);

@@ -11,9 +11,6 @@
 //   finalize_kernel  merges a head's chunks (the online-softmax merge of line 11, all at once):
 //                    out_g = sum over the chunks of the head's own prefix of the partial numerators,
 //                    over the sum of the partial exp-sums, both rescaled to one reference maximum
-#include <type_traits>
-#include <utility>
-
 #include "psa_attend.h"
 #include "psa_host.h"
 
@@ -23,12 +20,6 @@ namespace psa {
 __device__ __forceinline__ int stop_blocks(unsigned long long st, int N) {
     return (st != ~0ull && (int)(st >> 32) <= N) ? (int)(st >> 32) : N;
 }
-
-// f(0), f(1), ... f(N - 1) with the index as a constant: arrays indexed with it stay in registers.
-template <class F, int... I>
-__device__ __forceinline__ void static_for(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, class F>
-__device__ __forceinline__ void static_for(F f) { static_for(f, std::make_integer_sequence<int, N>{}); }
 
 // =================================================================================================
 // One workgroup per entry of the work list the selection kernel left (value unit = chunk c of stream s);
@@ -45,13 +36,12 @@ __device__ __forceinline__ void static_for(F f) { static_for(f, std::make_intege
 //             kernel left one per block): a reference every wave knows beforehand, so nothing is rescaled
 //             on the way and the four waves' sums simply add up.  (p <= 1, and the largest weight is at least
 //             1/16: the weights keep their precision as 16-bit halves.)
-//   numerator D[head][channel] += P[head][token] V[token][channel]: eight 16x16x16 products per block (one
-//             per channel of the lane's eight) with the weights split into hi + lo 16-bit halves.  The k
+//   numerator D[head][channel] += P[head][token] V[token][channel]: eight 16x16x16 products per block, the weights
+//             split into hi + lo 16-bit halves that sit in neighbouring rows (see add_weighted; in products of their
+//             own the two halves took sixteen).  The k
 //             index of both operands is the token: lane (rg, *) holds the value rows rg, 4+rg, 8+rg, 12+rg
 //             -- the rows its four loads fetched -- and the selection kernel stored the logits so that the
 //             16 bytes at [block][head][4 rg] are those same four tokens: one load, no transposition.
-//             A: row = head lane%16 (zero beyond G).  D: lane (rg, cl) gets heads 4rg..4rg+3 of channels
-//             8cl..8cl+7.
 // Output per unit and head: (L, sum of p, numerator[128]) for the final merge.
 // =================================================================================================
 constexpr int kValueDepth = 4;      // value slices a wave keeps in flight
@@ -95,7 +85,9 @@ __global__ __launch_bounds__(256, 3) void attend_kernel(KvView kv, DecodeWs ws, 
     const int jmax = (maxcnt - wave + 3) / 4;           // blocks of this wave (may be <= 0)
     if (!(kv.slot_pool != nullptr && pg < 0)) pg = clamp_page_quiet(pg, kv.num_pages);   // (a page of the pool, or ~slot)
     const float *lg = ws.logits + row0 * (kPage * G);
-    const int lg_lane = (cl < G ? cl : 0) * kPage + 4 * rg;
+    const int hd = cl >> 1;                             // the head whose weights the lane supplies (see add_weighted)
+    const int lg_lane = (hd < G ? hd : 0) * kPage + 4 * rg;
+    const int hdcnt = __shfl(mycnt, hd);
 
     Slice v[kValueDepth];
     f32x4_t x[kValueDepth];
@@ -110,7 +102,7 @@ __global__ __launch_bounds__(256, 3) void attend_kernel(KvView kv, DecodeWs ws, 
     float l = 0.0f, Lc = -INFINITY;
     // Reference exponent per head: the largest block log-sum-exp among the blocks the head uses (log2 units).  Lane =
     // (block, head) pairs, 64 / G blocks per load, then a butterfly over the lanes of a head: every lane l ends with
-    // the reference of head l % G, so lane (rg, cl < G) holds head cl's.  Every wave computes the same bits.
+    // the reference of head l % G, and takes its own head's from there.  Every wave computes the same bits.
     auto reference = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < kRef; ++k)
@@ -118,6 +110,7 @@ __global__ __launch_bounds__(256, 3) void attend_kernel(KvView kv, DecodeWs ws, 
         for (int i = kUnitBlocks + lane / G; i < mycnt; i += 64 / G) Lc = fmaxf(Lc, bl[(size_t)i * G + lane % G]);
 #pragma unroll
         for (int d = G; d < 64; d <<= 1) Lc = fmaxf(Lc, __shfl_xor(Lc, d));
+        Lc = __shfl(Lc, hd);
     };
     auto consume = [&](int j, auto slot) __attribute__((always_inline)) {
         constexpr int u = decltype(slot)::value;
@@ -130,8 +123,8 @@ __global__ __launch_bounds__(256, 3) void attend_kernel(KvView kv, DecodeWs ws, 
         if (valid < kPage) zero_invalid_rows(v[u], rg, valid);
         // tokens beyond `valid` hold -inf logits; blocks beyond the head's stop, and heads beyond the
         // group, weigh nothing
-        const bool on = cl < G && blk < mycnt;
-        add_values<DT>(acc, l, v[u], x[u], on, Lc);      // (a head that uses no block of the unit is never `on`)
+        const bool on = hd < G && blk < hdcnt;
+        add_values<DT>(acc, l, v[u], x[u], on, Lc, cl & 1);      // (a head that uses no block of the unit is never `on`)
     };
     if (maxcnt == kUnitBlocks) {
         // Eight blocks for every wave: a rolling window, the oldest slice is worked on and its registers go to the next
@@ -159,17 +152,11 @@ __global__ __launch_bounds__(256, 3) void attend_kernel(KvView kv, DecodeWs ws, 
     // the exp-sum over the four row groups, then the four waves through LDS (one reference: plain sums)
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int g = 4 * rg + r;
-        if (g < G) {
-            f32x4_t *row = reinterpret_cast<f32x4_t *>(&st_acc[wave][g][cl * 8]);
-            row[0] = f32x4_t{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-            row[1] = f32x4_t{acc[4][r], acc[5][r], acc[6][r], acc[7][r]};
-        }
+    store_heads<G>(acc, st_acc[wave], rg, cl);
+    if (rg == 0 && hd < G && !(cl & 1)) {
+        st_l[wave][hd] = l;
+        if (wave == 0) st_ref[hd] = Lc;
     }
-    if (rg == 0 && cl < G) st_l[wave][cl] = l;
-    if (wave == 0 && rg == 0 && cl < G) st_ref[cl] = Lc;
     lds_barrier();
     float *dst = ws.partial + ((size_t)s * ws.max_units + c) * G * kPartialStride;
     for (int idx = tid; idx < G * kHeadDim; idx += 256) {
