@@ -1,7 +1,7 @@
 // Host side of psa_decode_attention: workspace layout, launch plan and the kernel sequence
 //   score (Algorithm 1 line 5) -> order (line 6) -> select (lines 7-18, key side and stop rule) ->
 //   attend (value side of lines 10-12) -> finalize (line 19),
-// all enqueued on one stream with no host involvement in between.
+// all enqueued on one stream with no host involvement in between -- or, for short contexts, one kernel that does it all.
 #include "psa_host.h"
 
 namespace psa {
@@ -40,6 +40,16 @@ DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t) {
     p.force_bitonic = t ? t->force_bitonic : 0;
     p.depth_hint = t ? t->depth_hint : nullptr;
     p.events = t ? static_cast<hipEvent_t *>(t->phase_events) : nullptr;
+    // One launch for short contexts, where the chain of launches is what a call costs (psa_solo.hip).  One compute unit
+    // does a stream's work there, which is enough up to 128 blocks whatever is selected (2048 tokens, G = 4, 8 streams:
+    // 18 to 33 us against 31 to 33 for the chain, 256 streams: 28 against 48).  Above, a stream that selects nearly all
+    // its blocks wants more than one, unless there are streams for most of the chip: at 256 blocks 63 us against 32 with 8
+    // streams, 76 against 82 with 192; at 192 blocks 53 against 53 with 128.  Hence three streams for four blocks.
+    // Whoever tunes the general path, times its phases or brings a second tier gets the general path.
+    const bool tuned = t && (t->window_chunks > 0 || t->spin_limit > 0 || t->force_bitonic || t->phase_events ||
+                             (t->chunk_blocks && t->chunk_blocks != 32));
+    const int mb = d->max_blocks_per_seq;
+    p.solo = !d->tier && !tuned && mb <= kSoloBlocks && (mb <= 128 || 4 * S >= 3 * mb);
     return p;
 }
 
@@ -89,6 +99,7 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     ws.max_units = plan.max_chunks;
     const int G = d->num_q_heads / d->num_kv_heads;
     if (kv.batch == 0) return hipSuccess;
+    if (plan.solo) return launch_solo(kv, d->dtype, G, a, ws, st);
     hipEvent_t *ev = plan.events;
     hipError_t e;
     if (ev) (void)hipEventRecord(ev[0], st);

@@ -49,6 +49,7 @@
 // reproducible although the scheduling is dynamic.
 #include <limits.h>
 
+#include "psa_fold.h"
 #include "psa_host.h"
 
 namespace psa {
@@ -104,11 +105,6 @@ __device__ __forceinline__ int stream_ctx(const KvView &kv, int s) {
 __device__ __forceinline__ int window_of(int window, int frontier) {
     const int w = max(window, frontier >> 2);
     return w > kMaxWindowChunks ? kMaxWindowChunks : w;
-}
-
-// P_acc of Algorithm 1 lines 15-16 in the log2 domain: AS_acc / (AS_acc + AS_min * N_left).
-__device__ __forceinline__ float p_acc(float Lacc, float Lmin, int n_left) {
-    return 1.0f / (1.0f + (float)n_left * exp2_fast(Lmin - Lacc));
 }
 
 __device__ __forceinline__ void nap(int tries) {
@@ -178,12 +174,8 @@ __device__ __forceinline__ int granted(int window, int S, int closed) {
 // the stream closes.
 //
 // Chunks are folded a GROUP at a time: 64 / G consecutive chunks, aligned, lane = (chunk of the group, head).  One
-// load fetches the group's words; a prefix scan over the chunks (steps of G lanes) gives every head's AS_acc and
-// AS_min after every chunk of the group at once -- combined with the state carried into the group -- hence P_acc at
-// every chunk's end.  The chunks in which an open head passes the threshold are then visited in order (there are at
-// most G stops per stream) for the head's exact stop, with a second prefix scan over that chunk's blocks.  A
-// sequential walk, chunk by chunk on G lanes, cost a deep stream 0.3 us per chunk -- more than reading the chunk
-// costs the rest of the machine.
+// load fetches the group's words, fold_group takes them in rank order.  A sequential walk, chunk by chunk on G lanes,
+// cost a deep stream 0.3 us per chunk -- more than reading the chunk costs the rest of the machine.
 // The expression that gives the state after a chunk is fixed by the chunk's place in its group (the scan's tree over
 // the group's earlier chunks, then the carry), whatever part of the group was published when the wave looked: the
 // fold is reproducible bit for bit although its timing is not.
@@ -208,6 +200,7 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
     const int ctx = stream_ctx(kv, s);
     const int N = (ctx + kPage - 1) / kPage;
     const unsigned long long *agg = ws.agg + (size_t)s * ws.max_chunks * G;
+    const float *block_lse = ws.block_lse + (size_t)s * kv.max_blocks * G;
     // chunks that may ever be folded: all of them, or those a fixed budget of blocks covers (the limit in the
     // progress word is for the readers of keys and may be tighter: see stop_bound)
     const int nch = ((budget > 0 ? min(N, budget) : N) + KU - 1) / KU;
@@ -217,7 +210,6 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
     }
     const int S = kv.batch * kv.num_kv_heads;
     const float odds = eps > 0.0f ? (1.0f - eps) / eps : INFINITY;      // (1 - eps) / eps of the stop test
-    const unsigned long long head_lanes = (~0ull / ((1ull << G) - 1ull)) << g;   // the lanes of my head
     float Cacc = -INFINITY, Cmin = INFINITY;   // my head's (L_acc, L_min) at the start of the group
     unsigned long long stop = ~0ull;           // my head's stop (n << 32 | P_acc bits), ~0 = still open
     int base = 0, walked = 0;                  // the group's first chunk; chunks folded so far
@@ -248,69 +240,10 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
             continue;
         }
         closed = closed_now;
-        // (L_acc, L_min) of my head after my chunk: scan over the group's chunks, then the carry
         float L = __uint_as_float((uint32_t)(v & 0xffffffffull)), M = __uint_as_float((uint32_t)(v >> 32));
-#pragma unroll
-        for (int d = G; d < 64; d <<= 1) {
-            const float ol = __shfl_up(L, d), om = __shfl_up(M, d);
-            if (lane >= d) { L = lse2(ol, L); M = fminf(om, M); }
-        }
-        L = lse2(Cacc, L);
-        M = fminf(Cmin, M);
-        const int b0 = ci * KU, n_end = min(b0 + KU, N);
-        // a stop inside a chunk needs a position where the rule is tested (line 17 is reached every m blocks and
-        // at the last block) and, P_acc being non-decreasing, a pass at the chunk's end
-        const bool passes = ((n_end / m) * m > b0 || n_end == N) && p_acc(L, M, N - n_end) > eps;
-        int j = walked - base;                 // the next chunk of the group to fold
-        while (j < k) {
-            const unsigned long long cand = __ballot(jl >= j && jl < k && stop == ~0ull && passes);
-            if (cand == 0ull) { j = k; break; }
-            const int js = (__ffsll((long long)cand) - 1) / G;          // the first chunk in which an open head passes
-            const bool scan = (cand >> (js * G + g)) & 1ull;            // does mine?
-            // its blocks' values follow its words by a store round trip: if this look came in between, fold up to it
-            if (__shfl((int)ready, js * G) == 0) { j = js; break; }
-            {
-                // That chunk's blocks' L_b, lane = (block, head), 64 values to a register and all registers asked for at
-                // once; a prefix scan over the blocks of each head (steps of G lanes; the registers' scans side by side),
-                // on top of the state after the chunk before, gives AS_acc and AS_min after every block, hence P_acc at
-                // every position; the first tested position that passes is the stop.
-                const int cb0 = (base + js) * KU, cn_end = min(cb0 + KU, N);
-                const float *lb = ws.block_lse + ((size_t)s * kv.max_blocks + cb0) * G;
-                const int cnt = (cn_end - cb0) * G;
-                float cl = js == 0 ? Cacc : __shfl(L, (js - 1) * G + g);
-                float cm = js == 0 ? Cmin : __shfl(M, (js - 1) * G + g);
-                bool found = false;
-                float pl[kScan], pm[kScan];
-#pragma unroll
-                for (int u = 0; u < kScan; ++u) pm[u] = pl[u] = ld_relaxed(&lb[min(64 * u + lane, cnt - 1)]);
-#pragma nounroll
-                for (int d = G; d < 64; d <<= 1) {
-#pragma unroll
-                    for (int u = 0; u < kScan; ++u) {
-                        const float ol = __shfl_up(pl[u], d), om = __shfl_up(pm[u], d);
-                        if (lane >= d) { pl[u] = lse2(ol, pl[u]); pm[u] = fminf(om, pm[u]); }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kScan; ++u) {
-                    const float fl = lse2(cl, pl[u]), fm = fminf(cm, pm[u]);
-                    const int nn = cb0 + (64 * u + lane) / G + 1;
-                    const float P = p_acc(fl, fm, N - nn);
-                    const unsigned long long hits =
-                        __ballot(64 * u + lane < cnt && (nn % m == 0 || nn == N) && P > eps) & head_lanes;
-                    const int src = hits ? (__ffsll((long long)hits) - 1) : 0;
-                    const float Pf = __shfl(P, src);
-                    if (scan && !found && hits) {
-                        stop = ((unsigned long long)(cb0 + (64 * u + src) / G + 1) << 32) | __float_as_uint(Pf);
-                        found = true;
-                    }
-                    cl = __shfl(fl, 64 - G + g);       // my head's state after this register's last block
-                    cm = __shfl(fm, 64 - G + g);
-                }
-            }
-            j = js + 1;
-            if (__ballot(stop == ~0ull) == 0ull) { finished = true; break; }
-        }
+        // (a chunk's blocks' values follow its words by a store round trip: if this look came in between, it is not `ready`)
+        const int j = fold_group<G, kScan>(L, M, Cacc, Cmin, stop, (int)ready, base, walked - base, k, N, m, KU, eps, finished,
+                                           [&](int b, int i) { return ld_relaxed(&block_lse[(size_t)b * G + i]); });
         if (base + j == walked && !finished) {
             if (++looks > kFoldPatience) {
                 if (lane == 0) set_error(ws.header, PSA_DEVERR_STALLED);
@@ -402,10 +335,6 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
     // (the chunk's pages and valid-token counts are in LDS already: stage_pages)
     // B operand of the QK^T product (see load_queries): the same for every chunk of the stream
     const int n = lane & 15, kq = lane >> 4;
-    // Row r of the A operand stands for token 4*(r%4) + r/4, so that lane (kq, n) ends up with head n's logits of
-    // tokens kq, 4+kq, 8+kq, 12+kq: the value pass wants the four tokens whose value rows ITS lane (kq, *) loads,
-    // and finds them as the 16 bytes at [block][head][4 kq] of the stored logits.
-    const int arow = 4 * (n & 3) + (n >> 2);
     uint4 qb[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) qb[kk] = sh.qb[kk][lane];
@@ -420,28 +349,7 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
     auto consume = [&](int i, const uint4 (&k)[4]) {
         // (second tier with a staging buffer: a slice that came over the host link is kept for the update)
         if (kv.staging != nullptr && sh.page[i] >= 0) stage_key_slice(kv, sh.page[i], h, k, lane);
-        f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        // the slice arrived as four coalesced 1 KiB rows of lanes (loading it in the operand's layout
-        // would touch sixteen 64-byte segments per instruction); the wave turns it into that layout
-        // through its own LDS patch (row = token, 17 16-byte words apart: no bank conflicts)
-        uint4 *stg = sh.stage[wave];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) stg[(kk * 4 + (lane >> 4)) * 17 + (lane & 15)] = k[kk];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-        uint4 a[4];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) a[kk] = stg[arow * 17 + kk * 4 + kq];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) acc = mfma_16x16x32<DT>(a[kk], qb[kk], acc);
-        // the lane now holds head n's logits of tokens kq, 4+kq, 8+kq, 12+kq
-        const int valid = sh.valid[i];
-        f32x4_t sc;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) sc[x] = (4 * x + kq < valid) ? acc[x] * kScaleLog2 : -INFINITY;
+        const f32x4_t sc = block_logits<DT>(k, qb, sh.stage[wave], lane, sh.valid[i]);
         if (n < G) *reinterpret_cast<f32x4_t *>(&sh.lg[i][n][4 * kq]) = sc;
     };
     constexpr int kWaves = kSelectThreads / 64;
@@ -469,36 +377,8 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
         }
     }
     lds_barrier();
-    // ---- the blocks' log-sum-exp L_b per head, from the logits in LDS, all threads of the workgroup at once: kQuad
-    //      threads per (block, head) row of sixteen, each its share of the row's four quarters.  (Reduced slice by
-    //      slice inside the loop, the chain of lane exchanges, exponentials and a logarithm took longer than the
-    //      slice's product, eight times one after the other.)
-    {
-        constexpr int kQuad = G >= 8 ? 1 : (G == 4 ? 2 : 4), kShare = 4 / kQuad;
-        for (int x = tid; x < nblk * G * kQuad; x += kSelectThreads) {
-            const int row = x / kQuad, part = x % kQuad;
-            const f32x4_t *src = reinterpret_cast<const f32x4_t *>(&sh.lg[0][0][0]) + row * 4 + part * kShare;
-            f32x4_t v[kShare];
-            float mx = -INFINITY;
-#pragma unroll
-            for (int y = 0; y < kShare; ++y) {
-                v[y] = src[y];
-                mx = fmaxf(mx, fmaxf(fmaxf(v[y][0], v[y][1]), fmaxf(v[y][2], v[y][3])));
-            }
-            if constexpr (kQuad >= 2) mx = fmaxf(mx, dpp_f<0xB1>(mx));
-            if constexpr (kQuad == 4) mx = fmaxf(mx, dpp_f<0x4E>(mx));
-            float e[kShare];
-#pragma unroll
-            for (int y = 0; y < kShare; ++y)
-                e[y] = (exp2_fast(v[y][0] - mx) + exp2_fast(v[y][1] - mx)) + (exp2_fast(v[y][2] - mx) + exp2_fast(v[y][3] - mx));
-            float sum = e[0];
-            if constexpr (kShare == 2) sum = e[0] + e[1];
-            if constexpr (kShare == 4) sum = (e[0] + e[1]) + (e[2] + e[3]);
-            if constexpr (kQuad >= 2) sum += dpp_f<0xB1>(sum);
-            if constexpr (kQuad == 4) sum += dpp_f<0x4E>(sum);
-            if (part == 0) sh.Lb[row / G][row % G] = mx + log2_fast(sum);
-        }
-    }
+    // ---- the blocks' log-sum-exp L_b per head, from the logits in LDS, all threads of the workgroup at once ----------
+    rows_lse<G, kSelectThreads>(&sh.lg[0][0][0], &sh.Lb[0][0], nblk * G, tid);
     lds_barrier();
     // The chunk's logits leave as one contiguous piece (8 KiB at G = 4), every thread of waves 1-3 16 bytes at a time,
     // while wave 0 publishes.  Writes are what this kernel pays most for per byte; in whole, neighbouring cache lines
@@ -510,24 +390,9 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
         return;
     }
 
-    // ---- publish: the chunk's (log-sum-exp, minimum) of its blocks' L_b per head.  Lane = (slot, head):
-    //      64/G slots each fold every (64/G)-th block, then a butterfly over the slots -- a fixed tree, so
-    //      the word is reproducible; lse2 is symmetric, so every lane of a head ends with the same bits. -------
-    float aggL = -INFINITY, aggMin = INFINITY;
-    {
-        constexpr int kSlots = 64 / G;
-        const int g = lane % G;
-        for (int i = lane / G; i < nblk; i += kSlots) {
-            const float Lb = sh.Lb[i][g];
-            aggL = lse2(aggL, Lb);
-            aggMin = fminf(aggMin, Lb);
-        }
-#pragma unroll
-        for (int d = G; d < 64; d <<= 1) {
-            aggL = lse2(aggL, __shfl_xor(aggL, d));
-            aggMin = fminf(aggMin, __shfl_xor(aggMin, d));
-        }
-    }
+    // ---- publish: the chunk's (log-sum-exp, minimum) of its blocks' L_b per head ------------------------------------
+    float aggL, aggMin;
+    chunk_aggregate<G>(&sh.Lb[0][0], nblk, lane, aggL, aggMin);
     unsigned long long w = pack2(aggL, aggMin);
     if (w == kAggSentinel) w = kAggSentinel - 1;     // a NaN pair that happens to look like "not published"
     // The G words need no order among themselves: the fold takes a chunk only when it sees all of them.
