@@ -105,8 +105,7 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     if (ev) (void)hipEventRecord(ev[0], st);
     if ((e = launch_score(kv, d->dtype, G, a.scorer, a.q, a.meta, ws, a.scores_out, st)) != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[1], st);
-    if ((e = launch_order(kv, ws, G, plan, a.budget_blocks, a.order_out, st)) != hipSuccess) return e;
-    if (d->tier && (e = launch_tier_resolve(kv, d->tier, ws.ranked_page, st)) != hipSuccess) return e;
+    if ((e = launch_order(kv, ws, G, plan, a.budget_blocks, d->tier ? make_tier_view(d->tier).slot_of : nullptr, a.order_out, st)) != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[2], st);
     if ((e = launch_select(kv, d->dtype, G, a.q, ws, a.threshold, a.check_granularity, a.budget_blocks, plan, st)) != hipSuccess)
         return e;

@@ -86,7 +86,6 @@ size_t tier_staging_bytes(long long staging_slices);
 TierView make_tier_view(const psa_tier *t);
 size_t tier_update_workspace_bytes(const psa_kv_desc *d);
 hipError_t launch_tier_init(const psa_tier *tier, hipStream_t st);
-hipError_t launch_tier_resolve(const KvView &kv, const psa_tier *tier, int32_t *ranked_page, hipStream_t st);
 hipError_t launch_tier_update(const psa_kv_desc *d, const int32_t *order, const int32_t *blocks_read,
                               long long busy_first, long long busy_count, int32_t *stats_out, void *workspace,
                               hipStream_t st);
@@ -98,7 +97,7 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
 hipError_t launch_score(const KvView &kv, int dtype, int G, int scorer, const void *q, const void *meta,
                         const DecodeWs &ws, float *scores_out, hipStream_t st);
 hipError_t launch_order(const KvView &kv, const DecodeWs &ws, int G, const DecodePlan &plan, int budget_blocks,
-                        int32_t *order_out, hipStream_t st);
+                        const int32_t *slot_of, int32_t *order_out, hipStream_t st);
 hipError_t launch_select(const KvView &kv, int dtype, int G, const void *q, const DecodeWs &ws, float eps,
                          int m, int budget_blocks, const DecodePlan &plan, hipStream_t st);
 hipError_t launch_attend(const KvView &kv, int dtype, int G, const DecodeWs &ws, const DecodePlan &plan,

@@ -28,8 +28,8 @@
 // 8192 (32 streams), 40 -> 26 with 512 streams; where the time went: scores 0.9 us, range 0.5, counters 0.6, scan 0.4,
 // shares 0.5, layout 0.4, count 0.9, gather and stores 0.4, the rest is the launch.
 //
-// The kernel also resets the stream's control block and chunk words for the progressive kernel and
-// reports out-of-range contexts and block-table entries.
+// The kernel also resets the stream's control block and chunk words for the progressive kernel,
+// reports out-of-range contexts and block-table entries and, with a second tier, looks up which slices have slots.
 // grid (workgroups per stream, S), Np / K threads, 8*Np + 512 bytes of dynamic LDS; Np = power of two >= max(512, max_blocks).
 #include <limits.h>
 
@@ -109,7 +109,7 @@ __device__ void bitonic_sort(unsigned long long (&e)[8], unsigned long long *lds
 // K: keys per thread.
 template <int K>
 __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, int G, int KU, int budget_blocks, int Np,
-                                                      int force_bitonic,
+                                                      int force_bitonic, const int32_t *__restrict__ slot_of,
                                                       int32_t *__restrict__ order_out) {
     extern __shared__ unsigned long long lds_raw[];
     const int s = blockIdx.y, r = s / kv.num_kv_heads;
@@ -246,6 +246,12 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
     int32_t *rpage = ws.ranked_page + (size_t)s * kv.max_blocks;
     int32_t *oout = order_out ? order_out + (size_t)s * kv.max_blocks : nullptr;
 
+    // With a second tier, a block whose slice has a slot is read from the slot: ranked_page then holds ~slot (< 0).
+    auto location = [&](int page) {
+        if (!slot_of) return page;
+        const int slot = slot_of[kv.slice_base + (long long)page * kv.num_kv_heads + s % kv.num_kv_heads];
+        return slot >= 0 ? ~slot : page;
+    };
     if (!too_full && !force_bitonic) {
         // every workgroup of the stream builds its share of the slot table: the elements of a bucket side by side, in
         // arrival order (which may differ between the workgroups; the exact count below does not depend on it) ...
@@ -302,7 +308,7 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
                 if (q0 + tid + j * nthreads < mine) {
                     const uint32_t rank = b0[j] + before[j];
                     ord[rank] = (int)me[j];
-                    rpage[rank] = clamp_page_quiet(table[me[j]], kv.num_pages);
+                    rpage[rank] = location(clamp_page_quiet(table[me[j]], kv.num_pages));
                     if (oout) oout[rank] = (int)me[j];
                 }
             }
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
             if (tid < holders && p < N) {
                 const int b = (int)(e[j] & 0xffffffffull);
                 ord[p] = b;
-                rpage[p] = clamp_page_quiet(table[b], kv.num_pages);
+                rpage[p] = location(clamp_page_quiet(table[b], kv.num_pages));
                 if (oout) oout[p] = b;
             }
         }
@@ -333,7 +339,7 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
 }
 
 hipError_t launch_order(const KvView &kv, const DecodeWs &ws, int G, const DecodePlan &plan, int budget_blocks,
-                        int32_t *order_out, hipStream_t st) {
+                        const int32_t *slot_of, int32_t *order_out, hipStream_t st) {
     const int S = kv.batch * kv.num_kv_heads;
     int Np = 512;
     while (Np < kv.max_blocks) Np <<= 1;
@@ -344,9 +350,9 @@ hipError_t launch_order(const KvView &kv, const DecodeWs &ws, int G, const Decod
     if (Np < 2048) parts = 1;
     const int budget = budget_blocks;
     if (Np <= 2048) {
-        order_kernel<2><<<dim3(parts, S), Np / 2, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, order_out);
+        order_kernel<2><<<dim3(parts, S), Np / 2, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, slot_of, order_out);
     } else if (Np == 4096) {
-        order_kernel<4><<<dim3(parts, S), Np / 4, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, order_out);
+        order_kernel<4><<<dim3(parts, S), Np / 4, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, slot_of, order_out);
     } else {
         static bool raised = false;       // more than 64 KiB of dynamic LDS has to be asked for once
         if (!raised) {
@@ -355,7 +361,7 @@ hipError_t launch_order(const KvView &kv, const DecodeWs &ws, int G, const Decod
                 return hipErrorInvalidValue;
             raised = true;
         }
-        order_kernel<8><<<dim3(parts, S), Np / 8, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, order_out);
+        order_kernel<8><<<dim3(parts, S), Np / 8, lds, st>>>(kv, ws, G, plan.chunk_blocks, budget, Np, plan.force_bitonic, slot_of, order_out);
     }
     return hipGetLastError();
 }

@@ -10,7 +10,7 @@
 // candidate slots ordered by (age, slot index), oldest first.  The first order comes from prefix sums, the
 // second from a stable counting sort of the slots by their 17-bit age key, done here in two passes (8 and 9
 // bits): per-tile digit counts, one scan over the (digit, tile) table, a scatter that keeps slot order inside
-// a digit.
+// a digit.  Up to kRankSlots slots one workgroup does all of that, and both prefix sums, in LDS.
 #include "psa_host.h"
 
 namespace psa {
@@ -19,7 +19,7 @@ constexpr int kTierThreads = 256;
 constexpr unsigned long long kNoKey = ~0ull;
 constexpr uint32_t kMaxAge = 65535;      // updates after which a slot is as old as it gets
 // words of the state header
-constexpr int kClock = 0, kMisses = 1, kHits = 3, kEvicted = 4, kFromStaging = 5;
+constexpr int kClock = 0, kMisses = 1, kHits = 3, kEvicted = 4, kFromStaging = 5, kCandidates = 6, kArrived = 7;
 
 size_t tier_state_bytes(long long total_slices, long long num_slots) {
     return tier_staged_at_offset(total_slices, num_slots) + tier_align((size_t)total_slices * 4);
@@ -54,20 +54,6 @@ __global__ __launch_bounds__(kTierThreads) void tier_init_kernel(TierView t) {
     for (long long j = i; j < t.total_slices; j += stride) { t.slot_of[j] = -1; t.staged_at[j] = -1; }
     if (i == 0 && t.staging) *staging_count(t.staging) = 0;
     for (long long j = i; j < t.num_slots; j += stride) { t.owner[j] = -1; t.stamp[j] = 0; }
-}
-
-// Decode side: a ranked block whose slice has a slot is read from the slot.  ranked_page keeps the page
-// (>= 0) for slices in host memory and holds ~slot (< 0) for cached ones.
-// grid (ceil(max_blocks / 256), S)
-__global__ __launch_bounds__(kTierThreads) void tier_resolve_kernel(KvView kv, TierView t, int32_t *ranked_page) {
-    const int s = blockIdx.y, r = s / kv.num_kv_heads, h = s % kv.num_kv_heads;
-    const int i = blockIdx.x * kTierThreads + threadIdx.x;
-    const int N = (ctx_clamped_quiet(kv, r) + kPage - 1) / kPage;
-    if (i >= N) return;
-    int32_t *p = ranked_page + (size_t)s * kv.max_blocks + i;
-    const int page = *p;                                         // clamped into the pool by the ranking kernel
-    const int slot = t.slot_of[t.slice_base + (long long)page * kv.num_kv_heads + h];
-    if (slot >= 0) *p = ~slot;
 }
 
 // The slices the call used: stamp the cached ones, list the others -- per stream, in rank order, packed at
@@ -187,8 +173,13 @@ __global__ __launch_bounds__(kTierThreads) void tier_candidates_kernel(TierView 
         const bool ok = st < now && !(o >= 0 && o >= busy_first && o < busy_first + busy_count);
         const uint32_t age = st == 0 ? kMaxAge : min(now - st, kMaxAge);
         cand_keys[slot] = ok ? (((unsigned long long)(kMaxAge - age) << 32) | (uint32_t)slot) : kNoKey;
+        const unsigned long long oks = __ballot(ok);
+        if ((__ffsll((long long)__ballot(true)) - 1) == (int)(threadIdx.x & 63) && oks)
+            atomicAdd(&t.header[kCandidates], (uint32_t)__popcll(oks));
     }
 }
+
+constexpr int kSortBitsLow = 8, kSortBitsHigh = 9;       // the 17 bits of the age key, low digit first
 
 // ---- stable sort of the candidate keys by bits [SHIFT, SHIFT + BITS) -------------------------------------------
 // One pass of a least-significant-digit radix sort: tiles of 256 consecutive keys (one per thread); within a
@@ -315,6 +306,144 @@ __global__ __launch_bounds__(kTierThreads) void sort_scatter_kernel(const unsign
     if (live) out[counts[(size_t)digit * tiles + blockIdx.x] + rank] = key;
 }
 
+// ---- all of it in one workgroup ----------------------------------------------------------------------------------
+// The misses' offsets, the candidate keys and their sort for up to kRankSlots slots: eleven small launches (offsets,
+// candidates, and per pass count, two of the scan, scatter), 2.5 to 6 us each, in one of 15.7 us at 10000 slots, bound by
+// the one compute unit's instruction rate (a pass is 4 us of ballots).  1024 threads; wave w
+// holds a run of consecutive slots, 64 at a time, as 32-bit words (17 bits of age key, 14 of slot), and counts its digits in
+// a row of its own; a scan over (digit, wave) gives every wave its first position per digit, in slot order.
+constexpr int kRankSlots = 16384, kRankThreads = 1024, kRankWaves = kRankThreads / 64, kRankPer = kRankSlots / kRankThreads;
+constexpr int kRankBins = 512;
+constexpr uint32_t kRankNone = 0x1FFFFu << 14;            // the age key that sorts last
+
+// Exclusive prefix of v over the workgroup and the total of all.  `part` holds one word per wave.
+__device__ __forceinline__ uint32_t rank_prefix(uint32_t v, uint32_t *part, uint32_t &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t incl = wave_prefix_sum(v);
+    __syncthreads();                                       // (the previous use of `part` is over)
+    if (lane == 63) part[wave] = incl;
+    __syncthreads();
+    const uint32_t p = part[lane & (kRankWaves - 1)];
+    total = row_sum16(p);
+    return row_sum16((lane & 15) < wave ? p : 0u) + incl - v;
+}
+
+// Position of each of the thread's keys after a stable sort by bits [SHIFT, SHIFT + BITS).
+template <int SHIFT, int BITS>
+__device__ __forceinline__ void rank_pass(const uint32_t (&key)[kRankPer], uint32_t (&pos)[kRankPer], int first, int seg, int n,
+                                          uint32_t (*hist)[kRankBins], uint32_t *part) {
+    constexpr int BINS = 1 << BITS;
+    static_assert(BINS <= kRankBins, "room for the digits");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int b = tid; b < kRankWaves * kRankBins; b += kRankThreads) (&hist[0][0])[b] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {
+        if (64 * k < seg) {                                // (uniform over the workgroup)
+            const bool live = first + 64 * k + lane < n;
+            const int digit = (int)((key[k] >> SHIFT) & (uint32_t)(BINS - 1));
+            unsigned long long peers = __ballot(live);
+#pragma unroll
+            for (int b = 0; b < BITS; ++b) {
+                const bool bit = (digit >> b) & 1;
+                const unsigned long long bal = __ballot(bit);
+                peers &= bit ? bal : ~bal;
+            }
+            const uint32_t in_wave = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
+            const uint32_t before = hist[wave][digit];     // (the row is this wave's own; its accesses stay in order)
+            pos[k] = before + in_wave;
+            __builtin_amdgcn_wave_barrier();
+            if (live && in_wave == 0) hist[wave][digit] = before + (uint32_t)__popcll(peers);
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    uint32_t c[kRankWaves], all = 0, total;
+#pragma unroll
+    for (int w = 0; w < kRankWaves; ++w) c[w] = tid < BINS ? hist[w][tid] : 0u;
+#pragma unroll
+    for (int w = 0; w < kRankWaves; ++w) all += c[w];
+    uint32_t run = rank_prefix(all, part, total);
+    if (tid < BINS) {
+#pragma unroll
+        for (int w = 0; w < kRankWaves; ++w) { hist[w][tid] = run; run += c[w]; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k)
+        if (64 * k < seg) pos[k] += hist[wave][(key[k] >> SHIFT) & (uint32_t)(BINS - 1)];
+    __syncthreads();                                       // (the rows are cleared by the next pass)
+}
+
+__global__ __launch_bounds__(kRankThreads) void tier_rank_kernel(TierView t, const uint32_t *__restrict__ miss_count,
+                                                                 uint32_t *__restrict__ miss_offset, int S,
+                                                                 long long busy_first, long long busy_count,
+                                                                 unsigned long long *__restrict__ cands) {
+    extern __shared__ uint32_t rank_lds[];
+    uint32_t *sorted = rank_lds;                                                              // [kRankSlots]
+    auto hist = reinterpret_cast<uint32_t (*)[kRankBins]>(rank_lds + kRankSlots);             // [kRankWaves][kRankBins]
+    __shared__ uint32_t part[kRankWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = t.num_slots;
+    const int seg = (n + kRankThreads - 1) / kRankThreads * 64, first = wave * seg;           // slots of a wave
+    const uint32_t now = t.header[kClock] + 1;
+    uint32_t key[kRankPer], pos[kRankPer], mine = 0;
+    bool few = true;
+    uint32_t stamp[kRankPer];
+    int owner[kRankPer];
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {                   // (index clamped: no branch around a load, all in flight at once)
+        const int slot = min(first + 64 * k + lane, n - 1);
+        stamp[k] = t.stamp[slot];
+        owner[k] = t.owner[slot];
+    }
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {
+        const int slot = first + 64 * k + lane;
+        const bool mine_to_sort = 64 * k < seg && slot < n;
+        const long long o = owner[k];
+        const bool ok = mine_to_sort && stamp[k] < now && !(o >= 0 && o >= busy_first && o < busy_first + busy_count);
+        const uint32_t age = stamp[k] == 0 ? kMaxAge : min(now - stamp[k], kMaxAge);
+        key[k] = (ok ? (kMaxAge - age) << 14 : kRankNone) | (uint32_t)(slot & 0x3FFF);
+        pos[k] = 0;
+        mine += ok ? 1u : 0u;
+        few &= !ok || age <= 253u || age == kMaxAge;
+    }
+    uint32_t carry = 0, total;
+    for (int base = 0; base < S; base += kRankThreads) {   // the streams' misses one after the other
+        const int i = base + tid;
+        const uint32_t before = rank_prefix(i < S ? miss_count[i] : 0u, part, total);
+        if (i < S) miss_offset[i] = carry + before;
+        carry += total;
+    }
+    if (tid == 0) { miss_offset[S] = carry; t.header[kMisses] = carry; }
+    (void)rank_prefix(mine, part, total);
+    if (tid == 0) t.header[kCandidates] = total;
+    if (__syncthreads_and(few)) {
+        // No age between 254 and the saturated one: 255 different keys at most, one pass.
+        uint32_t small[kRankPer];
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            const uint32_t field = key[k] >> 14;           // 65535 - age, or all ones
+            small[k] = field == 0u ? 0u : (key[k] >= kRankNone ? 255u : field - (kMaxAge - 254u));
+        }
+        rank_pass<0, 8>(small, pos, first, seg, n, hist, part);
+    } else {
+        rank_pass<14, kSortBitsLow>(key, pos, first, seg, n, hist, part);
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k)
+            if (64 * k < seg && first + 64 * k + lane < n) sorted[pos[k]] = key[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k)
+            if (64 * k < seg && first + 64 * k + lane < n) key[k] = sorted[first + 64 * k + lane];
+        rank_pass<14 + kSortBitsLow, kSortBitsHigh>(key, pos, first, seg, n, hist, part);
+    }
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k)
+        if (64 * k < seg && first + 64 * k + lane < n)
+            cands[pos[k]] = key[k] >= kRankNone ? kNoKey : (((unsigned long long)(key[k] >> 14) << 32) | (key[k] & 0x3FFFu));
+}
+
 // The j-th miss takes the j-th candidate slot: the slice is copied into it (two 4 KiB slices, one 16-byte load
 // per thread each) -- from the staging buffer if the attention kernels left it there, from host memory if not --
 // and the tables are brought up to date.  Workgroups stride over the pairs.
@@ -362,26 +491,13 @@ __global__ __launch_bounds__(kTierThreads) void tier_promote_kernel(KvView kv, T
     }
 }
 
-// Empties the staging buffer: every entry's slice forgets it.  (The counter itself is cleared by the finishing kernel.)
-__global__ __launch_bounds__(kTierThreads) void tier_unstage_kernel(TierView t) {
-    const uint32_t n = min(*staging_count(t.staging), (uint32_t)t.staging_cap);
-    for (uint32_t i = blockIdx.x * kTierThreads + threadIdx.x; i < n; i += gridDim.x * kTierThreads) {
-        const int id = staging_ids(t.staging)[i];
-        if (id >= 0 && id < t.total_slices) t.staged_at[id] = -1;
-    }
-}
-
-__global__ void tier_finish_kernel(TierView t, const unsigned long long *__restrict__ cands, int32_t *stats_out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// The update's last step: the numbers for the caller, the clock, the counters.  (One thread.)
+__device__ void tier_finish(TierView t, int32_t *stats_out) {
     if (stats_out) {
-        int lo = 0, hi = t.num_slots;                      // first position of the sorted keys that is no candidate
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (cands[mid] == kNoKey) hi = mid; else lo = mid + 1;
-        }
+        const uint32_t misses_n = t.header[kMisses], lo = t.header[kCandidates];
         stats_out[0] = (int32_t)t.header[kHits];
-        stats_out[1] = (int32_t)t.header[kMisses];
-        stats_out[2] = (int32_t)min(t.header[kMisses], (uint32_t)lo);
+        stats_out[1] = (int32_t)misses_n;
+        stats_out[2] = (int32_t)min(misses_n, lo);
         stats_out[3] = (int32_t)t.header[kEvicted];
         stats_out[4] = (int32_t)t.header[kFromStaging];
     }
@@ -391,6 +507,23 @@ __global__ void tier_finish_kernel(TierView t, const unsigned long long *__restr
     t.header[kMisses] = 0;
     t.header[kHits] = 0;
     t.header[kEvicted] = 0;
+    t.header[kCandidates] = 0;
+    t.header[kArrived] = 0;
+}
+
+// Empties the staging buffer (every entry's slice forgets it); the workgroup that is done last finishes the update.
+__global__ __launch_bounds__(kTierThreads) void tier_unstage_kernel(TierView t, int32_t *stats_out) {
+    const uint32_t n = min(*staging_count(t.staging), (uint32_t)t.staging_cap);
+    for (uint32_t i = blockIdx.x * kTierThreads + threadIdx.x; i < n; i += gridDim.x * kTierThreads) {
+        const int id = staging_ids(t.staging)[i];
+        if (id >= 0 && id < t.total_slices) t.staged_at[id] = -1;
+    }
+    __syncthreads();                                       // (everyone has read the counter)
+    if (threadIdx.x == 0 && atomicAdd(&t.header[kArrived], 1u) == gridDim.x - 1) tier_finish(t, stats_out);
+}
+
+__global__ void tier_finish_kernel(TierView t, int32_t *stats_out) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) tier_finish(t, stats_out);
 }
 
 hipError_t launch_tier_init(const psa_tier *tier, hipStream_t st) {
@@ -399,18 +532,10 @@ hipError_t launch_tier_init(const psa_tier *tier, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_tier_resolve(const KvView &kv, const psa_tier *tier, int32_t *ranked_page, hipStream_t st) {
-    const TierView t = make_tier_view(tier);
-    const dim3 grid((kv.max_blocks + kTierThreads - 1) / kTierThreads, kv.batch * kv.num_kv_heads);
-    tier_resolve_kernel<<<grid, kTierThreads, 0, st>>>(kv, t, ranked_page);
-    return hipGetLastError();
-}
-
 struct TierScratch {
     size_t miss_ids, miss_count, miss_offset, cand_in, cand_out, counts, span_sums, total;
     int tiles;
 };
-constexpr int kSortBitsLow = 8, kSortBitsHigh = 9;       // the 17 bits of the age key, low digit first
 
 static TierScratch tier_scratch(const psa_kv_desc *d) {
     const size_t S = (size_t)d->batch * d->num_kv_heads;
@@ -449,34 +574,45 @@ hipError_t launch_tier_update(const psa_kv_desc *d, const int32_t *order, const 
     hipError_t e;
     tier_touch_kernel<<<S, kTierThreads, 0, st>>>(kv, t, order, blocks_read, miss_ids, miss_count);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    tier_offsets_kernel<<<1, kTierThreads, 0, st>>>(t, miss_count, miss_offset, S);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int cgrid = (t.num_slots + kTierThreads - 1) / kTierThreads;
-    tier_candidates_kernel<<<cgrid < 2048 ? cgrid : 2048, kTierThreads, 0, st>>>(t, busy_first, busy_count, cand_in);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // candidates by bits 32..48, low digit first (each pass is stable: equal ages stay in slot order)
-    auto *counts = reinterpret_cast<uint32_t *>(base + L.counts);
-    const int n = t.num_slots, tiles = L.tiles;
-    auto *span_sums = reinterpret_cast<uint32_t *>(base + L.span_sums);
-    const int total_low = (1 << kSortBitsLow) * tiles, total_high = (1 << kSortBitsHigh) * tiles;
-    const int spans_low = (total_low + kScanSpan - 1) / kScanSpan, spans_high = (total_high + kScanSpan - 1) / kScanSpan;
-    sort_count_kernel<32, kSortBitsLow><<<tiles, kTierThreads, 0, st>>>(cand_in, n, counts, tiles);
-    sort_scan_sums_kernel<<<spans_low, kTierThreads, 0, st>>>(counts, total_low, span_sums);
-    sort_scan_apply_kernel<<<spans_low, kTierThreads, 0, st>>>(counts, total_low, span_sums);
-    sort_scatter_kernel<32, kSortBitsLow><<<tiles, kTierThreads, 0, st>>>(cand_in, n, counts, tiles, cand_out);
-    sort_count_kernel<32 + kSortBitsLow, kSortBitsHigh><<<tiles, kTierThreads, 0, st>>>(cand_out, n, counts, tiles);
-    sort_scan_sums_kernel<<<spans_high, kTierThreads, 0, st>>>(counts, total_high, span_sums);
-    sort_scan_apply_kernel<<<spans_high, kTierThreads, 0, st>>>(counts, total_high, span_sums);
-    sort_scatter_kernel<32 + kSortBitsLow, kSortBitsHigh><<<tiles, kTierThreads, 0, st>>>(cand_out, n, counts, tiles, cand_in);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // Up to kRankSlots slots one workgroup is faster than launches that fill the chip (10000 slots, four steps with their attention: 460 -> 387 us), and a
+    // 32-bit word holds the age and the slot.
+    if (t.num_slots <= kRankSlots) {
+        constexpr int kRankLds = (kRankSlots + kRankWaves * kRankBins) * 4;
+        static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(tier_rank_kernel),
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kRankLds);
+        if (raised != hipSuccess) return raised;
+        tier_rank_kernel<<<1, kRankThreads, kRankLds, st>>>(t, miss_count, miss_offset, S, busy_first, busy_count, cand_in);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else {
+        tier_offsets_kernel<<<1, kTierThreads, 0, st>>>(t, miss_count, miss_offset, S);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const int cgrid = (t.num_slots + kTierThreads - 1) / kTierThreads;
+        tier_candidates_kernel<<<cgrid < 2048 ? cgrid : 2048, kTierThreads, 0, st>>>(t, busy_first, busy_count, cand_in);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        // candidates by bits 32..48, low digit first (each pass is stable: equal ages stay in slot order)
+        auto *counts = reinterpret_cast<uint32_t *>(base + L.counts);
+        const int n = t.num_slots, tiles = L.tiles;
+        auto *span_sums = reinterpret_cast<uint32_t *>(base + L.span_sums);
+        const int total_low = (1 << kSortBitsLow) * tiles, total_high = (1 << kSortBitsHigh) * tiles;
+        const int spans_low = (total_low + kScanSpan - 1) / kScanSpan, spans_high = (total_high + kScanSpan - 1) / kScanSpan;
+        sort_count_kernel<32, kSortBitsLow><<<tiles, kTierThreads, 0, st>>>(cand_in, n, counts, tiles);
+        sort_scan_sums_kernel<<<spans_low, kTierThreads, 0, st>>>(counts, total_low, span_sums);
+        sort_scan_apply_kernel<<<spans_low, kTierThreads, 0, st>>>(counts, total_low, span_sums);
+        sort_scatter_kernel<32, kSortBitsLow><<<tiles, kTierThreads, 0, st>>>(cand_in, n, counts, tiles, cand_out);
+        sort_count_kernel<32 + kSortBitsLow, kSortBitsHigh><<<tiles, kTierThreads, 0, st>>>(cand_out, n, counts, tiles);
+        sort_scan_sums_kernel<<<spans_high, kTierThreads, 0, st>>>(counts, total_high, span_sums);
+        sort_scan_apply_kernel<<<spans_high, kTierThreads, 0, st>>>(counts, total_high, span_sums);
+        sort_scatter_kernel<32 + kSortBitsLow, kSortBitsHigh><<<tiles, kTierThreads, 0, st>>>(cand_out, n, counts, tiles, cand_in);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     tier_promote_kernel<<<2048, kTierThreads, 0, st>>>(kv, t, miss_ids, miss_offset, S, cand_in);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (t.staging) {
         const int ugrid = (t.staging_cap + kTierThreads - 1) / kTierThreads;
-        tier_unstage_kernel<<<ugrid < 1024 ? ugrid : 1024, kTierThreads, 0, st>>>(t);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        tier_unstage_kernel<<<ugrid < 256 ? ugrid : 256, kTierThreads, 0, st>>>(t, stats_out);
+    } else {
+        tier_finish_kernel<<<1, 64, 0, st>>>(t, stats_out);
     }
-    tier_finish_kernel<<<1, 64, 0, st>>>(t, cand_in, stats_out);
     return hipGetLastError();
 }
 

@@ -127,6 +127,32 @@ def test_cold_then_warm_single_layer(psa, slots_share, staging_slices):
     rep.assert_accounted()
 
 
+@pytest.mark.parametrize("num_slots", [1, 63, 700, 1025, 16384, 16385, 20011])
+def test_slots_are_taken_oldest_first(psa, num_slots):
+    """The candidates' sort, in one workgroup (up to 16384 slots; one pass while no age lies between 254 and the saturated
+    one, two after 260 updates) and over the chip (beyond): the tables follow the model update by update."""
+    cfg = get_config(3).scaled(batch=3, ctx=2000, layers=1)
+    li = generate_layer(cfg, layer=3, device="cuda")
+    n_slices = li.k_pool.shape[0] * li.k_pool.shape[1]
+    tier = psa.Tier(n_slices, num_slots)
+    model = TierModel(n_slices, num_slots)
+    L = Layer(psa, li, tier, 0)
+    out = psa.decode_attention(L.dev, li.q, L.meta_dev, 0.9, 1, want_order=True)
+    full = out.blocks_read.clone()
+    for step, (num, den) in enumerate([(1, 3), (1, 2), (3, 1), (1, 1), (1, 2), (2, 1)]):
+        out.blocks_read.copy_((full * num) // den)
+        out.blocks_read[step % 3] = 0                    # one request sits the update out: its slots age
+        out.blocks_read.clamp_(max=li.block_table.shape[1])
+        _update(psa, L, out, tier, model, busy=(0, n_slices // 3) if step == 3 else (0, 0))
+        _check_tables(tier, model, [L])
+        if step == 3:
+            out.blocks_read.zero_()
+            for _ in range(260):
+                psa.tier_update(L.host, out.order, out.blocks_read, 0, 0)
+                model.update(np.zeros(0, dtype=np.int64), 0, 0)
+    assert model.clock == 266
+
+
 def test_two_layers_share_a_small_pool_over_a_decode_loop(psa):
     """Two layers, one pool too small for both: drifting queries, a token appended per step, the other
     layer named busy in every update.  Outputs equal the single-tier run's; tables equal the model's."""
