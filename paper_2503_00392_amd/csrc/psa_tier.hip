@@ -574,8 +574,8 @@ hipError_t launch_tier_update(const psa_kv_desc *d, const int32_t *order, const 
     hipError_t e;
     tier_touch_kernel<<<S, kTierThreads, 0, st>>>(kv, t, order, blocks_read, miss_ids, miss_count);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // Up to kRankSlots slots one workgroup is faster than launches that fill the chip (10000 slots, four steps with their attention: 460 -> 387 us), and a
-    // 32-bit word holds the age and the slot.
+    // Up to kRankSlots slots one workgroup is faster than launches that fill the chip (10000 slots, four steps with their
+    // attention: 460 -> 387 us), and a 32-bit word holds the age and the slot.
     if (t.num_slots <= kRankSlots) {
         constexpr int kRankLds = (kRankSlots + kRankWaves * kRankBins) * 4;
         static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(tier_rank_kernel),
