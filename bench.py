@@ -71,7 +71,7 @@ def load_read_probe():
     return lib.bench_stream_read_probe
 
 
-KERNEL_SOURCES = {"select_kernel": ["psa_select.hip", "psa_device.h"], "attend_kernel": ["psa_values.hip", "psa_attend.h", "psa_device.h"],
+KERNEL_SOURCES = {"select_kernel": ["psa_select.hip", "psa_fold.h", "psa_device.h"], "attend_kernel": ["psa_values.hip", "psa_attend.h", "psa_device.h"],
                   "score_kernel": ["psa_score.hip", "psa_device.h"]}
 
 
