@@ -46,13 +46,28 @@ struct SoloShared {
 // Bits of the sticky error word for everything this call's tables and lengths hold, found by one workgroup of its own:
 // a workgroup that only looks at its own request could not clear the word before the others write it.
 __device__ __forceinline__ void solo_report(const KvView &kv, int32_t *header) {
-    const int tid = threadIdx.x, nt = blockDim.x;
+    // A wave takes four requests at a time, a lane every 64th block: all their loads are in flight at once (one entry per
+    // thread and turn, in the grid's last workgroup, made a call of 1024 requests of one KV head 155 us long; 101 now).
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int bits = 0;
-    for (long long x = tid; x < (long long)kv.batch * kv.max_blocks; x += nt) {
-        const int r = (int)(x / kv.max_blocks), b = (int)(x % kv.max_blocks);
-        const int raw = kv.ctx_lens[r], ctx = ctx_clamped_quiet(kv, r);
-        if (raw != ctx) bits |= PSA_DEVERR_CTX_RANGE;
-        if (b < (ctx + kPage - 1) / kPage && (unsigned)kv.block_table[x] >= (unsigned)kv.num_pages) bits |= PSA_DEVERR_PAGE_RANGE;
+    for (int r0 = 4 * wave; r0 < kv.batch; r0 += 4 * kSoloWaves) {
+        int raw[4], page[4][kSoloBlocks / 64];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = min(r0 + u, kv.batch - 1);
+            raw[u] = kv.ctx_lens[r];
+#pragma unroll
+            for (int k = 0; k < kSoloBlocks / 64; ++k)
+                page[u][k] = kv.block_table[(size_t)r * kv.max_blocks + min(64 * k + lane, kv.max_blocks - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int ctx = max(0, min(raw[u], kv.max_blocks * kPage)), N = (ctx + kPage - 1) / kPage;
+            if (raw[u] != ctx) bits |= PSA_DEVERR_CTX_RANGE;
+#pragma unroll
+            for (int k = 0; k < kSoloBlocks / 64; ++k)
+                if (64 * k + lane < N && (unsigned)page[u][k] >= (unsigned)kv.num_pages) bits |= PSA_DEVERR_PAGE_RANGE;
+        }
     }
     const int page_bad = __syncthreads_or(bits & PSA_DEVERR_PAGE_RANGE), ctx_bad = __syncthreads_or(bits & PSA_DEVERR_CTX_RANGE);
     if (tid == 0) {
@@ -61,7 +76,7 @@ __device__ __forceinline__ void solo_report(const KvView &kv, int32_t *header) {
     }
 }
 
-// grid (S + 1), 1024 threads; the last workgroup writes the error word.
+// grid (1 + S), 1024 threads; the first workgroup writes the error word.
 template <int DT, int G, int SCORER>
 __global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, const uint8_t *__restrict__ q,
                                                     const uint8_t *__restrict__ meta, float eps, int m, int budget,
@@ -71,8 +86,8 @@ __global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, cons
                                                     float *__restrict__ scores_out, int32_t *__restrict__ traffic_out) {
     extern __shared__ __attribute__((aligned(16))) unsigned char solo_lds[];
     SoloShared<G> &sh = *reinterpret_cast<SoloShared<G> *>(solo_lds);
-    const int S = kv.batch * kv.num_kv_heads, s = blockIdx.x;
-    if (s == S) { solo_report(kv, ws.header); return; }
+    if (blockIdx.x == 0) { solo_report(kv, ws.header); return; }       // (first, so that it is over before the last stream)
+    const int s = (int)blockIdx.x - 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rg = lane >> 4, cl = lane & 15;
     const int r = s / kv.num_kv_heads, h = s % kv.num_kv_heads;
     const int32_t *table = kv.block_table + (size_t)r * kv.max_blocks;
