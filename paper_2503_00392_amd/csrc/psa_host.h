@@ -94,6 +94,11 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
                          hipStream_t st);
 
 // psa_score.hip, psa_order.hip, psa_select.hip, psa_values.hip: the kernels of one decode call
+// Whether the scores of such a call are formed on the matrix cores (see psa_score.hip).  Another order of sums can swap two
+// blocks whose scores nearly tie, so every path of a call has to form them in the same way.
+inline bool score_on_matrix_cores(int G, int num_kv_heads, int scorer) {
+    return G >= 8 && scorer != 2 && !(num_kv_heads > 1 && 16 % num_kv_heads == 0);
+}
 hipError_t launch_score(const KvView &kv, int dtype, int G, int scorer, const void *q, const void *meta,
                         const DecodeWs &ws, float *scores_out, hipStream_t st);
 hipError_t launch_order(const KvView &kv, const DecodeWs &ws, int G, const DecodePlan &plan, int budget_blocks,

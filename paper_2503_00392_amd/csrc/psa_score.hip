@@ -280,6 +280,17 @@ static hipError_t launch_score_t(const KvView &kv, int scorer, const void *q, co
                                                        scores_out, ws.header, rounds);
         return hipGetLastError();
     }
+    if constexpr (G >= 8) {
+        if (score_on_matrix_cores(G, kv.num_kv_heads, scorer)) {
+            if (scorer == 1)
+                score_mfma_kernel<DT, G, 1><<<grid, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
+                                                                  scores_out, ws.header);
+            else
+                score_mfma_kernel<DT, G, 0><<<grid, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
+                                                                  scores_out, ws.header);
+            return hipGetLastError();
+        }
+    }
     if (kv.num_kv_heads > 1 && 16 % kv.num_kv_heads == 0) {
         // all KV heads of a page together; blocks per workgroup: as many (up to 64) as still leave four
         // workgroups per compute unit, in whole rounds of four steps
@@ -294,14 +305,7 @@ static hipError_t launch_score_t(const KvView &kv, int scorer, const void *q, co
         else
             score_pages_kernel<DT, G, 0><<<grid_p, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
                                                                  scores_out, ws.header, nb);
-    } else if constexpr (G >= 8) {
-        if (scorer == 1)
-            score_mfma_kernel<DT, G, 1><<<grid, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
-                                                              scores_out, ws.header);
-        else
-            score_mfma_kernel<DT, G, 0><<<grid, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
-                                                              scores_out, ws.header);
-    } else {
+    } else if constexpr (G < 8) {
         if (scorer == 1)
             score_kernel<DT, G, 1><<<grid_r, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
                                                            scores_out, ws.header, rounds);

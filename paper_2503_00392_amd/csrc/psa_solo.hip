@@ -9,9 +9,9 @@
 // 4096 tokens, 256 streams: 60.4 -> 44.0.  What bounds it then is the one compute unit's instruction rate: reading keys a
 // step ahead, or four value slices instead of two, ran out of registers and was 5 to 20 % slower.
 //
-// The results are bit for bit those of the general path wherever that scores with packed dots (see psa_score.hip): the
-// same products, the same chunks of 32 ranked blocks with the same trees of sums (psa_fold.h), the same value units summed
-// by four waves each, the same merge.
+// The results are bit for bit those of the general path: the same products (scores on the matrix cores where that forms
+// them there), the same chunks of 32 ranked blocks with the same trees of sums (psa_fold.h), the same value units summed by
+// four waves each, the same merge.
 #include "psa_attend.h"
 #include "psa_fold.h"
 #include "psa_host.h"
@@ -76,8 +76,8 @@ __device__ __forceinline__ void solo_report(const KvView &kv, int32_t *header) {
     }
 }
 
-// grid (1 + S), 1024 threads; the first workgroup writes the error word.
-template <int DT, int G, int SCORER>
+// grid (1 + S), 1024 threads; the first workgroup writes the error word.  MFMA: scores on the matrix cores.
+template <int DT, int G, int SCORER, bool MFMA>
 __global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, const uint8_t *__restrict__ q,
                                                     const uint8_t *__restrict__ meta, float eps, int m, int budget,
                                                     float *__restrict__ out, int32_t *__restrict__ n_selected,
@@ -95,9 +95,16 @@ __global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, cons
     // everything the workgroup needs first, asked for at once: pages, queries in both layouts, the length
     const int lb = 16 * wave + cl;                             // block whose page this lane holds (lanes 0..15, repeated)
     int page_of_lane = table[min(lb, kv.max_blocks - 1)];
-    uint4 qw[G];
+    uint4 qw[MFMA ? 4 : G];                                    // (MFMA: the lane's part of the B operand, head cl)
 #pragma unroll
-    for (int g = 0; g < G; ++g) qw[g] = ld16(qh + (size_t)g * kRowBytes + cl * 16);
+    for (int g = 0; g < (MFMA ? 4 : G); ++g) {
+        if constexpr (MFMA) {
+            qw[g] = ld16(qh + (size_t)min(cl, G - 1) * kRowBytes + (4 * g + rg) * 16);
+            if (cl >= G) qw[g] = make_uint4(0, 0, 0, 0);
+        } else {
+            qw[g] = ld16(qh + (size_t)g * kRowBytes + cl * 16);
+        }
+    }
     if (tid < 256) {                                           // (see load_queries of the selection kernel)
         const int kk = tid >> 6, n = tid & 15, kq = (tid & 63) >> 4;
         uint4 v = make_uint4(0, 0, 0, 0);
@@ -108,45 +115,74 @@ __global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, cons
     const int N = (ctx + kPage - 1) / kPage;                   // <= max_blocks <= kSoloBlocks
     page_of_lane = lb < N ? clamp_page_quiet(page_of_lane, kv.num_pages) : 0;
 
-    // ---- scores (line 5): wave w takes blocks 16 w .. 16 w + 15, sixteen lanes to a block, four blocks a step --------
+    // ---- scores (line 5): wave w takes blocks 16 w .. 16 w + 15 -----------------------------------------------------
     if (16 * wave < N) {
-        constexpr int kRecord = SCORER == 2 ? 256 : kMetaBytes;
-        uint4 lo[4], hi[4];
+        auto put = [&](int blk, float cs) {
+            sh.key[blk] = descending_key(cs);
+            if (scores_out) scores_out[(size_t)s * kv.max_blocks + blk] = cs;
+        };
+        if constexpr (MFMA) {
+            // one product over the blocks' records, row = block, as score_mfma_kernel forms it
+            const uint8_t *mp = meta + ((size_t)page_of_lane * kv.num_kv_heads + h) * kMetaBytes + rg * 16;
+            uint4 a[8];
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int j = min(4 * it + rg, N - 1 - 16 * wave);     // (clamped: the loads need no branch)
-            const uint8_t *mp = meta + ((size_t)__shfl(page_of_lane, j) * kv.num_kv_heads + h) * kRecord + cl * 16;
-            lo[it] = ld16_stream(mp);
-            hi[it] = SCORER == 2 ? make_uint4(0, 0, 0, 0) : ld16_stream(mp + 256);
-        }
+            for (int kk = 0; kk < 8; ++kk) a[kk] = ld16(mp + kk * 64);
+            f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const uint32_t a[4] = {lo[it].x, lo[it].y, lo[it].z, lo[it].w};
-            const uint32_t b[4] = {hi[it].x, hi[it].y, hi[it].z, hi[it].w};
-            float cs = -INFINITY;
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const uint32_t w[4] = {qw[g].x, qw[g].y, qw[g].z, qw[g].w};
-                float p = 0.0f;
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const uint32_t neg = ((w[x] >> 15) & 0x00010001u) * 0xFFFFu;   // 0xFFFF in each negative half
-                    p = dot2<DT>(a[x], SCORER ? w[x] : (w[x] & neg), p);
-                }
-                if constexpr (SCORER != 2) {
+            for (int kk = 0; kk < 8; ++kk) {
+                uint32_t w[4] = {qw[kk & 3].x, qw[kk & 3].y, qw[kk & 3].z, qw[kk & 3].w};
+                if constexpr (SCORER == 0) {
 #pragma unroll
                     for (int x = 0; x < 4; ++x) {
                         const uint32_t neg = ((w[x] >> 15) & 0x00010001u) * 0xFFFFu;
-                        p = dot2<DT>(b[x], SCORER ? w[x] : (w[x] & ~neg), p);
+                        w[x] &= kk >= 4 ? ~neg : neg;
                     }
                 }
-                p = row_sum16(p);
-                cs = fmaxf(cs, p * (SCORER == 1 ? 0.5f * kScale : kScale));
+                d = mfma_16x16x32<DT>(a[kk], make_uint4(w[0], w[1], w[2], w[3]), d);
             }
-            const int blk = 16 * wave + 4 * it + rg;
-            if (cl == 0 && blk < N) {
-                sh.key[blk] = descending_key(cs);
-                if (scores_out) scores_out[(size_t)s * kv.max_blocks + blk] = cs;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const float cs = row_max16(cl < G ? d[x] : -INFINITY) * (SCORER == 1 ? 0.5f * kScale : kScale);
+                const int blk = 16 * wave + 4 * rg + x;
+                if (cl == 0 && blk < N) put(blk, cs);
+            }
+        } else {
+            // sixteen lanes to a block, four blocks a step, packed dots
+            constexpr int kRecord = SCORER == 2 ? 256 : kMetaBytes;
+            uint4 lo[4], hi[4];
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int j = min(4 * it + rg, N - 1 - 16 * wave);     // (clamped: the loads need no branch)
+                const uint8_t *mp = meta + ((size_t)__shfl(page_of_lane, j) * kv.num_kv_heads + h) * kRecord + cl * 16;
+                lo[it] = ld16_stream(mp);
+                hi[it] = SCORER == 2 ? make_uint4(0, 0, 0, 0) : ld16_stream(mp + 256);
+            }
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const uint32_t a[4] = {lo[it].x, lo[it].y, lo[it].z, lo[it].w};
+                const uint32_t b[4] = {hi[it].x, hi[it].y, hi[it].z, hi[it].w};
+                float cs = -INFINITY;
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const uint32_t w[4] = {qw[g].x, qw[g].y, qw[g].z, qw[g].w};
+                    float p = 0.0f;
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const uint32_t neg = ((w[x] >> 15) & 0x00010001u) * 0xFFFFu;   // 0xFFFF in each negative half
+                        p = dot2<DT>(a[x], SCORER ? w[x] : (w[x] & neg), p);
+                    }
+                    if constexpr (SCORER != 2) {
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            const uint32_t neg = ((w[x] >> 15) & 0x00010001u) * 0xFFFFu;
+                            p = dot2<DT>(b[x], SCORER ? w[x] : (w[x] & ~neg), p);
+                        }
+                    }
+                    p = row_sum16(p);
+                    cs = fmaxf(cs, p * (SCORER == 1 ? 0.5f * kScale : kScale));
+                }
+                const int blk = 16 * wave + 4 * it + rg;
+                if (cl == 0 && blk < N) put(blk, cs);
             }
         }
         if (lane < 16 && lb < N) sh.page[lb] = page_of_lane;
@@ -340,24 +376,32 @@ __global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, cons
     }
 }
 
-template <int DT, int G, int SCORER>
+template <int DT, int G, int SCORER, bool MFMA = false>
 static hipError_t launch_solo_t(const KvView &kv, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st) {
     // (more than 64 KiB of dynamic LDS has to be asked for, once per kernel)
-    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(solo_kernel<DT, G, SCORER>),
+    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(solo_kernel<DT, G, SCORER, MFMA>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SoloShared<G>));
     if (raised != hipSuccess) return raised;
     const unsigned S = (unsigned)(kv.batch * kv.num_kv_heads);
-    solo_kernel<DT, G, SCORER><<<S + 1, 1024, sizeof(SoloShared<G>), st>>>(
+    solo_kernel<DT, G, SCORER, MFMA><<<S + 1, 1024, sizeof(SoloShared<G>), st>>>(
         kv, ws, (const uint8_t *)a.q, (const uint8_t *)a.meta, a.threshold, a.check_granularity, a.budget_blocks, a.out,
         a.n_selected, a.mass_est, a.blocks_read, a.lse_out, a.order_out, a.scores_out, a.traffic_out);
     return hipGetLastError();
 }
 
+template <int DT, int G>
+static hipError_t launch_solo_g(const KvView &kv, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st) {
+    if constexpr (G >= 8) {
+        if (score_on_matrix_cores(G, kv.num_kv_heads, a.scorer))
+            return a.scorer == 1 ? launch_solo_t<DT, G, 1, true>(kv, a, ws, st) : launch_solo_t<DT, G, 0, true>(kv, a, ws, st);
+    }
+    return a.scorer == 2 ? launch_solo_t<DT, G, 2>(kv, a, ws, st)
+                         : (a.scorer == 1 ? launch_solo_t<DT, G, 1>(kv, a, ws, st) : launch_solo_t<DT, G, 0>(kv, a, ws, st));
+}
+
 hipError_t launch_solo(const KvView &kv, int dtype, int G, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st) {
 #define PSA_CASE(DT, GG) \
-    if (dtype == DT && G == GG) \
-        return a.scorer == 2 ? launch_solo_t<DT, GG, 2>(kv, a, ws, st) \
-                             : (a.scorer == 1 ? launch_solo_t<DT, GG, 1>(kv, a, ws, st) : launch_solo_t<DT, GG, 0>(kv, a, ws, st));
+    if (dtype == DT && G == GG) return launch_solo_g<DT, GG>(kv, a, ws, st);
     PSA_CASE(0, 1) PSA_CASE(0, 2) PSA_CASE(0, 4) PSA_CASE(0, 8)
     PSA_CASE(1, 1) PSA_CASE(1, 2) PSA_CASE(1, 4) PSA_CASE(1, 8)
 #undef PSA_CASE

@@ -76,12 +76,25 @@ def test_the_line_between_the_paths(psa, batch, ctx):
     assert (read[:, 0] <= blocks).all() and (read[:, 1] <= read[:, 0]).all()
 
 
-def test_scores_on_the_matrix_cores_have_another_order_of_sums(psa):
-    """G = 8 with five KV heads: the general path scores on the matrix cores, so here the oracle is what counts."""
-    li = _layer(8, 5, "f16", 3, 2000, 100)
-    out = gc.run_gpu_decode(li, 0.95, 1)
-    rep = gc.check_decode_against_oracle(gc.to_problem(li), out, 0.95, 1)
-    rep.assert_accounted(max_rank_swaps=1)
+@pytest.mark.parametrize("H,dtype", [(1, "bf16"), (1, "f16"), (3, "f16"), (5, "bf16")])
+@pytest.mark.parametrize("ctx,ctx_min", [(1, 1), (250, 3), (513, 513), (1041, 100), (2048, 1500), (2049, 30), (4096, 1024)])
+def test_scores_on_the_matrix_cores(psa, H, dtype, ctx, ctx_min):
+    """G = 8 and a KV-head count that is 1 or does not divide 16: both paths score on the matrix cores, so a tuning that
+    takes the call to the general path moves no bit of a score, and with it no rank and no stop."""
+    blocks = (ctx + 15) // 16
+    batch = 5 if blocks <= 128 else (3 * blocks + 4 * H - 1) // (4 * H)
+    li = _layer(8, H, dtype, batch, ctx, ctx_min)
+    kv = gc.to_kv(li)
+    meta = psa.build_block_metadata(kv, page_fill=li.page_fill)
+    for eps, m, scorer in [(0.9, 1, 0), (0.6, 3, 1), (1.0, 1, 0)]:
+        args = dict(scorer=scorer, want_order=True, want_scores=True)
+        one = psa.decode_attention(kv, li.q, meta, eps, m, **args)
+        five = psa.decode_attention(kv, li.q, meta, eps, m, tuning=_general(psa), **args)
+        _same(one, five)
+    if batch == 5:
+        out = gc.run_gpu_decode(li, 0.95, 1)
+        rep = gc.check_decode_against_oracle(gc.to_problem(li), out, 0.95, 1)
+        rep.assert_accounted(max_rank_swaps=1)
 
 
 def test_bad_tables_and_lengths_are_clamped_and_reported(psa):
