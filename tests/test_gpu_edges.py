@@ -118,6 +118,31 @@ def test_inputs_only_the_device_can_see_are_wrong(psa):
     assert psa.read_device_error(again._workspace) == 0
 
 
+@pytest.mark.parametrize("max_blocks", [20, 300])
+def test_a_pool_without_pages_is_never_read(psa, max_blocks):
+    """num_pages = 0 leaves the pools and the metadata without an address.  Requests with tokens then have table entries
+    that no page can match: they read as empty and the error word says so, in the one-launch path (20 columns), the
+    general path (300) and the dense control; without tokens there is nothing to report."""
+    B, H, G = 3, 2, 4
+    pool = torch.empty((0, H, 16, 128), dtype=torch.float16, device="cuda")
+    assert pool.data_ptr() == 0
+    q = torch.randn((B, H * G, 128), device="cuda").half()
+    meta = torch.empty((0, H, 2, 128), dtype=torch.float16, device="cuda")
+    for lens, want in (([0, 0, 0], 0), ([40, 0, 16 * max_blocks], 1), ([16 * max_blocks + 1, 0, 5], 3), ([0, -1, 0], 2)):
+        kv = psa.KvCache(pool, pool, torch.zeros((B, max_blocks), dtype=torch.int32, device="cuda"),
+                         torch.tensor(lens, dtype=torch.int32, device="cuda"), H * G)
+        for o in (psa.decode_attention(kv, q, meta, 0.9, 1, want_order=True, want_traffic=True),
+                  psa.topk_attention(kv, q, meta, 2, want_order=True, want_traffic=True)):
+            torch.cuda.synchronize()
+            assert psa.read_device_error(o._workspace) == want
+            assert not o.out.any() and not o.n_selected.any() and not o.mass_est.any() and not o.blocks_read.any()
+            assert torch.isneginf(o.lse).all() and (o.order == -1).all() and not o.traffic.any()
+        out, lse = psa.dense_attention(kv, q)
+        torch.cuda.synchronize()
+        assert psa.read_device_error(out._workspace) == want
+        assert not out.any() and torch.isneginf(lse).all()
+
+
 def test_bench_read_probe_sizes_and_alignment(psa):
     """The benchmark's measurement aid (bench_probe.hip) reads and keeps nothing: any size runs (empty, below one
     load, ragged, several workgroups' worth), the source is unchanged, a misaligned source is refused on the host."""
