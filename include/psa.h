@@ -271,8 +271,8 @@ psa_status psa_decode_attention_static(const psa_kv_desc *desc, const void *q, c
  * "KV Cache Selection": a fixed top-k, e.g. k = 64 or 128 blocks).  Same scoring and ranking as
  * psa_decode_attention; every query head then attends exactly the first min(k_blocks, N) ranked
  * blocks, and keys are read no further than that.  mass_est is P_acc of Algorithm 1 (lines 15-16)
- * evaluated at that point.  All other arguments, the workspace size and the error behaviour are those
- * of psa_decode_attention; k_blocks < 1 is PSA_ERR_INVALID_ARG.
+ * evaluated at that point (NaN for a head whose logits there are no numbers).  All other arguments, the
+ * workspace size and the error behaviour are those of psa_decode_attention; k_blocks < 1 is PSA_ERR_INVALID_ARG.
  */
 psa_status psa_topk_attention(const psa_kv_desc *desc, const void *q, const void *meta, int32_t k_blocks,
                               int32_t scorer, float *out, int32_t *n_selected, float *mass_est, int32_t *blocks_read,

@@ -12,6 +12,12 @@ __device__ __forceinline__ float p_acc(float Lacc, float Lmin, int n_left) {
     return 1.0f / (1.0f + (float)n_left * exp2_fast(Lmin - Lacc));
 }
 
+// Line 17's test.  P_acc is no number for a head whose logits are none: it passes no threshold of the caller's, but ends
+// where a fixed budget of blocks below N ends, which is tested there alone (m = budget) and against kBudgetEps.
+constexpr float kBudgetEps = -1.0f;
+__device__ __forceinline__ float stop_threshold(float eps, int budget, int N) { return budget > 0 && budget < N ? kBudgetEps : eps; }
+__device__ __forceinline__ bool passes_test(float P, float eps) { return fmaxf(P, 0.0f) > eps; }
+
 // Scaled logits (log2 units) of one block against the heads of its group.  k: the block's key slice as four coalesced
 // 1 KiB rows of lanes; qb: the B operand (column n = lane % 16 is head n, zero beyond the group).  Loading the slice in
 // the operand's layout would touch sixteen 64-byte segments per instruction, so the wave turns it into that layout
@@ -120,7 +126,7 @@ __device__ __forceinline__ int fold_group(float &L, float &M, float Cacc, float 
     const int b0 = (base + jl) * KU, n_end = min(b0 + KU, N);
     // a stop inside a chunk needs a position where the rule is tested (line 17 is reached every m blocks and
     // at the last block) and, P_acc being non-decreasing, a pass at the chunk's end
-    const bool passes = ((n_end / m) * m > b0 || n_end == N) && p_acc(L, M, N - n_end) > eps;
+    const bool passes = ((n_end / m) * m > b0 || n_end == N) && passes_test(p_acc(L, M, N - n_end), eps);
     while (j < k) {
         const unsigned long long cand = __ballot(jl >= j && jl < k && stop == ~0ull && passes);
         if (cand == 0ull) return k;
@@ -152,7 +158,7 @@ __device__ __forceinline__ int fold_group(float &L, float &M, float Cacc, float 
             const int nn = cb0 + (64 * u + lane) / G + 1;
             const float P = p_acc(fl, fm, N - nn);
             const unsigned long long hits =
-                __ballot(64 * u + lane < cnt && (nn % m == 0 || nn == N) && P > eps) & head_lanes;
+                __ballot(64 * u + lane < cnt && (nn % m == 0 || nn == N) && passes_test(P, eps)) & head_lanes;
             const int src = hits ? (__ffsll((long long)hits) - 1) : 0;
             const float Pf = __shfl(P, src);
             if (scan && !found && hits) {

@@ -207,6 +207,7 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
         if (lane == 0) atomicAdd(&ws.header[kClosedStreams], 1);
         return;
     }
+    eps = stop_threshold(eps, budget, N);
     const int S = kv.batch * kv.num_kv_heads;
     const float odds = eps > 0.0f ? (1.0f - eps) / eps : INFINITY;      // (1 - eps) / eps of the stop test
     float Cacc = -INFINITY, Cmin = INFINITY;   // my head's (L_acc, L_min) at the start of the group

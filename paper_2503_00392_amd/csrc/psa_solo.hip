@@ -216,6 +216,7 @@ __global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, cons
     // ---- keys and the stop rule (lines 7-18), 64 ranked blocks at a time ----------------------------------------
     const int nlim = budget > 0 ? min(N, budget) : N;
     const int nch = (nlim + kSoloChunk - 1) / kSoloChunk;      // chunks that may ever be folded
+    eps = stop_threshold(eps, budget, N);
     float *logits = ws.logits + (size_t)s * kv.max_blocks * (kPage * G);
     int nread = 0;                                             // key slices read (traffic accounting)
     if (nch > 0) {

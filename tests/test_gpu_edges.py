@@ -118,6 +118,43 @@ def test_inputs_only_the_device_can_see_are_wrong(psa):
     assert psa.read_device_error(again._workspace) == 0
 
 
+@pytest.mark.parametrize("bad", ["query", "key", "all keys"])
+@pytest.mark.parametrize("ctx,G", [(1000, 4), (1800, 8), (5000, 4), (5000, 1)])
+def test_a_fixed_budget_holds_for_heads_without_a_number(psa, ctx, G, bad):
+    """A NaN query, a NaN in the best block or in every key of one request: P_acc of a head is then no number and passes no
+    test, and the head attends its budget all the same.  Other requests, and the other heads of a group whose keys are
+    sound, come out as without the NaN.  (1000 and 1800 tokens: one launch; 5000: the general path.)"""
+    cfg = get_config(1).scaled(batch=2, ctx=ctx, num_q_heads=2 * G, num_kv_heads=2)
+    li = generate_layer(cfg, device="cuda")
+    kv = gc.to_kv(li)
+    meta = psa.build_block_metadata(kv, page_fill=li.page_fill)
+    N = (ctx + 15) // 16
+    first = psa.topk_attention(kv, li.q, meta, 1, want_order=True)
+    q, nan = li.q.clone(), float("nan")
+    if bad == "query":
+        q[0, G - 1] = q[0, 0]           # (the group's scores are the maximum over its heads that are numbers)
+        sound = q.clone()
+        q[0, G - 1, 7] = nan
+    elif bad == "key":
+        li.k_pool[li.block_table[0, first.order[0, 0, 0]].long(), 0, 3, 9] = nan       # (the metadata stays as it was)
+    else:
+        li.k_pool[li.block_table[0, :N].long(), 0] = nan
+    for k in (1, 5, 32, 33, N - 1, N, N + 7):
+        top = psa.topk_attention(kv, q, meta, k, want_order=True, want_traffic=True)
+        torch.cuda.synchronize()
+        assert psa.read_device_error(top._workspace) == 0
+        want = min(k, N)
+        assert (top.n_selected == want).all() and (top.blocks_read == want).all()
+        assert (top.traffic[:, :, 1] == want).all() and (top.traffic[:, :, 0] >= want).all()
+        assert torch.isfinite(top.out[1]).all() and torch.isfinite(top.out[0, G:]).all()
+        if bad == "query":
+            clean = psa.topk_attention(kv, sound, meta, k)
+            for name in ("out", "mass_est", "lse"):
+                a, b = getattr(top, name).clone(), getattr(clean, name).clone()
+                a[0, G - 1] = b[0, G - 1] = 0
+                assert torch.equal(a, b), name
+
+
 @pytest.mark.parametrize("max_blocks", [20, 300])
 def test_a_pool_without_pages_is_never_read(psa, max_blocks):
     """num_pages = 0 leaves the pools and the metadata without an address.  Requests with tokens then have table entries
