@@ -30,9 +30,7 @@ __device__ __forceinline__ f32x4_t block_logits(const uint4 (&k)[4], const uint4
     f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) stg[(kk * 4 + kq) * 17 + n] = k[kk];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    lds_wave_sync();
     uint4 a[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) a[kk] = stg[arow * 17 + kk * 4 + kq];

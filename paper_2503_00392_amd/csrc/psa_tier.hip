@@ -350,11 +350,11 @@ __device__ __forceinline__ void rank_pass(const uint32_t (&key)[kRankPer], uint3
                 peers &= bit ? bal : ~bal;
             }
             const uint32_t in_wave = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
-            const uint32_t before = hist[wave][digit];     // (the row is this wave's own; its accesses stay in order)
+            const uint32_t before = hist[wave][digit];     // (the row is this wave's own)
             pos[k] = before + in_wave;
-            __builtin_amdgcn_wave_barrier();
+            lds_wave_sync();
             if (live && in_wave == 0) hist[wave][digit] = before + (uint32_t)__popcll(peers);
-            __builtin_amdgcn_wave_barrier();
+            lds_wave_sync();
         }
     }
     __syncthreads();
