@@ -153,6 +153,29 @@ def test_slots_are_taken_oldest_first(psa, num_slots):
     assert model.clock == 266
 
 
+@pytest.mark.parametrize("num_slots", [16384, 16385, 17001])
+def test_more_misses_than_slots_that_may_be_taken(psa, num_slots):
+    """24000 slices over a smaller pool, in one workgroup (16384 slots) and over the chip: the number of slots that may be
+    taken limits what is placed -- all of them, none (the whole pool used by this very update), those of the request that
+    sat out, and those outside the busy range."""
+    cfg = get_config(3).scaled(batch=3, ctx=16000, layers=1)
+    li = generate_layer(cfg, layer=2, device="cuda")
+    n_slices = li.k_pool.shape[0] * li.k_pool.shape[1]
+    tier = psa.Tier(n_slices, num_slots)
+    model = TierModel(n_slices, num_slots)
+    L = Layer(psa, li, tier, 0)
+    out = psa.decode_attention(L.dev, li.q, L.meta_dev, 0.9, 1, want_order=True)
+    all_blocks = (li.ctx_lens + 15).to(out.blocks_read.device)[:, None] // 16
+    placed = []
+    for sits_out, busy in ((3, (0, 0)), (3, (0, 0)), (0, (0, 0)), (1, (0, n_slices // 2)), (3, (0, n_slices))):
+        out.blocks_read.copy_(all_blocks.expand_as(out.blocks_read))
+        if sits_out < 3:
+            out.blocks_read[sits_out] = 0
+        placed.append(_update(psa, L, out, tier, model, busy=busy).promoted)
+        _check_tables(tier, model, [L])
+    assert placed[0] == num_slots and placed[1] == 0 and placed[2] > 0 and placed[4] == 0
+
+
 def test_two_layers_share_a_small_pool_over_a_decode_loop(psa):
     """Two layers, one pool too small for both: drifting queries, a token appended per step, the other
     layer named busy in every update.  Outputs equal the single-tier run's; tables equal the model's."""
