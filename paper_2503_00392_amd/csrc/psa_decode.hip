@@ -79,6 +79,48 @@ static WsLayout layout(const psa_kv_desc *d, const DecodePlan &p) {
 
 size_t decode_workspace_bytes_plan(const psa_kv_desc *d, const DecodePlan &p) { return layout(d, p).total; }
 
+// num_pages == 0: the kernels read a bad table entry as page 0, which does not exist then (the pools may be NULL), so no
+// kernel that reads slices is launched.  Every request comes out empty; those with tokens have table entries outside the
+// pool, which the error word says.  Workgroup 0 finds the word, the others write the outputs (each may be NULL but `out`).
+__global__ __launch_bounds__(256) void no_pages_kernel(KvView kv, int32_t *header, float *out, int32_t *n_selected, float *mass_est,
+                                                       int32_t *blocks_read, float *lse, int32_t *order, int32_t *traffic) {
+    if (blockIdx.x == 0) {
+        int page_bad = 0, ctx_bad = 0;
+        for (int r = threadIdx.x; r < kv.batch; r += 256) {
+            const int ctx = ctx_clamped_quiet(kv, r);
+            page_bad |= ctx > 0;
+            ctx_bad |= ctx != kv.ctx_lens[r];
+        }
+        page_bad = __syncthreads_or(page_bad);
+        ctx_bad = __syncthreads_or(ctx_bad);
+        if (threadIdx.x == 0) {
+            header[0] = 0;
+            header[1] = (page_bad ? PSA_DEVERR_PAGE_RANGE : 0) | (ctx_bad ? PSA_DEVERR_CTX_RANGE : 0);
+        }
+        return;
+    }
+    const long long heads = (long long)kv.batch * kv.num_q_heads, S = (long long)kv.batch * kv.num_kv_heads;
+    const long long first = (long long)(blockIdx.x - 1) * 256 + threadIdx.x, step = (long long)(gridDim.x - 1) * 256;
+    for (long long i = first; i < heads * kHeadDim; i += step) out[i] = 0.0f;
+    for (long long i = first; i < heads; i += step) {
+        if (n_selected) n_selected[i] = 0;
+        if (mass_est) mass_est[i] = 0.0f;
+        if (lse) lse[i] = -INFINITY;
+    }
+    for (long long i = first; i < S; i += step) {
+        if (blocks_read) blocks_read[i] = 0;
+        if (traffic) traffic[2 * i] = traffic[2 * i + 1] = 0;
+    }
+    if (order)
+        for (long long i = first; i < S * kv.max_blocks; i += step) order[i] = -1;
+}
+
+hipError_t launch_no_pages(const KvView &kv, const DecodeArgs &a, int32_t *header, hipStream_t st) {
+    no_pages_kernel<<<1 + 1024, 256, 0, st>>>(kv, header, a.out, a.n_selected, a.mass_est, a.blocks_read, a.lse_out, a.order_out,
+                                              a.traffic_out);
+    return hipGetLastError();
+}
+
 hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const DecodePlan &plan, void *wsp,
                          hipStream_t st) {
     const KvView kv = make_view(d);
@@ -99,9 +141,15 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     ws.max_units = plan.max_chunks;
     const int G = d->num_q_heads / d->num_kv_heads;
     if (kv.batch == 0) return hipSuccess;
-    if (plan.solo) return launch_solo(kv, d->dtype, G, a, ws, st);
     hipEvent_t *ev = plan.events;
     hipError_t e;
+    if (kv.num_pages == 0) {
+        if (ev) (void)hipEventRecord(ev[0], st);
+        e = launch_no_pages(kv, a, ws.header, st);
+        for (int i = 1; ev && i < 6; ++i) (void)hipEventRecord(ev[i], st);
+        return e;
+    }
+    if (plan.solo) return launch_solo(kv, d->dtype, G, a, ws, st);
     if (ev) (void)hipEventRecord(ev[0], st);
     if ((e = launch_score(kv, d->dtype, G, a.scorer, a.q, a.meta, ws, a.scores_out, st)) != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[1], st);

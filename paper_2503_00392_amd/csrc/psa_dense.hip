@@ -27,8 +27,8 @@ __global__ __launch_bounds__(256) void dense_split_kernel(KvView kv, const uint8
     // the call's error word: cleared here, set by the merge kernel from what the workgroups found (a launch of its own for
     // the clearing cost 5 us)
     if (split == 0 && s == 0 && tid < 64) header[tid] = 0;
-    const int ctx = ctx_clamped_quiet(kv, r);
-    int err = ctx_error_bits(kv, r);
+    const int raw_ctx = kv.ctx_lens[r], ctx = ctx_clamped_quiet(kv, r);
+    int err = raw_ctx != ctx ? PSA_DEVERR_CTX_RANGE : 0;
     const int N = (ctx + kPage - 1) / kPage;
     // every request is cut into the same number of splits, each over its own length: ragged batches stay balanced
     const int bps = min(blocks_per_split, (N + nsplit - 1) / nsplit);
@@ -219,6 +219,12 @@ hipError_t launch_dense(const psa_kv_desc *d, const void *q, float *out, float *
     const KvView kv = make_view(d);
     const int G = d->num_q_heads / d->num_kv_heads;
     const int nsplit = dense_num_splits(d);
+    if (kv.num_pages == 0) {
+        DecodeArgs a{};
+        a.out = out;
+        a.lse_out = lse;
+        return launch_no_pages(kv, a, reinterpret_cast<int32_t *>(ws), st);
+    }
 #define PSA_CASE(DT, GG) \
     if (d->dtype == DT && G == GG) return launch_dense_t<DT, GG>(kv, q, out, lse, ws, nsplit, st);
     PSA_CASE(0, 1) PSA_CASE(0, 2) PSA_CASE(0, 4) PSA_CASE(0, 8)

@@ -339,21 +339,17 @@ __device__ __forceinline__ int clamp_page(int page, int num_pages, int32_t *head
     return page;
 }
 
-// Tokens of request r, clamped into the request's row of the block table.
-__device__ __forceinline__ int ctx_in_table(const KvView &kv, int r) {
+// Blocks of request r, clamped into [0, max_blocks]; reports a context outside the table.
+__device__ __forceinline__ int ctx_clamped(const KvView &kv, int r, int32_t *header) {
+    int ctx = kv.ctx_lens[r];
+    if (ctx < 0) { set_error(header, PSA_DEVERR_CTX_RANGE); ctx = 0; }
+    if (ctx > kv.max_blocks * kPage) { set_error(header, PSA_DEVERR_CTX_RANGE); ctx = kv.max_blocks * kPage; }
+    return ctx;
+}
+
+__device__ __forceinline__ int ctx_clamped_quiet(const KvView &kv, int r) {
     const int ctx = kv.ctx_lens[r];
     return ctx < 0 ? 0 : (ctx > kv.max_blocks * kPage ? kv.max_blocks * kPage : ctx);
-}
-// The tokens every kernel works with: those, or none where the pool has no pages at all (a bad table entry is read as
-// page 0, which does not exist then).
-__device__ __forceinline__ int ctx_clamped_quiet(const KvView &kv, int r) {
-    const int ctx = ctx_in_table(kv, r);
-    return kv.num_pages > 0 ? ctx : 0;
-}
-// What the error word says about the length: outside the table, or blocks where no table entry can be a page.
-__device__ __forceinline__ int ctx_error_bits(const KvView &kv, int r) {
-    const int in_table = ctx_in_table(kv, r);
-    return (kv.ctx_lens[r] != in_table ? PSA_DEVERR_CTX_RANGE : 0) | (in_table > 0 && kv.num_pages <= 0 ? PSA_DEVERR_PAGE_RANGE : 0);
 }
 __device__ __forceinline__ int clamp_page_quiet(int page, int num_pages) {
     return (unsigned)page >= (unsigned)num_pages ? 0 : page;

@@ -80,6 +80,8 @@ struct DecodeArgs {
     float *scores_out;
     int32_t *traffic_out;
 };
+// A call over a pool without pages: empty outputs and the error word.
+hipError_t launch_no_pages(const KvView &kv, const DecodeArgs &a, int32_t *header, hipStream_t st);
 // psa_tier.hip
 size_t tier_state_bytes(long long total_slices, long long num_slots);
 size_t tier_staging_bytes(long long staging_slices);

@@ -137,8 +137,7 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
 #pragma unroll
     for (int j = 0; j < K; ++j) page_at[j] = table[min(tid + j * nthreads, kv.max_blocks - 1)];
     // the scoring kernel clamps silently (it clears the error word); out-of-range inputs are reported here
-    const int ctx = ctx_clamped_quiet(kv, r);
-    if (tid == 0 && part == 0 && ctx_error_bits(kv, r)) set_error(ws.header, ctx_error_bits(kv, r));
+    const int ctx = (tid == 0 && blockIdx.x == 0) ? ctx_clamped(kv, r, ws.header) : ctx_clamped_quiet(kv, r);
     const int N = (ctx + kPage - 1) / kPage;
 #pragma unroll
     for (int j = 0; j < K; ++j) bad_page |= tid + j * nthreads < N && (unsigned)page_at[j] >= (unsigned)kv.num_pages;

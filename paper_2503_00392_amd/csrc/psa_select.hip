@@ -98,7 +98,8 @@ constexpr int kSelectThreads = 256;  // 4 waves; four such workgroups fit a CU (
 
 // Tokens of stream s's request, clamped like everywhere else.
 __device__ __forceinline__ int stream_ctx(const KvView &kv, int s) {
-    return ctx_clamped_quiet(kv, s / kv.num_kv_heads);
+    const int ctx = kv.ctx_lens[s / kv.num_kv_heads];
+    return ctx < 0 ? 0 : (ctx > kv.max_blocks * kPage ? kv.max_blocks * kPage : ctx);
 }
 
 __device__ __forceinline__ int window_of(int window, int frontier) {

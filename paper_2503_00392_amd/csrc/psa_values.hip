@@ -188,7 +188,8 @@ __global__ __launch_bounds__(512) void finalize_kernel(KvView kv, DecodeWs ws, i
     const int s = blockIdx.x / G, g = blockIdx.x % G, tid = threadIdx.x;
     const int cq = tid & 31, uj = tid >> 5;
     const int r = s / kv.num_kv_heads, h = s % kv.num_kv_heads;
-    const int ctx = ctx_clamped_quiet(kv, r);
+    int ctx = kv.ctx_lens[r];
+    ctx = ctx < 0 ? 0 : (ctx > kv.max_blocks * kPage ? kv.max_blocks * kPage : ctx);
     const int N = (ctx + kPage - 1) / kPage;
     const StreamCtl *ctl = &ws.ctl[s];
     const unsigned long long st = ctl->stop[g];

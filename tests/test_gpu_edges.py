@@ -158,8 +158,9 @@ def test_a_fixed_budget_holds_for_heads_without_a_number(psa, ctx, G, bad):
 @pytest.mark.parametrize("max_blocks", [20, 300])
 def test_a_pool_without_pages_is_never_read(psa, max_blocks):
     """num_pages = 0 leaves the pools and the metadata without an address.  Requests with tokens then have table entries
-    that no page can match: they read as empty and the error word says so, in the one-launch path (20 columns), the
-    general path (300) and the dense control; without tokens there is nothing to report."""
+    that no page can match: they read as empty and the error word says so, whether the table would take the call to the
+    one-launch path (20 columns) or to the general one (300), and in the dense control; without tokens there is nothing to
+    report."""
     B, H, G = 3, 2, 4
     pool = torch.empty((0, H, 16, 128), dtype=torch.float16, device="cuda")
     assert pool.data_ptr() == 0
