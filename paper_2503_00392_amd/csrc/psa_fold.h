@@ -15,7 +15,10 @@ __device__ __forceinline__ float p_acc(float Lacc, float Lmin, int n_left) {
 // Line 17's test.  P_acc is no number for a head whose logits are none: it passes no threshold of the caller's, but ends
 // where a fixed budget of blocks below N ends, which is tested there alone (m = budget) and against kBudgetEps.
 constexpr float kBudgetEps = -1.0f;
-__device__ __forceinline__ float stop_threshold(float eps, int budget, int N) { return budget > 0 && budget < N ? kBudgetEps : eps; }
+__device__ __forceinline__ float stop_threshold(float eps, int budget, int N) {     // (uniform: in a scalar register)
+    const float t = budget > 0 && budget < N ? kBudgetEps : eps;
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(t)));
+}
 __device__ __forceinline__ bool passes_test(float P, float eps) { return fmaxf(P, 0.0f) > eps; }
 
 // Scaled logits (log2 units) of one block against the heads of its group.  k: the block's key slice as four coalesced
