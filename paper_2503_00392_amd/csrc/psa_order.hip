@@ -251,8 +251,6 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
     int32_t *ord = ws.order + (size_t)s * kv.max_blocks;
     int32_t *rpage = ws.ranked_page + (size_t)s * kv.max_blocks;
     int32_t *oout = order_out ? order_out + (size_t)s * kv.max_blocks : nullptr;
-    if (oout && part == 0)
-        for (int p = N + tid; p < kv.max_blocks; p += nthreads) oout[p] = -1;
 
     // With a second tier, a block whose slice has a slot is read from the slot: ranked_page then holds ~slot (< 0).
     auto location = [&](int page) {
@@ -345,7 +343,12 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
                 if (oout) oout[p] = b;
             }
         }
+        if (oout)
+            for (int p = N + tid; p < kv.max_blocks; p += holders) oout[p] = -1;
+        return;
     }
+    if (oout && part == 0)
+        for (int p = N + tid; p < kv.max_blocks; p += nthreads) oout[p] = -1;
 }
 
 template <bool TIER>
