@@ -4,8 +4,22 @@
 #include <hip/hip_runtime.h>
 
 #include "psa_device.h"
+#include "psa_once.h"
 
 namespace psa {
+
+// More than 64 KiB of dynamic LDS has to be asked for, per kernel and GPU.  `once` belongs to that kernel.
+template <class Kernel>
+hipError_t allow_dynamic_lds(OncePerDevice &once, Kernel kernel, size_t bytes) {
+    int device = -1;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess)
+        e = once(device, [&] {
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        });
+    if (e != hipSuccess) (void)hipGetLastError();      // (reported here; the next launch's check must not see it again)
+    return e;
+}
 
 // Layout of a psa_tier's state: header, slice -> slot, slot -> slice, slot -> stamp, slice -> staging entry.
 inline size_t tier_align(size_t v) { return (v + 255) / 256 * 256; }

@@ -361,10 +361,9 @@ static hipError_t launch_order_t(dim3 grid, const KvView &kv, const DecodeWs &ws
     } else if (Np == 4096) {
         order_kernel<4, TIER><<<grid, Np / 4, lds, st>>>(kv, ws, G, KU, budget, Np, bitonic, slot_of, order_out);
     } else {
-        // (more than 64 KiB of dynamic LDS has to be asked for once)
-        static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(order_kernel<8, TIER>),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kMaxBlocks * 8 + 512);
-        if (raised != hipSuccess) return raised;
+        static OncePerDevice once;
+        const hipError_t e = allow_dynamic_lds(once, order_kernel<8, TIER>, kMaxBlocks * 8 + 512);
+        if (e != hipSuccess) return e;
         order_kernel<8, TIER><<<grid, Np / 8, lds, st>>>(kv, ws, G, KU, budget, Np, bitonic, slot_of, order_out);
     }
     return hipGetLastError();

@@ -379,10 +379,9 @@ __global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, cons
 
 template <int DT, int G, int SCORER, bool MFMA = false>
 static hipError_t launch_solo_t(const KvView &kv, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st) {
-    // (more than 64 KiB of dynamic LDS has to be asked for, once per kernel)
-    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(solo_kernel<DT, G, SCORER, MFMA>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SoloShared<G>));
-    if (raised != hipSuccess) return raised;
+    static OncePerDevice once;
+    const hipError_t e = allow_dynamic_lds(once, solo_kernel<DT, G, SCORER, MFMA>, sizeof(SoloShared<G>));
+    if (e != hipSuccess) return e;
     const unsigned S = (unsigned)(kv.batch * kv.num_kv_heads);
     solo_kernel<DT, G, SCORER, MFMA><<<S + 1, 1024, sizeof(SoloShared<G>), st>>>(
         kv, ws, (const uint8_t *)a.q, (const uint8_t *)a.meta, a.threshold, a.check_granularity, a.budget_blocks, a.out,

@@ -578,9 +578,8 @@ hipError_t launch_tier_update(const psa_kv_desc *d, const int32_t *order, const 
     // attention: 460 -> 387 us), and a 32-bit word holds the age and the slot.
     if (t.num_slots <= kRankSlots) {
         constexpr int kRankLds = (kRankSlots + kRankWaves * kRankBins) * 4;
-        static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(tier_rank_kernel),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kRankLds);
-        if (raised != hipSuccess) return raised;
+        static OncePerDevice once;
+        if ((e = allow_dynamic_lds(once, tier_rank_kernel, kRankLds)) != hipSuccess) return e;
         tier_rank_kernel<<<1, kRankThreads, kRankLds, st>>>(t, miss_count, miss_offset, S, busy_first, busy_count, cand_in);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
