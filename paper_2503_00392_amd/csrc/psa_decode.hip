@@ -45,11 +45,12 @@ DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t) {
     // 18 to 33 us against 31 to 33 for the chain, 256 streams: 28 against 48).  Above, a stream that selects nearly all
     // its blocks wants more than one, unless there are streams for most of the chip: at 256 blocks 63 us against 32 with 8
     // streams, 76 against 82 with 192; at 192 blocks 53 against 53 with 128.  Hence three streams for four blocks.
-    // Whoever tunes the general path, times its phases or brings a second tier gets the general path.
+    // Whoever tunes the general path, times its phases or brings a second tier gets the general path.  So does a call of more
+    // streams than one grid of workgroups of 1024 threads can have (fewer than 2^32 threads).
     const bool tuned = t && (t->window_chunks > 0 || t->spin_limit > 0 || t->force_bitonic || t->phase_events ||
                              (t->chunk_blocks && t->chunk_blocks != 32));
     const int mb = d->max_blocks_per_seq;
-    p.solo = !d->tier && !tuned && mb <= kSoloBlocks && (mb <= 128 || 4 * S >= 3 * mb);
+    p.solo = !d->tier && !tuned && mb <= kSoloBlocks && (mb <= 128 || 4 * S >= 3 * mb) && (S + 1ll) * kSoloThreads < (1ll << 32);
     return p;
 }
 

@@ -123,7 +123,8 @@ hipError_t launch_select(const KvView &kv, int dtype, int G, const void *q, cons
                          int m, int budget_blocks, const DecodePlan &plan, hipStream_t st);
 hipError_t launch_attend(const KvView &kv, int dtype, int G, const DecodeWs &ws, const DecodePlan &plan,
                          hipStream_t st);
-// psa_solo.hip: all of the above in one kernel
+// psa_solo.hip: all of the above in one kernel, 1 + (streams) workgroups of kSoloThreads
+constexpr int kSoloThreads = 1024;
 hipError_t launch_solo(const KvView &kv, int dtype, int G, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st);
 hipError_t launch_finalize(const KvView &kv, const DecodeWs &ws, int G, int VU, float *out,
                            int32_t *n_selected, float *mass_est, int32_t *blocks_read, float *lse_out,

@@ -78,7 +78,7 @@ __device__ __forceinline__ void solo_report(const KvView &kv, int32_t *header) {
 
 // grid (1 + S), 1024 threads; the first workgroup writes the error word.  MFMA: scores on the matrix cores.
 template <int DT, int G, int SCORER, bool MFMA>
-__global__ __launch_bounds__(1024) void solo_kernel(KvView kv, DecodeWs ws, const uint8_t *__restrict__ q,
+__global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs ws, const uint8_t *__restrict__ q,
                                                     const uint8_t *__restrict__ meta, float eps, int m, int budget,
                                                     float *__restrict__ out, int32_t *__restrict__ n_selected,
                                                     float *__restrict__ mass_est, int32_t *__restrict__ blocks_read,
@@ -383,7 +383,7 @@ static hipError_t launch_solo_t(const KvView &kv, const DecodeArgs &a, const Dec
     const hipError_t e = allow_dynamic_lds(once, solo_kernel<DT, G, SCORER, MFMA>, sizeof(SoloShared<G>));
     if (e != hipSuccess) return e;
     const unsigned S = (unsigned)(kv.batch * kv.num_kv_heads);
-    solo_kernel<DT, G, SCORER, MFMA><<<S + 1, 1024, sizeof(SoloShared<G>), st>>>(
+    solo_kernel<DT, G, SCORER, MFMA><<<S + 1, kSoloThreads, sizeof(SoloShared<G>), st>>>(
         kv, ws, (const uint8_t *)a.q, (const uint8_t *)a.meta, a.threshold, a.check_granularity, a.budget_blocks, a.out,
         a.n_selected, a.mass_est, a.blocks_read, a.lse_out, a.order_out, a.scores_out, a.traffic_out);
     return hipGetLastError();

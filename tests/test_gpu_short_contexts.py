@@ -97,6 +97,26 @@ def test_scores_on_the_matrix_cores(psa, H, dtype, ctx, ctx_min):
         rep.assert_accounted(max_rank_swaps=1)
 
 
+def test_more_streams_than_one_launch_can_have(psa):
+    """4194304 streams would be 2^32 threads and a workgroup more: the general path, whose workgroups are smaller, takes
+    them.  All requests share a page and a query, so all results are those of one."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    k, v = (torch.randn((1, 1, 16, 128), generator=gen, device="cuda").half() for _ in range(2))
+    q = torch.randn((1, 1, 128), generator=gen, device="cuda").half()
+
+    def call(batch):
+        kv = psa.KvCache(k, v, torch.zeros((batch, 1), dtype=torch.int32, device="cuda"),
+                         torch.full((batch,), 13, dtype=torch.int32, device="cuda"), 1)
+        meta = psa.build_block_metadata(kv, page_fill=torch.tensor([13], dtype=torch.int32, device="cuda"))
+        out = psa.decode_attention(kv, q.expand(batch, 1, 128).contiguous(), meta, 0.9, 1)
+        torch.cuda.synchronize()
+        assert psa.read_device_error(out._workspace) == 0
+        return out
+    one, many = call(1), call(1 << 22)
+    for name in ("out", "n_selected", "mass_est", "blocks_read", "lse"):
+        assert (getattr(many, name) == getattr(one, name)).all(), name
+
+
 def test_bad_tables_and_lengths_are_clamped_and_reported(psa):
     li = _layer(4, 2, "f16", 3, 900, 900)
     kv = gc.to_kv(li)
