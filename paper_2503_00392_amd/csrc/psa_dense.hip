@@ -5,6 +5,7 @@
 
 namespace psa {
 
+constexpr int kMaxSplits = 1024;   // splits of a request at most: their weights are an array in the merge's LDS
 constexpr int kDenseStride = 132;  // M, l, error bits (head 0), pad, acc[128]
 
 // grid (nsplit, S); 256 threads.  Wave w of the workgroup takes blocks b0+w, b0+w+4, ... and carries its own
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(512) void dense_combine_kernel(const float *__restr
                                                             float *__restrict__ out,
                                                             float *__restrict__ lse, int32_t *header) {
     __shared__ float red[8];
-    __shared__ float wgt[1024];                 // rescale factor of every split (nsplit <= 1024)
+    __shared__ float wgt[kMaxSplits];           // rescale factor of every split
     __shared__ float num_part[4][kHeadDim];
     __shared__ float den_part[4];
     const int s = blockIdx.x / G, g = blockIdx.x % G, tid = threadIdx.x;
@@ -193,6 +194,7 @@ int dense_num_splits(const psa_kv_desc *d) {
     int want = (2048 + S - 1) / S;
     int max_by_len = (d->max_blocks_per_seq + 7) / 8;
     int n = want < max_by_len ? want : max_by_len;
+    if (n > kMaxSplits) n = kMaxSplits;
     return n < 1 ? 1 : n;
 }
 

@@ -181,6 +181,26 @@ def test_a_pool_without_pages_is_never_read(psa, max_blocks):
         assert not out.any() and torch.isneginf(lse).all()
 
 
+@pytest.mark.parametrize("blocks,G", [(8192, 1), (8193, 8), (20011, 4)])
+def test_dense_attention_of_one_very_long_stream(psa, blocks, G):
+    """One request, one KV head, beyond the 131072 tokens of the sparse call: the dense control takes any length, and cuts
+    it into as many splits as its merge has room for."""
+    gen = torch.Generator(device="cuda").manual_seed(blocks)
+    k, v = (torch.randn((blocks, 1, 16, 128), generator=gen, device="cuda").half() for _ in range(2))
+    q = torch.randn((1, G, 128), generator=gen, device="cuda").half()
+    table = torch.randperm(blocks, generator=gen, device="cuda").to(torch.int32)[None]
+    ctx = 16 * blocks - 5
+    kv = psa.KvCache(k, v, table, torch.tensor([ctx], dtype=torch.int32, device="cuda"), G)
+    out, lse = psa.dense_attention(kv, q)
+    torch.cuda.synchronize()
+    assert psa.read_device_error(out._workspace) == 0
+    kk, vv = (x[table[0].long(), 0].reshape(-1, 128)[:ctx].cpu().double() for x in (k, v))
+    logits = q[0].cpu().double() @ kk.T / 128 ** 0.5
+    want = torch.softmax(logits, 1) @ vv
+    assert gc.rel_l2(out[0].cpu().double().numpy(), want.numpy()).max() <= gc.OUT_RTOL
+    assert (lse[0].cpu().double() - torch.logsumexp(logits, 1)).abs().max() <= gc.LSE_ATOL
+
+
 def test_bench_read_probe_sizes_and_alignment(psa):
     """The benchmark's measurement aid (bench_probe.hip) reads and keeps nothing: any size runs (empty, below one
     load, ragged, several workgroups' worth), the source is unchanged, a misaligned source is refused on the host."""
