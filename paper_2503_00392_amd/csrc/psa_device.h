@@ -331,15 +331,7 @@ __device__ __forceinline__ uint4 ld16_stream(const uint8_t *p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-__device__ __forceinline__ int clamp_page(int page, int num_pages, int32_t *header) {
-    if ((unsigned)page >= (unsigned)num_pages) {
-        set_error(header, PSA_DEVERR_PAGE_RANGE);
-        return 0;
-    }
-    return page;
-}
-
-// Blocks of request r, clamped into [0, max_blocks]; reports a context outside the table.
+// Tokens of request r, clamped into [0, max_blocks]; reports a context outside the table.
 __device__ __forceinline__ int ctx_clamped(const KvView &kv, int r, int32_t *header) {
     int ctx = kv.ctx_lens[r];
     if (ctx < 0) { set_error(header, PSA_DEVERR_CTX_RANGE); ctx = 0; }
