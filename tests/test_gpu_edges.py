@@ -181,6 +181,40 @@ def test_a_pool_without_pages_is_never_read(psa, max_blocks):
         assert not out.any() and torch.isneginf(lse).all()
 
 
+def _shared_pages(psa, batch, H, G, blocks, seed):
+    """Requests over a small pool, every page in many tables; keys too small for anything to stand out."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    k, v = (torch.randn((997, H, 16, 128), generator=gen, device="cuda").mul_(scale).half() for scale in (0.2, 1.0))
+    table = torch.randint(0, 997, (batch, blocks), generator=gen, device="cuda", dtype=torch.int32)
+    lens = torch.randint(8 * blocks, 16 * blocks + 1, (batch,), generator=gen, device="cuda", dtype=torch.int32)
+    q = torch.randn((batch, H * G, 128), generator=gen, device="cuda").half()
+    return psa.KvCache(k, v, table, lens, H * G), q
+
+
+@pytest.mark.parametrize("batch,H,G,blocks", [(1024, 4, 1, 512), (129, 4, 8, 300), (171, 7, 2, 700), (1100, 1, 4, 333)])
+def test_more_streams_than_waves_that_fold_them(psa, batch, H, G, blocks):
+    """The selection kernel folds 512 streams at a time.  4096, 516, 1197 and 1100 streams: the call completes without giving
+    up on any, with threshold 1 it is dense attention, and at any threshold a request's results are bit for bit those it
+    has in a call of its own."""
+    kv, q = _shared_pages(psa, batch, H, G, blocks, blocks)
+    fill = torch.full((997,), 16, dtype=torch.int32, device="cuda")
+    meta = psa.build_block_metadata(kv, page_fill=fill)
+    dense, lse = psa.dense_attention(kv, q)
+    for eps, hint in ((1.0, None), (0.9, None), (0.5, 40)):
+        tuning = psa.Tuning(depth_hint=torch.full((batch, H), hint, dtype=torch.int32, device="cuda")) if hint else None
+        o = psa.decode_attention(kv, q, meta, eps, 1, want_order=True, tuning=tuning)
+        torch.cuda.synchronize()
+        assert psa.read_device_error(o._workspace) == 0
+        if eps == 1.0:
+            assert gc.rel_l2(o.out.cpu().double().numpy(), dense.cpu().double().numpy()).max() <= gc.OUT_RTOL
+            assert (o.lse - lse).abs().max() <= gc.LSE_ATOL
+        for r in (0, 1, batch // 2, batch - 1):
+            alone = psa.KvCache(kv.k_pool, kv.v_pool, kv.block_table[r:r + 1].contiguous(), kv.ctx_lens[r:r + 1].contiguous(), H * G)
+            one = psa.decode_attention(alone, q[r:r + 1].contiguous(), meta, eps, 1, want_order=True)
+            for name in ("out", "n_selected", "mass_est", "blocks_read", "lse", "order"):
+                assert torch.equal(getattr(one, name)[0], getattr(o, name)[r]), (eps, r, name)
+
+
 @pytest.mark.parametrize("blocks,G", [(8192, 1), (8193, 8), (20011, 4)])
 def test_dense_attention_of_one_very_long_stream(psa, blocks, G):
     """One request, one KV head, beyond the 131072 tokens of the sparse call: the dense control takes any length, and cuts
