@@ -125,7 +125,10 @@ typedef struct {
 } psa_kv_desc;
 
 /* Tuning knobs of psa_decode_attention; all zero = library defaults.  They change how much is read
- * speculatively and how work is cut, never which blocks are selected. */
+ * speculatively and how work is cut, never which blocks are selected.  Short contexts (max_blocks_per_seq <= 128,
+ * or <= 256 with at least three (request, KV head) pairs for every four blocks) run as one kernel by default; any
+ * knob but depth_hint takes them to the kernels that longer contexts run, whose results are the same (bit for bit at
+ * the default chunk size) -- so phase_events then times kernels that the call without it does not launch. */
 typedef struct {
     int32_t chunk_blocks;   /* ranked blocks per work item: a multiple of 4 in 8..64 (default 32)      */
     int32_t window_chunks;  /* least number of chunks of one (request, KV head) read beyond the chunks

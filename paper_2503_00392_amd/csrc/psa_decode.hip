@@ -41,10 +41,12 @@ DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t) {
     p.depth_hint = t ? t->depth_hint : nullptr;
     p.events = t ? static_cast<hipEvent_t *>(t->phase_events) : nullptr;
     // One launch for short contexts, where the chain of launches is what a call costs (psa_solo.hip).  One compute unit
-    // does a stream's work there, which is enough up to 128 blocks whatever is selected (2048 tokens, G = 4, 8 streams:
-    // 18 to 33 us against 31 to 33 for the chain, 256 streams: 28 against 48).  Above, a stream that selects nearly all
-    // its blocks wants more than one, unless there are streams for most of the chip: at 256 blocks 63 us against 32 with 8
-    // streams, 76 against 82 with 192; at 192 blocks 53 against 53 with 128.  Hence three streams for four blocks.
+    // does a stream's work there.  Up to 128 blocks that is the better bargain with any number of streams (one launch
+    // against the chain, 2048 tokens, G = 4): where the rule selects little, 17 us against 26 to 30 with 1 to 8 streams, 31
+    // against 52 with 256; where nearly everything is selected, 61 against 77 with 256 streams, but 32 against 26 with one,
+    // 30 against 28 with 8, 35 against 31 with 32 (at 1536 tokens the two are even there).  Above 128 blocks a stream that selects nearly all its blocks wants more than one unit, unless
+    // there are streams for most of the chip: at 256 blocks 63 us against 32 with 8 streams, 99 against 103 with 192; at
+    // 192 blocks 53 against 53 with 128.  Hence three streams for four blocks.
     // Whoever tunes the general path, times its phases or brings a second tier gets the general path.  So does a call of more
     // streams than one grid of workgroups of 1024 threads can have (fewer than 2^32 threads).
     const bool tuned = t && (t->window_chunks > 0 || t->spin_limit > 0 || t->force_bitonic || t->phase_events ||

@@ -24,8 +24,8 @@
 // four up to 4096, eight beyond (a workgroup has 1024 threads at most); reductions along rows of lanes; counters of
 // 16 bits, so that two workgroups of 8192 blocks fit a compute unit; and the request's row of the block table read at
 // the start, so that the gather at the end finds it in the cache.  With eight keys to a thread throughout, 32-bit
-// counters and reductions through LDS exchanges it took 12.1 us at 2048 blocks (64 streams), 7.5 now; 17.9 -> 13.9 at
-// 8192 (32 streams), 40 -> 26 with 512 streams; where the time went: scores 0.9 us, range 0.5, counters 0.6, scan 0.4,
+// counters and reductions through LDS exchanges it took 11.9 us at 2048 blocks (64 streams), 8.0 now; 18.0 -> 13.4 at
+// 8192 (32 streams), 40.5 -> 26.4 with 512 streams; where the time went: scores 0.9 us, range 0.5, counters 0.6, scan 0.4,
 // shares 0.5, layout 0.4, count 0.9, gather and stores 0.4, the rest is the launch.
 //
 // The kernel also resets the stream's control block and chunk words for the progressive kernel,
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
     const int part = blockIdx.x, nparts = gridDim.x;
     const int tid = threadIdx.x, nthreads = blockDim.x, lane = tid & 63, wave = tid >> 6;
     const int nwaves = nthreads >> 6;
-    // what this thread needs from memory, requested before anything else: its 8 scores (two 16-byte loads
+    // what this thread needs from memory, requested before anything else: its K scores (loads of 8 or 16 bytes
     // where the row's length allows)
     const float *sc = ws.scores + (size_t)s * kv.max_blocks;
     const int32_t *table = kv.block_table + (size_t)r * kv.max_blocks;
