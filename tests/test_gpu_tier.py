@@ -237,6 +237,27 @@ def test_fixed_budget_and_ragged_batch_with_a_tier(psa):
     _same(got, ref)
 
 
+@pytest.mark.parametrize("batch,H,G,ctx", [(130, 4, 2, 400), (520, 1, 8, 300), (3, 1, 8, 2000)])
+def test_short_contexts_with_a_tier(psa, batch, H, G, ctx):
+    """Without a tier these calls are one launch, with it the kernels of the general path (520 streams: more than are folded
+    at a time), one KV head with eight query heads scored on the matrix cores in both: the results are the same bits."""
+    cfg = get_config(4).scaled(batch=batch, ctx=ctx, ctx_min=20, num_q_heads=G * H, num_kv_heads=H)
+    li = generate_layer(cfg, device="cuda", poison_tail=True)
+    n_slices = li.k_pool.shape[0] * li.k_pool.shape[1]
+    tier = psa.Tier(n_slices, max(1, n_slices // 2))
+    model = TierModel(n_slices, max(1, n_slices // 2))
+    L = Layer(psa, li, tier, 0)
+    L.host.staging = psa.Tier.staging_buffer(1 << 12)
+    for eps in (0.95, 1.0):
+        ref = psa.decode_attention(L.dev, li.q, L.meta_dev, eps, 1, want_order=True)
+        got = psa.decode_attention(L.host, li.q, L.meta_host, eps, 1, want_order=True)
+        torch.cuda.synchronize()
+        assert psa.read_device_error(got._workspace) == 0
+        _same(got, ref)
+        _update(psa, L, got, tier, model)
+        _check_tables(tier, model, [L])
+
+
 def test_metadata_builds_read_a_tiered_cache_in_place(psa):
     """Both metadata builds over pools in pinned host memory give the bits they give over the same pools in device
     memory."""
