@@ -71,7 +71,7 @@ def load_read_probe():
     return lib.bench_stream_read_probe
 
 
-KERNEL_SOURCES = {"select_kernel": ["psa_select.hip", "psa_fold.h", "psa_device.h"], "attend_kernel": ["psa_values.hip", "psa_attend.h", "psa_device.h"],
+KERNEL_SOURCES = {"select_kernel": ["psa_select.hip", "psa_fold.h", "psa_attend.h", "psa_device.h"],
                   "score_kernel": ["psa_score.hip", "psa_device.h"]}
 
 
@@ -509,7 +509,7 @@ def main():
     for k in range(args.steps):
         step([psa.Tuning(phase_events=ev_sets[k][i], **tuning_kw) for i in range(L)])
     torch.cuda.synchronize()
-    names = ["score", "order", "select", "attend", "finalize"]
+    names = ["score", "order", "select", "attend", "finalize"]       # ("attend" is empty: the selection reads the values)
     phase_ms = {n: [] for n in names}
     for k in range(args.steps):
         for i in range(L):
@@ -518,15 +518,12 @@ def main():
                 phase_ms[n].append(hev.elapsed_ms(ev[j], ev[j + 1]))
     hev.destroy()
     phase_avg = {n: float(np.mean(v)) for n, v in phase_ms.items()}
-    # algorithmic bytes per launch: the selection kernel must move the key
-    # slices of the blocks read and their page ids, the attention kernel the value slices and page ids,
-    # the scoring kernel the metadata and the block table.  Scratch the implementation adds (stored
-    # logits, partials) is not counted.
-    kern_bytes = {"select_kernel": float(blocks_read.sum() * (4096 + 8) / L),
-                  "attend_kernel": float(blocks_read.sum() * (4096 + 8) / L),
+    # algorithmic bytes per launch: the selection kernel must move the key and the value
+    # slices of the blocks read and their page ids, the scoring kernel the metadata and the block table.
+    # Scratch the implementation adds (partials) is not counted.
+    kern_bytes = {"select_kernel": float(blocks_read.sum() * (8192 + 8) / L),
                   "score_kernel": float((meta_read.sum() + table_read.sum()) / L)}
-    kern_ms = {"select_kernel": phase_avg["select"], "attend_kernel": phase_avg["attend"],
-               "score_kernel": phase_avg["score"]}
+    kern_ms = {"select_kernel": phase_avg["select"], "score_kernel": phase_avg["score"]}
     dom = max(kern_ms, key=kern_ms.get)
     dom_gbs = kern_bytes[dom] / (kern_ms[dom] * 1e-3) / 1e9
     kern_gbs = {k: kern_bytes[k] / (kern_ms[k] * 1e-3) / 1e9 for k in kern_ms}
@@ -824,7 +821,7 @@ def main():
         "other_configs": others,
         "metadata_bulk_build": {"ms": meta_ms, "GBps": meta_bytes / (meta_ms * 1e-3) / 1e9},
     }
-    for n in ("select", "attend"):
+    for n in ("select",):
         log(f"[bench] per-layer {n} ms: " + " ".join(f"{x:.3f}" for x in per_layer[n]))
     log("[bench] per-layer blocks read, min/mean/max over the (request, KV head) pairs: " +
         " ".join(f"{int(x.min())}/{int(x.mean())}/{int(x.max())}" for x in blocks_read.reshape(L, -1)))

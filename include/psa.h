@@ -147,7 +147,7 @@ typedef struct {
                                correctness                                                            */
     void *phase_events;     /* host pointer: NULL, or hipEvent_t[6] the call records on `stream`
                                before scoring and after each of its kernels: scoring, ranking,
-                               selection (key pass), attention (value pass), final merge
+                               selection with the values it reads, nothing, final merge
                                (profiling aid)                                                        */
 } psa_tuning;
 

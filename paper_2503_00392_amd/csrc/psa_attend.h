@@ -1,4 +1,4 @@
-// Per-block building blocks shared by the dense control kernel, the value pass and the metadata kernel:
+// Per-block building blocks shared by the dense control kernel, the selection kernel and the metadata kernel:
 // how one wave reads a 4 KiB (page, KV head) slice and what each lane holds, and the 16x16x16 matrix
 // product with 16-bit operands that both attention kernels accumulate values with.
 //

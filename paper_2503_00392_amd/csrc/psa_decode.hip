@@ -1,6 +1,5 @@
 // Host side of psa_decode_attention: workspace layout, launch plan and the kernel sequence
-//   score (Algorithm 1 line 5) -> order (line 6) -> select (lines 7-18, key side and stop rule) ->
-//   attend (value side of lines 10-12) -> finalize (line 19),
+//   score (Algorithm 1 line 5) -> order (line 6) -> select (lines 7-18) -> finalize (line 19),
 // all enqueued on one stream with no host involvement in between -- or, for short contexts, one kernel that does it all.
 #include "psa_host.h"
 
@@ -57,7 +56,7 @@ DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t) {
 }
 
 struct WsLayout {
-    size_t header, ctl, scores, order, ranked_page, agg, block_lse, logits, partial, value_items, total;
+    size_t header, ctl, scores, order, ranked_page, agg, block_lse, logits, partial, total;
 };
 
 static WsLayout layout(const psa_kv_desc *d, const DecodePlan &p) {
@@ -75,8 +74,9 @@ static WsLayout layout(const psa_kv_desc *d, const DecodePlan &p) {
     L.block_lse = at;   at = align_up(at + S * MB * G * 4, 256);
     L.logits = at;      at = align_up(at + S * MB * kPage * G * 4, 256);
     L.partial = at;     at = align_up(at + S * p.max_chunks * G * kPartialStride * 4, 256);
-    L.value_items = at; at = align_up(at + S * p.max_chunks * 4, 256);
-    L.total = at;
+    // The size is part of the interface (callers keep buffers of it, and what fits the static array is drawn in it), so it
+    // stays what it was when every path kept its logits here and the value pass had a work list.
+    L.total = align_up(at + S * p.max_chunks * 4, 256);
     return L;
 }
 
@@ -139,7 +139,6 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     ws.block_lse = reinterpret_cast<float *>(base + L.block_lse);
     ws.logits = reinterpret_cast<float *>(base + L.logits);
     ws.partial = reinterpret_cast<float *>(base + L.partial);
-    ws.value_items = reinterpret_cast<int32_t *>(base + L.value_items);
     ws.max_chunks = plan.max_chunks;
     ws.max_units = plan.max_chunks;
     const int G = d->num_q_heads / d->num_kv_heads;
@@ -161,8 +160,7 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     if ((e = launch_select(kv, d->dtype, G, a.q, ws, a.threshold, a.check_granularity, a.budget_blocks, plan, st)) != hipSuccess)
         return e;
     if (ev) (void)hipEventRecord(ev[3], st);
-    if ((e = launch_attend(kv, d->dtype, G, ws, plan, st)) != hipSuccess) return e;
-    if (ev) (void)hipEventRecord(ev[4], st);
+    if (ev) (void)hipEventRecord(ev[4], st);      // (no kernel in between: the selection reads the values as well)
     e = launch_finalize(kv, ws, G, plan.chunk_blocks, a.out, a.n_selected, a.mass_est, a.blocks_read, a.lse_out,
                         a.traffic_out, st);
     if (ev) (void)hipEventRecord(ev[5], st);

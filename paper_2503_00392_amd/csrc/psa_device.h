@@ -116,23 +116,23 @@ struct alignas(128) StreamCtl {
     unsigned long long key_progress;    // bits 0-15: frontier = key chunks folded into the stop rule so far;
                                         // bits 16-31: the read-ahead window the fold grants beyond the frontier,
                                         // in chunks (0 = the launch's default);
-                                        // high word: k_limit = key chunks worth reading (all of them, or what a
+                                        // bits 32-47: k_limit = key chunks worth reading (all of them, or what a
                                         // block budget covers, or what the stop rule can still reach; once the
-                                        // fold has finished, what it used)
+                                        // fold has finished, what it used);
+                                        // bits 48-55: heads whose stop (line 2) is in memory
     int32_t pad0[30];
     // line 1: counters
     int32_t k_blocks;   // key slices loaded (traffic accounting)
     int32_t pad1[15];
     uint32_t lse_ready_hi[16];   // as lse_ready, chunks 512 and up (chunks of eight blocks make 1024 of them)
-    // line 2: the fold's result, written when it closes the stream
+    // line 2: the fold's result, each head's written before its bit in the progress word
     unsigned long long stop[8];  // per head: (n << 32) | float bits of P_acc at the stop; ~0 = not stopped
     uint32_t lse_ready[16];      // bit c: chunk c's block_lse values are in memory (set after its words in agg)
 };
 static_assert(sizeof(StreamCtl) == 384, "three cache lines");
 
 struct DecodeWs {
-    int32_t *header;        // [128]: word 1 = sticky error bits; word kValueCount (a cache line of its own) =
-                            // number of entries of value_items; word kClosedStreams (again its own line) =
+    int32_t *header;        // [128]: word 1 = sticky error bits; word kClosedStreams (a cache line of its own) =
                             // streams whose stop rule has finished
     StreamCtl *ctl;         // [S]
     float *scores;          // [S][max_blocks]
@@ -140,11 +140,9 @@ struct DecodeWs {
     int32_t *ranked_page;   // [S][max_blocks]  physical page of each ranked block
     unsigned long long *agg;  // [S][max_chunks][G]  (L_chunk, Lmin_chunk) as two floats, or kAggSentinel
     float *block_lse;       // [S][max_blocks][G]  log2 of each ranked block's AS (Algorithm 1 line 10)
-    float *logits;          // [S][max_blocks][G][16]  scaled logits (log2 units) by ranked block; position
-                            // 4*r + j of a (block, head) row holds token 4*j + r
+    float *logits;          // [S][max_blocks][G][16]  short contexts only: scaled logits (log2 units) by ranked block;
+                            // position 4*r + j of a (block, head) row holds token 4*j + r
     float *partial;         // [S][max_chunks][G][kPartialStride]
-    int32_t *value_items;   // [S * max_chunks] value units to attend: stream * max_chunks + chunk, appended by
-                            // each stream's fold when it closes the stream
     int32_t max_chunks;     // chunks per stream at most
     int32_t max_units;      // = max_chunks (stride of `partial`)
 };
@@ -154,7 +152,6 @@ __device__ __forceinline__ uint32_t *lse_ready_word(StreamCtl *ctl, int c) {
 }
 constexpr int kPartialStride = 132;  // M, l, pad, pad, acc[128]
 constexpr int kMaxWindowChunks = 256; // chunks read beyond the fold's frontier, at most
-constexpr int kValueCount = 32;      // index of the value-item counter in the workspace header
 constexpr int kClosedStreams = 64;   // index of the closed-stream counter in the workspace header
 // A chunk word holds (L_chunk, Lmin_chunk) as two floats once the chunk is published.  Before that
 // it holds a NaN pattern no publisher writes: "not published".

@@ -121,8 +121,6 @@ hipError_t launch_order(const KvView &kv, const DecodeWs &ws, int G, const Decod
                         const int32_t *slot_of, int32_t *order_out, hipStream_t st);
 hipError_t launch_select(const KvView &kv, int dtype, int G, const void *q, const DecodeWs &ws, float eps,
                          int m, int budget_blocks, const DecodePlan &plan, hipStream_t st);
-hipError_t launch_attend(const KvView &kv, int dtype, int G, const DecodeWs &ws, const DecodePlan &plan,
-                         hipStream_t st);
 // psa_solo.hip: all of the above in one kernel, 1 + (streams) workgroups of kSoloThreads
 constexpr int kSoloThreads = 1024;
 hipError_t launch_solo(const KvView &kv, int dtype, int G, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st);

@@ -1,6 +1,6 @@
-// Progressive selection (Algorithm 1, lines 7-18 without the value side): walks every stream's ranked
-// blocks, computes the exact scaled logits q.k/sqrt(d) of each block from its key slice, keeps them
-// for the value pass, and decides on the GPU where every query head stops.
+// Progressive selection and attention (Algorithm 1, lines 7-18): walks every stream's ranked blocks, computes the
+// exact scaled logits q.k/sqrt(d) of each block from its key slice, decides on the GPU where every query head stops, and
+// multiplies the selected blocks' weights with their value slices.
 //
 // Terms.  "Stream": one (request, KV head) pair -- one ranking, G query heads.  "Chunk": CB
 // consecutive ranked blocks, the unit of work of a workgroup.
@@ -23,32 +23,45 @@
 //      cores (heads beyond G are zero columns), keeps them in LDS until the chunk is done, and then reduces
 //      every block's log-sum-exp L_b (= log AS of line 10) at once;
 //   4. publishes the chunk's (log-sum-exp, minimum) of L_b per head as one 64-bit word per head, then the L_b
-//      themselves, then a bit that says they are there; the logits leave for the workspace meanwhile.
+//      themselves, then a bit that says they are there;
+//   5. waits until the fold has passed the chunk and knows how many of its blocks every head uses, reads those value
+//      slices, and leaves the chunk's part of the output (reference, sum of weights, numerator) for the final merge.
+// Keys and values in one kernel: the logits stay in LDS.  In a kernel of its own the value pass had them written to memory
+// and read back (6 % of the keys' bytes at G = 4, 12 % at G = 8, and writes cost this kernel several times their bytes), and
+// it could not begin before the last stream's fold had ended, nor the launch gap be hidden; here the values of the streams
+// that stop early are read while the deep ones are still folding.  Two kernels -> one: 32K tokens, batch 8 102.5 -> 89.2 us a
+// call, four layers at 128K 767 -> 679, 64 ragged requests at G = 8 1610 -> 1399, everything selected (64K, batch 16)
+// 862 -> 773, one request of 4K tokens 32.6 -> 29.0.  A slot is held while a workgroup waits for the fold, which is why this
+// lost in an earlier form with fewer resident workgroups: four fit a compute unit with two value slices in flight per wave
+// (128 registers); three with four slices were 4 % slower at G = 8, and no faster elsewhere.  Value slices asked for before the
+// fold's answer, where the stream was likely to need them, made no difference.
 // From the last key to the published word a chunk takes 0.9 us, and 3.2 us from its first load on an idle chip; with
 // the reduction inside the loop over the slices, and the words after all stores, these were 1.0 us (3 us under load)
 // and 4.6 us.  A call at 32K tokens, batch 8, went from 112.5 to 109.7 us, at 4K, batch 31, from 58.1 to 54.1.
-// The wait of step 2 is a courtesy, not a dependency: no chunk workgroup needs anything to proceed
-// (when the looks run out it simply reads its chunk), so the grid drains whatever order it runs in.
+// The wait of step 2 is a courtesy: when the looks run out the workgroup simply reads its chunk.  The wait of step 5 is for
+// chunks of the same stream that come before, whose workgroups have smaller indexes and publish before they wait for anything
+// themselves: the hardware starts workgroups in the order of their indexes (within each of the chip's partitions), so the
+// one with the smallest index that is not done never waits for one that has not started.  It is bounded all the same.
 // THE FOLD applies lines 12-17 strictly in rank order: AS_acc, AS_min, N_left and P_acc at the end
 // of each published chunk after the frontier and, in the first chunk where P_acc exceeds the
 // threshold, with a prefix scan over the chunk's blocks to find the head's exact stop.  One wave per
 // stream does it, in workgroups of its own at the head of the grid (so they start first): it looks at the
 // words of the next chunks, folds what is published, moves the frontier, tells the readers how far the
 // stream can still go (stop_bound), and looks again.  Once every head has stopped (or the blocks ran
-// out) it closes the stream -- the chunks beyond what it used are never read -- and puts the stream's
-// value units on the work list of the value pass.
+// out) it closes the stream: the chunks beyond what it used are never read.
 //
 // Communication between workgroups: every shared word is read and written with relaxed agent-scope
 // atomics (coherent accesses); a writer waits for its data stores to complete before it stores the
 // word that announces them (the chunk words, the progress word), and a reader looks at the announcing
 // word before it issues the loads that depend on it.  Accesses to one cache line are served one at a
 // time (tens of nanoseconds each), which is why one thread per workgroup touches the stream's control
-// block.  The logits are plain stores: their reader is the next kernel.
+// block.  The chunks' partial outputs are plain stores: their reader is the next kernel.
 //
 // The fold is one scan in rank order and every reduction has a fixed shape, so results are bitwise
 // reproducible although the scheduling is dynamic.
 #include <limits.h>
 
+#include "psa_attend.h"
 #include "psa_fold.h"
 #include "psa_host.h"
 
@@ -94,7 +107,8 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 
 
 constexpr int kBatch = 4;            // key slices a wave keeps in flight
-constexpr int kSelectThreads = 256;  // 4 waves; four such workgroups fit a CU (register budget)
+constexpr int kValueDepth = 2;       // value slices a wave keeps in flight
+constexpr int kSelectThreads = 256;  // 4 waves; four such workgroups fit a CU (registers, LDS at G = 8)
 
 // Tokens of stream s's request, clamped like everywhere else.
 __device__ __forceinline__ int stream_ctx(const KvView &kv, int s) {
@@ -122,10 +136,11 @@ struct SelectShared {
     int page[MAXB];
     int valid[MAXB];
     int go;                                // after the wait for the window: 1 = read the chunk, 0 = the stream closed
-    unsigned long long kp0;                // the stream's progress word as the workgroup first saw it
-    uint4 stage[kSelectThreads / 64][16 * 17];   // per wave: one key slice, rows padded to 272 bytes
-    // the chunk's logits in the layout of the workspace, written out as one piece
+    unsigned long long kp0;                // the stream's progress word as the workgroup first saw it, later as it saw it last
+    uint4 stage[kSelectThreads / 64][16 * 17];   // per wave: one key slice, rows padded to 272 bytes; later its numerators
+    // the chunk's logits: position 4 r + j of a (block, head) row holds token 4 j + r
     __attribute__((aligned(16))) float lg[MAXB][G][kPage];
+    float st_l[kSelectThreads / 64][G], st_ref[G];   // value phase: per wave the sum of its weights, the reference
 };
 
 // How far a stream can still go, in chunks, given what the fold knows after n blocks.  AS_acc only grows and
@@ -159,10 +174,14 @@ __device__ __forceinline__ int stop_bound(float Lacc, float Lmin, unsigned long 
     return (need + KU - 1) / KU + 1;
 }
 
-// The progress word of a stream that is still open (see StreamCtl).
-__device__ __forceinline__ unsigned long long progress_word(int lim, int grant, int walked) {
-    return ((unsigned long long)(unsigned)lim << 32) | ((unsigned)grant << 16) | (unsigned)walked;
+// The progress word of a stream (see StreamCtl).
+__device__ __forceinline__ unsigned long long progress_word(int stopped, int lim, int grant, int walked) {
+    return ((unsigned long long)(unsigned)stopped << 48) | ((unsigned long long)(unsigned)lim << 32) | ((unsigned)grant << 16) | (unsigned)walked;
 }
+__device__ __forceinline__ int progress_frontier(unsigned long long kp) { return (int)(kp & 0xffffull); }
+__device__ __forceinline__ int progress_grant(unsigned long long kp) { return (int)((kp >> 16) & 0xffffull); }
+__device__ __forceinline__ int progress_limit(unsigned long long kp) { return (int)((kp >> 32) & 0xffffull); }
+__device__ __forceinline__ int progress_stopped(unsigned long long kp) { return (int)(kp >> 48); }
 // The read-ahead window of a stream when `closed` of the S streams have finished: the launch's total of chunks in
 // flight (window per stream x S) shared by the streams still open.
 __device__ __forceinline__ int granted(int window, int S, int closed) {
@@ -220,6 +239,14 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
     int closed = 0, lim_now = nch;             // streams seen closed at the last look; the limit last published
     int looks = 0, seen = 0;                   // looks in vain since the stream moved or another one closed
     bool finished = false;
+    int stopped = 0;                           // bit g: head g's stop is in memory
+    auto publish_stops = [&]() __attribute__((always_inline)) {
+        const int now = (int)(__ballot(lane < G && stop != ~0ull) & 0xffull);
+        if (now == stopped) return;
+        stopped = now;
+        if (lane < G) st_relaxed(&ctl->stop[lane], stop);
+        stores_done();                         // (whoever sees the bit in the progress word reads the stop)
+    };
     while (!finished) {
         // the group's words, and (in flight at the same time) how many streams have closed
         const int ci = base + jl;
@@ -239,7 +266,7 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
             if (closed_now != seen) { seen = closed_now; looks = 0; }
             if (closed_now != closed && walked > 0) {
                 closed = closed_now;
-                if (lane == 0) st_relaxed(&ctl->key_progress, progress_word(lim_now, granted(window, S, closed), walked));
+                if (lane == 0) st_relaxed(&ctl->key_progress, progress_word(stopped, lim_now, granted(window, S, closed), walked));
             }
             __builtin_amdgcn_s_sleep(8);
             continue;
@@ -269,24 +296,15 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
         // machine idle once most of them have closed).
         const int lim = min(nch, stop_bound<G>(Lw, Mw, stop, walked * KU, N, m, KU, odds));
         lim_now = lim;
-        if (lane == 0) st_relaxed(&ctl->key_progress, progress_word(lim, granted(window, S, closed), walked));
+        publish_stops();
+        if (lane == 0) st_relaxed(&ctl->key_progress, progress_word(stopped, lim, granted(window, S, closed), walked));
     }
-    // every head has stopped, or the blocks ran out: close the key side (limit = frontier)
-    if (lane < G) st_relaxed(&ctl->stop[lane], stop);
+    // every head has stopped, or the blocks ran out: close the stream (limit = frontier)
+    publish_stops();
     if (lane == 0) {
-        st_relaxed(&ctl->key_progress, ((unsigned long long)(unsigned)walked << 32) | (unsigned)walked);
+        st_relaxed(&ctl->key_progress, progress_word(stopped, walked, 0, walked));
         atomicAdd(&ws.header[kClosedStreams], 1);
     }
-    // the stream's value units (the chunks up to its slowest head's stop) go onto the work list of the
-    // value pass, which therefore starts no workgroup for a chunk nobody selected
-    int nmax = (lane < G) ? ((stop == ~0ull) ? N : (int)(stop >> 32)) : 0;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) nmax = max(nmax, __shfl_xor(nmax, d));
-    const int units = (nmax + KU - 1) / KU;
-    int base_item = 0;
-    if (lane == 0) base_item = atomicAdd(&ws.header[kValueCount], units);
-    base_item = uniform(base_item);
-    for (int i = lane; i < units; i += 64) ws.value_items[base_item + i] = s * ws.max_chunks + i;
 }
 
 // Physical page and valid-token count of each ranked block of chunk c of stream s -> LDS.  Issued before
@@ -344,7 +362,6 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
     uint4 qb[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) qb[kk] = sh.qb[kk][lane];
-    float *lg_out = ws.logits + row0 * (kPage * G);
     // ---- keys: wave w takes blocks w, w + 4, ..., each a 4 KiB slice read as four coalesced 1 KiB loads.  A operand
     //      of the product: row n = token n of the block, same channel assignment as the queries. ------------------
     auto issue = [&](int i, uint4 (&dst)[4]) {
@@ -386,15 +403,7 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
     // ---- the blocks' log-sum-exp L_b per head, from the logits in LDS, all threads of the workgroup at once ----------
     rows_lse<G, kSelectThreads>(&sh.lg[0][0][0], &sh.Lb[0][0], nblk * G, tid);
     lds_barrier();
-    // The chunk's logits leave as one contiguous piece (8 KiB at G = 4), every thread of waves 1-3 16 bytes at a time,
-    // while wave 0 publishes.  Writes are what this kernel pays most for per byte; in whole, neighbouring cache lines
-    // they cost a third less than as 256 bytes per block in between the loads.
-    if (wave != 0) {
-        const float *staged = &sh.lg[0][0][0];
-        for (int idx = (tid - 64) * 4; idx < nblk * G * kPage; idx += (kSelectThreads - 64) * 4)
-            store_stream(lg_out + idx, *reinterpret_cast<const f32x4_t *>(staged + idx));
-        return;
-    }
+    if (wave != 0) return;
 
     // ---- publish: the chunk's (log-sum-exp, minimum) of its blocks' L_b per head ------------------------------------
     float aggL, aggMin;
@@ -409,6 +418,134 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
     stores_done();
     if (lane == 0)
         __hip_atomic_fetch_or(lse_ready_word(&ws.ctl[s], c), 1u << (c & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// =================================================================================================
+// The chunk's values (lines 10-12), by the workgroup that holds its logits, once the fold has passed the chunk: the heads
+// that are still open use all of it, and those that stop in it their stop's share.  (A fixed budget says how much beforehand,
+// so nothing is waited for.)  The four waves stream independently: wave w takes blocks w, w+4, ... of the chunk, and
+// nothing is shared until the sums at the end.
+//   weights   p = exp(logit - L), L = per head the largest log-sum-exp of a block the head uses: a reference every wave
+//             knows beforehand, so nothing is rescaled on the way and the four waves' sums simply add up.  (p <= 1, and
+//             the largest weight is at least 1/16: the weights keep their precision as 16-bit halves.)
+//   numerator D[head][channel] += P[head][token] V[token][channel]: eight 16x16x16 products per block, the weights
+//             split into hi + lo 16-bit halves that sit in neighbouring rows (see add_weighted).  The k index of both
+//             operands is the token: lane (rg, *) holds the value rows rg, 4+rg, 8+rg, 12+rg -- the rows its four loads
+//             fetched -- and the key product left the logits so that the 16 bytes at [block][head][4 rg] are those
+//             same four tokens: one read of LDS, no transposition.
+// Output per chunk and head: (L, sum of p, numerator[128]) for the final merge.
+// =================================================================================================
+constexpr int kWholeChunk = 32;      // blocks of a chunk in the default plan: the size with a fixed schedule
+template <int DT, int G, int MAXB>
+__device__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int CB, int budget, int s, int c) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), rg = lane >> 4, cl = lane & 15;
+    const int ctx = stream_ctx(kv, s), N = (ctx + kPage - 1) / kPage;
+    const int h = s % kv.num_kv_heads, start = c * CB, nblk = min(CB, N - start);
+    int mycnt = nblk;                                          // blocks of the chunk that head lane % G uses
+    if (budget > 0) {
+        mycnt = min(nblk, budget - start);
+    } else {
+        if (tid == 0) {
+            unsigned long long kp;
+            for (int looks = 0, seen = -1;; ++looks) {
+                kp = ld_relaxed(&ws.ctl[s].key_progress);
+                const int fr = progress_frontier(kp);
+                if (c < fr || c >= progress_limit(kp)) break;
+                if (fr != seen) { seen = fr; looks = 0; }
+                if (looks > kFoldPatience) { set_error(ws.header, PSA_DEVERR_STALLED); kp = 0; break; }   // (as good as closed)
+                // a fifth of a microsecond, and the same again for every four chunks the fold has to go: the pollers of
+                // one stream share a cache line
+                for (int i = c - fr; i >= 0; i -= 4) __builtin_amdgcn_s_sleep(8);
+            }
+            sh.kp0 = kp;
+        }
+        lds_barrier();
+        const unsigned long long kp = sh.kp0;
+        if (c >= progress_frontier(kp)) return;                // closed before this chunk
+        if (progress_stopped(kp) != 0) {                       // (the stops of the bits that are set are in memory)
+            const unsigned long long stop = ld_relaxed(&ws.ctl[s].stop[lane % G]);
+            if (stop != ~0ull) mycnt = min(nblk, max(0, (int)(stop >> 32) - start));
+        }
+    }
+    int maxcnt = mycnt;
+#pragma unroll
+    for (int d = 1; d < G; d <<= 1) maxcnt = max(maxcnt, __shfl_xor(maxcnt, d));
+    maxcnt = uniform(maxcnt);
+    if (maxcnt <= 0) return;
+    const int jmax = (maxcnt - wave + 3) / 4;                  // blocks of this wave (may be <= 0)
+    const int hd = cl >> 1;                                    // the head whose weights the lane supplies (see add_weighted)
+    const int lg_lane = (hd < G ? hd : 0) * kPage + 4 * rg;
+    const int hdcnt = __shfl(mycnt, hd);
+    Slice v[kValueDepth];
+    auto issue = [&](int j, auto slot) __attribute__((always_inline)) {
+        constexpr int u = decltype(slot)::value;
+        v[u] = load_slice(value_slice(kv, uniform(sh.page[wave + 4 * j]), h), lane);
+    };
+    f32x4_t acc[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    float l = 0.0f, Lc = -INFINITY;
+    auto reference = [&]() __attribute__((always_inline)) {    // of head lane % G first: every wave computes the same bits
+        for (int i = lane / G; i < mycnt; i += 64 / G) Lc = fmaxf(Lc, sh.Lb[i][lane % G]);
+#pragma unroll
+        for (int d = G; d < 64; d <<= 1) Lc = fmaxf(Lc, __shfl_xor(Lc, d));
+        Lc = __shfl(Lc, hd);
+    };
+    auto consume = [&](int j, auto slot) __attribute__((always_inline)) {
+        constexpr int u = decltype(slot)::value;
+        const int blk = wave + 4 * j;
+        if (kv.staging != nullptr) {                           // (second tier: see stage_key_slice; the entry is this wave's own)
+            const int loc = uniform(sh.page[blk]);
+            if (loc >= 0) stage_value_slice(kv, loc, h, v[u].r, lane);
+        }
+        const int valid = uniform(sh.valid[blk]);
+        if (valid < kPage) zero_invalid_rows(v[u], rg, valid);
+        // tokens beyond `valid` hold -inf logits; blocks beyond the head's stop, and heads beyond the group, weigh nothing
+        const bool on = hd < G && blk < hdcnt;
+        const f32x4_t x = *reinterpret_cast<const f32x4_t *>(&sh.lg[blk][0][0] + lg_lane);
+        add_values<DT>(acc, l, v[u], x, on, Lc, cl & 1);
+    };
+    if (maxcnt == kWholeChunk) {                               // eight blocks for every wave: a rolling window, as for the keys
+        static_for<kValueDepth>([&](auto u) { issue(u, u); });
+        reference();
+        static_for<kWholeChunk / 4>([&](auto j) {
+            const std::integral_constant<int, j % kValueDepth> slot;
+            consume(j, slot);
+            if (j + kValueDepth < kWholeChunk / 4) issue(j + kValueDepth, slot);
+            __builtin_amdgcn_sched_barrier(0);                 // (steps that are interleaved run out of registers)
+        });
+    } else {
+        static_for<kValueDepth>([&](auto u) { if (u < jmax) issue(u, u); });
+        reference();
+        for (int j0 = 0; j0 < jmax; j0 += kValueDepth) {
+            static_for<kValueDepth>([&](auto u) {
+                if (j0 + u < jmax) {
+                    consume(j0 + u, u);
+                    if (j0 + kValueDepth + u < jmax) issue(j0 + kValueDepth + u, u);
+                }
+            });
+        }
+    }
+    // the exp-sum over the four row groups, then the four waves through LDS (one reference: plain sums)
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    float (*st_acc)[G][kHeadDim] = reinterpret_cast<float (*)[G][kHeadDim]>(&sh.stage[0][0]);
+    store_heads<G>(acc, st_acc[wave], rg, cl);
+    if (rg == 0 && hd < G && !(cl & 1)) {
+        sh.st_l[wave][hd] = l;
+        if (wave == 0) sh.st_ref[hd] = Lc;
+    }
+    lds_barrier();
+    float *dst = ws.partial + ((size_t)s * ws.max_units + c) * G * kPartialStride;
+    for (int idx = tid; idx < G * kHeadDim; idx += 256) {
+        const int g = idx / kHeadDim, ch = idx % kHeadDim;
+        dst[g * kPartialStride + 4 + ch] =
+            (st_acc[0][g][ch] + st_acc[1][g][ch]) + (st_acc[2][g][ch] + st_acc[3][g][ch]);
+        if (ch == 0) {
+            dst[g * kPartialStride] = sh.st_ref[g];
+            dst[g * kPartialStride + 1] = (sh.st_l[0][g] + sh.st_l[1][g]) + (sh.st_l[2][g] + sh.st_l[3][g]);
+        }
+    }
 }
 
 // =================================================================================================
@@ -455,7 +592,7 @@ __global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select
     stage_pages<G, MAXB>(sh, kv, ws, CB, s, c);
     if (threadIdx.x == 0) sh.kp0 = kp_first;
     lds_barrier();
-    if (c >= (int)(sh.kp0 >> 32)) return;          // closed, out of reach, or beyond a block budget
+    if (c >= progress_limit(sh.kp0)) return;          // closed, out of reach, or beyond a block budget
     // Second tier: a chunk with slices that are not cached is read over the host link, where reading ahead
     // of the stop costs far more than waiting does: such a chunk is read when it is expected to be needed
     // (inside the hint) or when the fold is about to reach it.
@@ -470,7 +607,7 @@ __global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select
         int go = 1;
         for (int tries = 0;; ++tries) {
             const unsigned long long kp = tries == 0 ? sh.kp0 : ld_relaxed(&ws.ctl[s].key_progress);
-            const int fr = (int)(kp & 0xffffull), grant = (int)((kp >> 16) & 0xffffull), lim = (int)(kp >> 32);
+            const int fr = progress_frontier(kp), grant = progress_grant(kp), lim = progress_limit(kp);
             const int win = max(window_of(window, fr), grant);      // (the fold grants more once streams have closed)
             if (c >= lim) { go = 0; break; }       // closed, or a block budget ends before this chunk
             // with a hint: everything up to it plus a margin (a sixteenth and two chunks: the depth of a
@@ -488,6 +625,7 @@ __global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select
     if (!sh.go) return;
     if (threadIdx.x == 0) atomicAdd(&ws.ctl[s].k_blocks, min(CB, N - c * CB));     // traffic accounting
     process_chunk<DT, G, MAXB>(sh, kv, q, ws, eps, m, CB, budget, s, c);
+    attend_chunk<DT, G, MAXB>(sh, kv, ws, CB, budget, s, c);
 }
 
 template <int DT, int G>

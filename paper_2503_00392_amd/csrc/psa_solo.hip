@@ -1,9 +1,9 @@
 // A whole decode step in one launch for short contexts: one workgroup per (request, KV head) scores, ranks, reads keys,
 // applies the stop rule, reads values and merges, with everything it hands from step to step in LDS.
 //
-// What bounds a short request is not memory but the chain of dependent launches: the five kernels of the general path
-// take 28 us one after the other at 1024 tokens (8 streams), 35 at 4096, of which each spends 4 to 9 us on being
-// started, on its first loads and on draining, and the selection kernel another 4 on passing words between workgroups.
+// What bounds a short request is not memory but the chain of dependent launches: the general path's kernels (five, when
+// this was measured) take 28 us one after the other at 1024 tokens (8 streams), 35 at 4096, of which each spends 4 to 9 us on
+// being started, on its first loads and on draining, and the selection kernel another 4 on passing words between workgroups.
 // One workgroup of sixteen waves has no one to wait for: a barrier replaces a launch, LDS replaces the workspace.
 // 1024 tokens, 8 streams, G = 4: 28.0 -> 14.4 us; 256 streams: 38.2 -> 19.7; 2048 tokens: 30.8 -> 18.4 and 47.9 -> 28.1;
 // 4096 tokens, 256 streams: 60.4 -> 44.0.  What bounds it then is what one compute unit can have in flight between the
