@@ -56,7 +56,7 @@ DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t) {
 }
 
 struct WsLayout {
-    size_t header, ctl, scores, order, ranked_page, agg, block_lse, logits, partial, total;
+    size_t header, ctl, scores, order, ranked_page, agg, logits, agg_tested, carry, partial, total;
 };
 
 static WsLayout layout(const psa_kv_desc *d, const DecodePlan &p) {
@@ -71,11 +71,15 @@ static WsLayout layout(const psa_kv_desc *d, const DecodePlan &p) {
     L.order = at;       at = align_up(at + S * MB * 4, 256);
     L.ranked_page = at; at = align_up(at + S * MB * 4, 256);
     L.agg = at;         at = align_up(at + S * p.max_chunks * G * 8, 256);
-    L.block_lse = at;   at = align_up(at + S * MB * G * 4, 256);
-    L.logits = at;      at = align_up(at + S * MB * kPage * G * 4, 256);
     L.partial = at;     at = align_up(at + S * p.max_chunks * G * kPartialStride * 4, 256);
+    // one launch: the logits; the general path: two small tables
+    L.logits = at;
+    L.agg_tested = at;
+    L.carry = align_up(at + S * p.max_chunks * G * 8, 256);
     // The size is part of the interface (callers keep buffers of it, and what fits the static array is drawn in it), so it
-    // stays what it was when every path kept its logits here and the value pass had a work list.
+    // stays what it was when every path kept its logits here, block by block sums beside them, and had a work list.
+    at = align_up(at + S * MB * kPage * G * 4, 256);
+    at = align_up(at + S * MB * G * 4, 256);
     L.total = align_up(at + S * p.max_chunks * 4, 256);
     return L;
 }
@@ -136,12 +140,14 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     ws.order = reinterpret_cast<int32_t *>(base + L.order);
     ws.ranked_page = reinterpret_cast<int32_t *>(base + L.ranked_page);
     ws.agg = reinterpret_cast<unsigned long long *>(base + L.agg);
-    ws.block_lse = reinterpret_cast<float *>(base + L.block_lse);
     ws.logits = reinterpret_cast<float *>(base + L.logits);
+    ws.agg_tested = reinterpret_cast<float2 *>(base + L.agg_tested);
+    ws.carry = reinterpret_cast<unsigned long long *>(base + L.carry);
     ws.partial = reinterpret_cast<float *>(base + L.partial);
     ws.max_chunks = plan.max_chunks;
     ws.max_units = plan.max_chunks;
     const int G = d->num_q_heads / d->num_kv_heads;
+    ws.max_groups = (plan.max_chunks * G + 63) / 64;
     if (kv.batch == 0) return hipSuccess;
     hipEvent_t *ev = plan.events;
     hipError_t e;

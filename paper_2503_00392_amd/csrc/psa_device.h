@@ -116,18 +116,16 @@ struct alignas(128) StreamCtl {
     unsigned long long key_progress;    // bits 0-15: frontier = key chunks folded into the stop rule so far;
                                         // bits 16-31: the read-ahead window the fold grants beyond the frontier,
                                         // in chunks (0 = the launch's default);
-                                        // bits 32-47: k_limit = key chunks worth reading (all of them, or what a
+                                        // high word: k_limit = key chunks worth reading (all of them, or what a
                                         // block budget covers, or what the stop rule can still reach; once the
-                                        // fold has finished, what it used);
-                                        // bits 48-55: heads whose stop (line 2) is in memory
+                                        // fold has finished, what it used)
     int32_t pad0[30];
     // line 1: counters
     int32_t k_blocks;   // key slices loaded (traffic accounting)
-    int32_t pad1[15];
-    uint32_t lse_ready_hi[16];   // as lse_ready, chunks 512 and up (chunks of eight blocks make 1024 of them)
-    // line 2: the fold's result, each head's written before its bit in the progress word
+    int32_t pad1[31];
+    // line 2: the heads' stops, each written by the workgroup of the chunk it lies in
     unsigned long long stop[8];  // per head: (n << 32) | float bits of P_acc at the stop; ~0 = not stopped
-    uint32_t lse_ready[16];      // bit c: chunk c's block_lse values are in memory (set after its words in agg)
+    int32_t pad2[16];
 };
 static_assert(sizeof(StreamCtl) == 384, "three cache lines");
 
@@ -139,23 +137,25 @@ struct DecodeWs {
     int32_t *order;         // [S][max_blocks]  ranked logical blocks
     int32_t *ranked_page;   // [S][max_blocks]  physical page of each ranked block
     unsigned long long *agg;  // [S][max_chunks][G]  (L_chunk, Lmin_chunk) as two floats, or kAggSentinel
-    float *block_lse;       // [S][max_blocks][G]  log2 of each ranked block's AS (Algorithm 1 line 10)
+    float2 *agg_tested;     // [S][max_chunks][G]  the same up to the chunk's last tested position, where that can be another
+                            // than its end; written before the chunk's words in agg
+    unsigned long long *carry;  // [S][max_groups][G]  (L_acc, L_min) of the head before the group of chunks, kCarryStopped, or
+                            // kAggSentinel (the fold has not come there)
     float *logits;          // [S][max_blocks][G][16]  short contexts only: scaled logits (log2 units) by ranked block;
                             // position 4*r + j of a (block, head) row holds token 4*j + r
     float *partial;         // [S][max_chunks][G][kPartialStride]
     int32_t max_chunks;     // chunks per stream at most
     int32_t max_units;      // = max_chunks (stride of `partial`)
+    int32_t max_groups;     // groups of 64 / G chunks per stream at most
 };
-// The word of a stream's control block that holds the lse_ready bit of chunk c (bit c % 32), c < 1024.
-__device__ __forceinline__ uint32_t *lse_ready_word(StreamCtl *ctl, int c) {
-    return c < 512 ? &ctl->lse_ready[c >> 5] : &ctl->lse_ready_hi[(c >> 5) & 15];
-}
 constexpr int kPartialStride = 132;  // M, l, pad, pad, acc[128]
 constexpr int kMaxWindowChunks = 256; // chunks read beyond the fold's frontier, at most
 constexpr int kClosedStreams = 64;   // index of the closed-stream counter in the workspace header
 // A chunk word holds (L_chunk, Lmin_chunk) as two floats once the chunk is published.  Before that
 // it holds a NaN pattern no publisher writes: "not published".
 constexpr unsigned long long kAggSentinel = 0xFFFFFFFFFFFFFFFFull;
+// The carry word of a head that has stopped before the group (another NaN pattern that is not written otherwise).
+constexpr unsigned long long kCarryStopped = 0xFFFFFFFFFFFFFFFEull;
 
 __device__ __forceinline__ void set_error(int32_t *header, int bit) { atomicOr(&header[1], bit); }
 

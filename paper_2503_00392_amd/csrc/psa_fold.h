@@ -100,23 +100,25 @@ __device__ __forceinline__ void chunk_aggregate(const float *Lb, int nblk, int l
     }
 }
 
-// Folds chunks j .. k-1 of a group of 64 / G consecutive chunks (the first is chunk `base` of the stream), one wave,
-// lane = (chunk of the group, head).  In: L, M = the lane's chunk's words; (Cacc, Cmin) = the lane's head's state at
-// the start of the group; stop = its stop so far; ready = whether the lane's chunk's block values can be had.
-// A prefix scan over the chunks (steps of G lanes) gives every head's AS_acc and AS_min after every chunk of the group
-// at once, hence P_acc at every chunk's end.  The chunks in which an open head passes the threshold are then visited in
-// order (there are at most G stops per stream) for the head's exact stop, with a second prefix scan over that chunk's
-// blocks; block_value(b, i) is value i = (block, head) of the chunk that starts at block b.
-// Out: L, M = the state after the lane's chunk; returns the chunks of the group folded now: k, or less when every head
-// has stopped (then all_stopped), or when it came to a chunk that is not `ready`.
-// kScan: registers that hold one value per (block, head) of a chunk.
-template <int G, int kScan, class BlockValue>
-__device__ __forceinline__ int fold_group(float &L, float &M, float Cacc, float Cmin, unsigned long long &stop, int ready,
-                                          int base, int j, int k, int N, int m, int KU, float eps, bool &all_stopped,
-                                          BlockValue block_value) {
-    const int lane = threadIdx.x & 63, g = lane % G, jl = lane / G;
-    const unsigned long long head_lanes = (~0ull / ((1ull << G) - 1ull)) << g;   // the lanes of my head
-    all_stopped = false;
+// The rule is tested after every m-th block and after the last one (line 17); a fixed budget ends the blocks that count.
+// In the chunk of blocks b0 .. b1 - 1 (b1: not beyond a budget) the last such position, b0 if there is none, and the first.
+// Where m divides the chunk size and there is no budget, the last one is the chunk's end, whose state the chunk's word gives;
+// else a second word per chunk and head covers the blocks up to that position ("split").
+__device__ __forceinline__ int last_test(int b0, int b1, int m, int N) {
+    const int t = b1 == N ? N : b1 / m * m;
+    return t > b0 ? t : b0;
+}
+__device__ __forceinline__ int first_test(int b0, int m, int N) { return min(N, (b0 / m + 1) * m); }
+__device__ __forceinline__ bool split_words(int KU, int m, int budget) { return budget > 0 || KU % m != 0; }
+__device__ __forceinline__ int blocks_that_count(int N, int budget) { return budget > 0 ? min(N, budget) : N; }
+
+// A group is 64 / G consecutive chunks, aligned, lane = (chunk of the group, head).  In: L, M = the lane's chunk's words;
+// (Cacc, Cmin) = the lane's head's state at the start of the group.  Out: (L, M) = its AS_acc (log domain) and AS_min after
+// the lane's chunk, by a prefix scan over the chunks (steps of G lanes); (E, F) = before it.  What stands in the lanes of later
+// chunks does not matter, so the state after a chunk is a fixed expression of the chunk's place in its group, whichever chunks
+// were published when a wave looked, and whichever wave looks.
+template <int G>
+__device__ __forceinline__ void group_states(float &L, float &M, float Cacc, float Cmin, float &E, float &F, int lane) {
 #pragma unroll
     for (int d = G; d < 64; d <<= 1) {
         const float ol = __shfl_up(L, d), om = __shfl_up(M, d);
@@ -124,51 +126,89 @@ __device__ __forceinline__ int fold_group(float &L, float &M, float Cacc, float 
     }
     L = lse2(Cacc, L);
     M = fminf(Cmin, M);
-    const int b0 = (base + jl) * KU, n_end = min(b0 + KU, N);
-    // a stop inside a chunk needs a position where the rule is tested (line 17 is reached every m blocks and
-    // at the last block) and, P_acc being non-decreasing, a pass at the chunk's end
-    const bool passes = ((n_end / m) * m > b0 || n_end == N) && passes_test(p_acc(L, M, N - n_end), eps);
+    E = __shfl_up(L, G);
+    F = __shfl_up(M, G);
+    if (lane < G) { E = Cacc; F = Cmin; }
+}
+
+// Whether the lane's head passes the threshold in the lane's chunk, blocks b0 .. b1 - 1, if it is open before it: P_acc is
+// non-decreasing, so it does if it passes at the last position tested there; P is P_acc at that position.  (LT, MT): the
+// chunk's second word, if there are any.
+__device__ __forceinline__ bool chunk_passes(float L, float M, float E, float F, bool split, float LT, float MT, int b0, int b1,
+                                             int N, int m, float eps, float &P) {
+    const int t = last_test(b0, b1, m, N);
+    if (split) { L = lse2(E, LT); M = fminf(F, MT); }
+    P = p_acc(L, M, N - t);
+    return t > b0 && passes_test(P, eps);
+}
+
+// The exact stop of the heads that pass in the chunk of blocks b0 .. b1 - 1, one wave: (cl, cm) = the state of head lane % G
+// before it, Pt = its P_acc at the last tested position, block_value(i) = value i = (block, head) of the chunk's L_b.
+// Lane = (block, head), 64 values to a register and all registers asked for at once; a prefix scan over the blocks of each
+// head (steps of G lanes; the registers' scans side by side), on top of the state before, gives AS_acc and AS_min after every
+// block, hence P_acc at every position; the first tested position that passes is the stop -- the last one, should rounding
+// (another tree of sums than the chunk's word) let none pass.  kScan: registers that hold one value per (block, head).
+template <int G, int kScan, class BlockValue>
+__device__ __forceinline__ void stop_in_chunk(int b0, int b1, float cl, float cm, float Pt, int N, int m, float eps,
+                                              BlockValue block_value, int &n, float &P_stop, int lane) {
+    const int g = lane % G, cnt = (b1 - b0) * G;
+    const unsigned long long head_lanes = (~0ull / ((1ull << G) - 1ull)) << g;   // the lanes of my head
+    n = last_test(b0, b1, m, N);
+    P_stop = Pt;
+    if (first_test(b0, m, N) == n) return;     // (uniform)
+    bool found = false;
+    float pl[kScan], pm[kScan];
+#pragma unroll
+    for (int u = 0; u < kScan; ++u) pm[u] = pl[u] = block_value(min(64 * u + lane, cnt - 1));
+#pragma nounroll
+    for (int d = G; d < 64; d <<= 1) {
+#pragma unroll
+        for (int u = 0; u < kScan; ++u) {
+            const float ol = __shfl_up(pl[u], d), om = __shfl_up(pm[u], d);
+            if (lane >= d) { pl[u] = lse2(ol, pl[u]); pm[u] = fminf(om, pm[u]); }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kScan; ++u) {
+        const float fl = lse2(cl, pl[u]), fm = fminf(cm, pm[u]);
+        const int nn = b0 + (64 * u + lane) / G + 1;
+        const float P = p_acc(fl, fm, N - nn);
+        const unsigned long long hits =
+            __ballot(64 * u + lane < cnt && (nn % m == 0 || nn == N) && passes_test(P, eps)) & head_lanes;
+        const int src = hits ? (__ffsll((long long)hits) - 1) : 0;
+        const float Pf = __shfl(P, src);
+        if (!found && hits) {
+            n = b0 + (64 * u + src) / G + 1;
+            P_stop = Pf;
+            found = true;
+        }
+        cl = __shfl(fl, 64 - G + g);       // my head's state after this register's last block
+        cm = __shfl(fm, 64 - G + g);
+    }
+}
+__device__ __forceinline__ unsigned long long stop_word(int n, float P) { return ((unsigned long long)n << 32) | __float_as_uint(P); }
+
+// Folds chunks j .. k-1 of the stream's first group, whose words and block values are all at hand, one wave: the chunks in
+// which an open head passes are visited in order (there are at most G stops per stream) for the head's exact stop.
+// stop = the head's stop so far; block_value(b, i) is value i = (block, head) of the chunk that starts at block b.
+// Returns the chunks folded now: k, or less when every head has stopped (then all_stopped).
+template <int G, int kScan, class BlockValue>
+__device__ __forceinline__ int fold_group(float L, float M, float LT, float MT, unsigned long long &stop, int j, int k, int N,
+                                          int m, int KU, int budget, float eps, bool &all_stopped, BlockValue block_value, int lane) {
+    const int nlim = blocks_that_count(N, budget), g = lane % G, jl = lane / G;
+    all_stopped = false;
+    float E, F, P;
+    group_states<G>(L, M, -INFINITY, INFINITY, E, F, lane);
+    const bool passes = chunk_passes(L, M, E, F, split_words(KU, m, budget), LT, MT, jl * KU, min(jl * KU + KU, nlim), N, m, eps, P);
     while (j < k) {
         const unsigned long long cand = __ballot(jl >= j && jl < k && stop == ~0ull && passes);
         if (cand == 0ull) return k;
-        const int js = (__ffsll((long long)cand) - 1) / G;          // the first chunk in which an open head passes
-        const bool scan = (cand >> (js * G + g)) & 1ull;            // does mine?
-        if (__shfl(ready, js * G) == 0) return js;
-        // That chunk's blocks' L_b, lane = (block, head), 64 values to a register and all registers asked for at
-        // once; a prefix scan over the blocks of each head (steps of G lanes; the registers' scans side by side),
-        // on top of the state after the chunk before, gives AS_acc and AS_min after every block, hence P_acc at
-        // every position; the first tested position that passes is the stop.
-        const int cb0 = (base + js) * KU, cnt = (min(cb0 + KU, N) - cb0) * G;
-        float cl = js == 0 ? Cacc : __shfl(L, (js - 1) * G + g);
-        float cm = js == 0 ? Cmin : __shfl(M, (js - 1) * G + g);
-        bool found = false;
-        float pl[kScan], pm[kScan];
-#pragma unroll
-        for (int u = 0; u < kScan; ++u) pm[u] = pl[u] = block_value(cb0, min(64 * u + lane, cnt - 1));
-#pragma nounroll
-        for (int d = G; d < 64; d <<= 1) {
-#pragma unroll
-            for (int u = 0; u < kScan; ++u) {
-                const float ol = __shfl_up(pl[u], d), om = __shfl_up(pm[u], d);
-                if (lane >= d) { pl[u] = lse2(ol, pl[u]); pm[u] = fminf(om, pm[u]); }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kScan; ++u) {
-            const float fl = lse2(cl, pl[u]), fm = fminf(cm, pm[u]);
-            const int nn = cb0 + (64 * u + lane) / G + 1;
-            const float P = p_acc(fl, fm, N - nn);
-            const unsigned long long hits =
-                __ballot(64 * u + lane < cnt && (nn % m == 0 || nn == N) && passes_test(P, eps)) & head_lanes;
-            const int src = hits ? (__ffsll((long long)hits) - 1) : 0;
-            const float Pf = __shfl(P, src);
-            if (scan && !found && hits) {
-                stop = ((unsigned long long)(cb0 + (64 * u + src) / G + 1) << 32) | __float_as_uint(Pf);
-                found = true;
-            }
-            cl = __shfl(fl, 64 - G + g);       // my head's state after this register's last block
-            cm = __shfl(fm, 64 - G + g);
-        }
+        const int js = (__ffsll((long long)cand) - 1) / G, src = js * G + g;   // the first chunk in which an open head passes
+        int n;
+        float Ps;
+        stop_in_chunk<G, kScan>(js * KU, min(js * KU + KU, nlim), __shfl(E, src), __shfl(F, src), __shfl(P, src), N, m, eps,
+                                [&](int i) { return block_value(js * KU, i); }, n, Ps, lane);
+        if ((cand >> src) & 1ull) stop = stop_word(n, Ps);
         j = js + 1;
         if (__ballot(stop == ~0ull) == 0ull) { all_stopped = true; return j; }
     }

@@ -160,7 +160,8 @@ __global__ __launch_bounds__(1024, 8) void order_kernel(KvView kv, DecodeWs ws, 
     if (part == 0) {
         unsigned long long *a = ws.agg + (size_t)s * ws.max_chunks * G;
         for (int i = tid; i < ws.max_chunks * G; i += nthreads) a[i] = kAggSentinel;      // nothing published yet
-        if (tid < 32) *lse_ready_word(&ws.ctl[s], tid * 32) = 0u;
+        unsigned long long *c = ws.carry + (size_t)s * ws.max_groups * G;
+        for (int i = tid; i < ws.max_groups * G; i += nthreads) c[i] = kAggSentinel;
     }
 
     // LDS carve-up of the bucket path: 8*Np bytes + scratch

@@ -22,10 +22,12 @@
 //      scaled logits of all G heads as a 16-token x 16-head x 128-channel product on the matrix
 //      cores (heads beyond G are zero columns), keeps them in LDS until the chunk is done, and then reduces
 //      every block's log-sum-exp L_b (= log AS of line 10) at once;
-//   4. publishes the chunk's (log-sum-exp, minimum) of L_b per head as one 64-bit word per head, then the L_b
-//      themselves, then a bit that says they are there;
-//   5. waits until the fold has passed the chunk and knows how many of its blocks every head uses, reads those value
-//      slices, and leaves the chunk's part of the output (reference, sum of weights, numerator) for the final merge.
+//   4. publishes the chunk's (log-sum-exp, minimum) of L_b per head as one 64-bit word per head;
+//   5. waits for the words of the chunks before it and finds how many of its blocks every head uses -- a head stops in the
+//      first chunk at whose last tested position P_acc exceeds the threshold, and if that is this one, at a block that a
+//      prefix scan over the chunk's L_b finds;
+//   6. reads those value slices, and leaves the chunk's part of the output (reference, sum of weights, numerator) for the
+//      final merge.
 // Keys and values in one kernel: the logits stay in LDS.  In a kernel of its own the value pass had them written to memory
 // and read back (6 % of the keys' bytes at G = 4, 12 % at G = 8, and writes cost this kernel several times their bytes), and
 // it could not begin before the last stream's fold had ended, nor the launch gap be hidden; here the values of the streams
@@ -38,29 +40,33 @@
 // From the last key to the published word a chunk takes 0.9 us, and 3.2 us from its first load on an idle chip; with
 // the reduction inside the loop over the slices, and the words after all stores, these were 1.0 us (3 us under load)
 // and 4.6 us.  A call at 32K tokens, batch 8, went from 112.5 to 109.7 us, at 4K, batch 31, from 58.1 to 54.1.
-// The wait of step 2 is a courtesy: when the looks run out the workgroup simply reads its chunk.  The wait of step 5 is for
-// chunks of the same stream that come before, whose workgroups have smaller indexes and publish before they wait for anything
-// themselves: the hardware starts workgroups in the order of their indexes (within each of the chip's partitions), so the
+// The wait of step 2 is a courtesy: when the looks run out the workgroup simply reads its chunk.  The wait of step 5 is for the words of
+// chunks of the same stream that come before, whose workgroups have smaller indexes and publish before they wait for those
+// before them: the hardware starts workgroups in the order of their indexes (within each of the chip's partitions), so the
 // one with the smallest index that is not done never waits for one that has not started.  It is bounded all the same.
-// THE FOLD applies lines 12-17 strictly in rank order: AS_acc, AS_min, N_left and P_acc at the end
-// of each published chunk after the frontier and, in the first chunk where P_acc exceeds the
-// threshold, with a prefix scan over the chunk's blocks to find the head's exact stop.  One wave per
-// stream does it, in workgroups of its own at the head of the grid (so they start first): it looks at the
-// words of the next chunks, folds what is published, moves the frontier, tells the readers how far the
-// stream can still go (stop_bound), and looks again.  Once every head has stopped (or the blocks ran
-// out) it closes the stream: the chunks beyond what it used are never read.
+// THE FOLD applies lines 12-17 chunk by chunk, strictly in rank order, to steer the reading: AS_acc, AS_min and P_acc at
+// the last tested position of each published chunk after the frontier say in which chunk every head stops.  One wave per
+// stream does it, in workgroups of its own at the head of the grid (so they start first): it looks at the words of the next
+// chunks, folds what is published, moves the frontier, tells the readers how far the stream can still go (stop_bound),
+// and looks again.  Once every head has stopped (or the blocks ran out) it closes the stream: the chunks beyond what it used
+// are never read.  Chunks are folded in groups (see fold_stream); the state at the start of a group goes into a carry word,
+// from which the group's workgroups go on by themselves in step 5.  They had waited for the fold to pass their chunk and to
+// hand out the stops before, which it found from the L_b in memory: a chunk's way from its word to its values was then the
+// fold's look, its arithmetic, a load of the L_b, two stores one after the other, and the workgroup's look and load of the
+// stops -- 3.7 to 5.2 us on an idle chip and 7.5 in the median of a busy one.  One request of 4K tokens 29.0 -> 25.9 us a call,
+// 32K tokens, batch 8 89.2 -> 86.1, four layers at 128K 681 -> 669, 64 ragged requests at G = 8 1401 -> 1366, two tiers 353 ->
+// 335.  (With every waiting workgroup looking at its group's words all the time, instead of at one word until the fold has come
+// to the group, everything selected at 64K, batch 16, took 820 us instead of 766.)
 //
 // Communication between workgroups: every shared word is read and written with relaxed agent-scope
 // atomics (coherent accesses); a writer waits for its data stores to complete before it stores the
 // word that announces them (the chunk words, the progress word), and a reader looks at the announcing
 // word before it issues the loads that depend on it.  Accesses to one cache line are served one at a
 // time (tens of nanoseconds each), which is why one thread per workgroup touches the stream's control
-// block.  The chunks' partial outputs are plain stores: their reader is the next kernel.
+// block.  The chunks' partial outputs and the heads' stops are plain stores: their reader is the next kernel.
 //
 // The fold is one scan in rank order and every reduction has a fixed shape, so results are bitwise
 // reproducible although the scheduling is dynamic.
-#include <limits.h>
-
 #include "psa_attend.h"
 #include "psa_fold.h"
 #include "psa_host.h"
@@ -140,6 +146,7 @@ struct SelectShared {
     uint4 stage[kSelectThreads / 64][16 * 17];   // per wave: one key slice, rows padded to 272 bytes; later its numerators
     // the chunk's logits: position 4 r + j of a (block, head) row holds token 4 j + r
     __attribute__((aligned(16))) float lg[MAXB][G][kPage];
+    int cnt[G];                                      // blocks of the chunk each head uses (-1: nobody needs the chunk)
     float st_l[kSelectThreads / 64][G], st_ref[G];   // value phase: per wave the sum of its weights, the reference
 };
 
@@ -148,16 +155,15 @@ struct SelectShared {
 //     P_acc(n*) >= AS_acc(n) / (AS_acc(n) + AS_min(n) (N - n*)),
 // and the right-hand side exceeds eps as soon as N - n* < (AS_acc(n) / AS_min(n)) (1 - eps) / eps: the head stops at
 // the first tested position from there on, whatever the blocks in between hold.  Lane g < G carries head g
-// (a stopped head needs its stop, lanes >= G nothing); the result, the largest need of the group plus one chunk
+// (stop_end > 0: it has stopped in the chunk that ends there; lanes >= G need nothing); the result, the largest need of the group plus one chunk
 // to spare against rounding, is the same in every lane.  Keys beyond it are never worth reading.
 template <int G>
-__device__ __forceinline__ int stop_bound(float Lacc, float Lmin, unsigned long long stop, int n, int N, int m, int KU,
-                                          float odds) {
+__device__ __forceinline__ int stop_bound(float Lacc, float Lmin, int stop_end, int n, int N, int m, int KU, float odds) {
     const int lane = threadIdx.x & 63;
     int need = 0;
     if (lane < G) {
-        if (stop != ~0ull) {
-            need = (int)(stop >> 32);
+        if (stop_end > 0) {
+            need = stop_end;
         } else {
             // blocks that may be left over when the test first passes: fewer than ratio * odds (taken a little
             // low, and one lower still: the bound must hold in binary32)
@@ -175,13 +181,12 @@ __device__ __forceinline__ int stop_bound(float Lacc, float Lmin, unsigned long 
 }
 
 // The progress word of a stream (see StreamCtl).
-__device__ __forceinline__ unsigned long long progress_word(int stopped, int lim, int grant, int walked) {
-    return ((unsigned long long)(unsigned)stopped << 48) | ((unsigned long long)(unsigned)lim << 32) | ((unsigned)grant << 16) | (unsigned)walked;
+__device__ __forceinline__ unsigned long long progress_word(int lim, int grant, int walked) {
+    return ((unsigned long long)(unsigned)lim << 32) | ((unsigned)grant << 16) | (unsigned)walked;
 }
 __device__ __forceinline__ int progress_frontier(unsigned long long kp) { return (int)(kp & 0xffffull); }
 __device__ __forceinline__ int progress_grant(unsigned long long kp) { return (int)((kp >> 16) & 0xffffull); }
-__device__ __forceinline__ int progress_limit(unsigned long long kp) { return (int)((kp >> 32) & 0xffffull); }
-__device__ __forceinline__ int progress_stopped(unsigned long long kp) { return (int)(kp >> 48); }
+__device__ __forceinline__ int progress_limit(unsigned long long kp) { return (int)(kp >> 32); }
 // The read-ahead window of a stream when `closed` of the S streams have finished: the launch's total of chunks in
 // flight (window per stream x S) shared by the streams still open.
 __device__ __forceinline__ int granted(int window, int S, int closed) {
@@ -189,18 +194,17 @@ __device__ __forceinline__ int granted(int window, int S, int closed) {
 }
 
 // =================================================================================================
-// The fold (Algorithm 1 lines 12-18 in rank order): one wave per stream, from the kernel's first moment until
-// the stream closes.
+// The fold (Algorithm 1 lines 12-18 in rank order, a chunk at a time): one wave per stream, from the kernel's first moment
+// until the stream closes.
 //
-// Chunks are folded a GROUP at a time: 64 / G consecutive chunks, aligned, lane = (chunk of the group, head).  One
-// load fetches the group's words, fold_group takes them in rank order.  A sequential walk, chunk by chunk on G lanes,
-// cost a deep stream 0.3 us per chunk -- more than reading the chunk costs the rest of the machine.
-// The expression that gives the state after a chunk is fixed by the chunk's place in its group (the scan's tree over
-// the group's earlier chunks, then the carry), whatever part of the group was published when the wave looked: the
-// fold is reproducible bit for bit although its timing is not.
+// Chunks are folded a GROUP at a time: 64 / G consecutive chunks, aligned, lane = (chunk of the group, head), kLook groups
+// to a look; a look's loads are in flight together.  A sequential walk, chunk by chunk on G lanes, cost a deep stream 0.3 us
+// per chunk -- more than reading the chunk costs the rest of the machine.
+// The expression that gives the state after a chunk is fixed by the chunk's place in its group (see group_states): the
+// fold is reproducible bit for bit although its timing is not, and the chunks' own workgroups find the same bits.
 //
-// The wave waits for nothing but chunks whose workgroups are in this kernel's grid and never wait for anything
-// themselves beyond a bounded number of looks, so it always ends; a count of looks bounds it all the same
+// The wave waits for nothing but chunks whose workgroups are in this kernel's grid and never wait for anything but
+// chunks before them and, a bounded number of looks, for the window; so it always ends.  A count of looks bounds it all the same
 // (kFoldPatience: about half a second in which neither this stream moves nor another one closes), after which the stream
 // is closed as it stands and PSA_DEVERR_STALLED is raised.  With more streams than folding waves (4 * kMaxFoldGroups) a
 // wave folds several streams, one after the other, and the grid hands out the chunks in the same order: all chunks of the
@@ -212,20 +216,21 @@ constexpr int kFoldPatience = 1 << 19;
 constexpr int kMaxFoldGroups = 128;            // workgroups of four folding waves at most: they must leave the
                                                // compute units room for the chunks they wait for
 
-template <int G, int MAXB>
-__device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float eps, int m, int KU, int budget,
-                            int window) {
+template <int G>
+__device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float eps, int m, int KU, int budget, int window) {
     constexpr int CPG = 64 / G;                // chunks per group
-    constexpr int kScan = (MAXB * G + 63) / 64;   // registers that hold one value per (block, head) of a chunk
+    constexpr int kLook = CPG >= 32 ? 1 : 32 / CPG;   // groups per look: 32 chunks, 64 with one head
     const int lane = threadIdx.x & 63, g = lane % G, jl = lane / G;     // my head, my chunk of the group
+    const unsigned long long head_lanes = (~0ull / ((1ull << G) - 1ull)) << g;   // the lanes of my head
     StreamCtl *ctl = &ws.ctl[s];
-    const int ctx = stream_ctx(kv, s);
-    const int N = (ctx + kPage - 1) / kPage;
+    const int N = (stream_ctx(kv, s) + kPage - 1) / kPage;
     const unsigned long long *agg = ws.agg + (size_t)s * ws.max_chunks * G;
-    const float *block_lse = ws.block_lse + (size_t)s * kv.max_blocks * G;
+    const float2 *tested = ws.agg_tested + (size_t)s * ws.max_chunks * G;
+    unsigned long long *carry = ws.carry + (size_t)s * ws.max_groups * G;
+    const bool split = split_words(KU, m, budget);
     // chunks that may ever be folded: all of them, or those a fixed budget of blocks covers (the limit in the
     // progress word is for the readers of keys and may be tighter: see stop_bound)
-    const int nch = ((budget > 0 ? min(N, budget) : N) + KU - 1) / KU;
+    const int nlim = blocks_that_count(N, budget), nch = (nlim + KU - 1) / KU;
     if (nch == 0) {                            // an empty request: the ranking kernel left it closed
         if (lane == 0) atomicAdd(&ws.header[kClosedStreams], 1);
         return;
@@ -234,29 +239,68 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
     const int S = kv.batch * kv.num_kv_heads;
     const float odds = eps > 0.0f ? (1.0f - eps) / eps : INFINITY;      // (1 - eps) / eps of the stop test
     float Cacc = -INFINITY, Cmin = INFINITY;   // my head's (L_acc, L_min) at the start of the group
-    unsigned long long stop = ~0ull;           // my head's stop (n << 32 | P_acc bits), ~0 = still open
+    float P_end = 0.0f;                        // my head's P_acc at the last position tested in the chunk it stops in
+    int stop_end = 0;                          // blocks up to the end of the chunk my head stops in, 0 = still open
     int base = 0, walked = 0;                  // the group's first chunk; chunks folded so far
     int closed = 0, lim_now = nch;             // streams seen closed at the last look; the limit last published
     int looks = 0, seen = 0;                   // looks in vain since the stream moved or another one closed
     bool finished = false;
-    int stopped = 0;                           // bit g: head g's stop is in memory
-    auto publish_stops = [&]() __attribute__((always_inline)) {
-        const int now = (int)(__ballot(lane < G && stop != ~0ull) & 0xffull);
-        if (now == stopped) return;
-        stopped = now;
-        if (lane < G) st_relaxed(&ctl->stop[lane], stop);
-        stores_done();                         // (whoever sees the bit in the progress word reads the stop)
-    };
     while (!finished) {
-        // the group's words, and (in flight at the same time) how many streams have closed
-        const int ci = base + jl;
-        const unsigned long long v = (ci < nch) ? ld_relaxed(&agg[(size_t)ci * G + g]) : kAggSentinel;
-        const int cr = min(ci, nch - 1);
-        const uint32_t ready = (ld_relaxed(lse_ready_word(ctl, cr)) >> (cr & 31)) & 1u;   // are the chunk's block values there?
+        // the groups' words, and (in flight at the same time) how many streams have closed
+        unsigned long long v[kLook];
+#pragma unroll
+        for (int u = 0; u < kLook; ++u) {
+            const int ci = base + u * CPG + jl;
+            v[u] = (ci < nch) ? ld_relaxed(&agg[(size_t)ci * G + g]) : kAggSentinel;
+        }
         const int closed_now = uniform(ld_relaxed(&ws.header[kClosedStreams]));
-        const unsigned long long pub = __ballot(v != kAggSentinel);
-        const int k = ((pub == ~0ull) ? 64 : (__ffsll((long long)~pub) - 1)) / G;     // leading published chunks
-        if (base + k <= walked) {
+        const int before = walked;
+        float Lw = Cacc, Mw = Cmin;            // my head's state at the frontier (for stop_bound)
+#pragma unroll
+        for (int u = 0; u < kLook; ++u) {
+            const unsigned long long pub = __ballot(v[u] != kAggSentinel);
+            const int k = ((pub == ~0ull) ? 64 : (__ffsll((long long)~pub) - 1)) / G;     // leading published chunks
+            const int j = walked - base;                                                   // of which folded before
+            if (finished || k <= j) break;
+            float L = __uint_as_float((uint32_t)(v[u] & 0xffffffffull)), M = __uint_as_float((uint32_t)(v[u] >> 32)), E, F, P;
+            float LT = -INFINITY, MT = INFINITY;
+            if (split) {                       // (written before the chunk's word)
+                const size_t at = (size_t)min(base + jl, nch - 1) * G + g;
+                LT = ld_relaxed(&tested[at].x);
+                MT = ld_relaxed(&tested[at].y);
+            }
+            group_states<G>(L, M, Cacc, Cmin, E, F, lane);
+            const int b0 = (base + jl) * KU;
+            const bool passes = chunk_passes(L, M, E, F, split, LT, MT, b0, min(b0 + KU, nlim), N, m, eps, P);
+            const unsigned long long mine = __ballot(jl >= j && jl < k && stop_end == 0 && passes) & head_lanes;
+            if (mine != 0ull) {
+                const int src = __ffsll((long long)mine) - 1;
+                stop_end = min((base + src / G + 1) * KU, N);
+                P_end = __shfl(P, src);
+            }
+            if (__ballot(stop_end == 0) == 0ull) {                // every head has stopped: up to the last one's chunk
+                int last = stop_end;
+#pragma unroll
+                for (int d = 1; d < G; d <<= 1) last = max(last, __shfl_xor(last, d));
+                walked = uniform((last + KU - 1) / KU);
+                finished = true;
+            } else {
+                walked = base + k;
+                if (walked >= nch) finished = true;
+                Lw = __shfl(L, (k - 1) * G + g);
+                Mw = __shfl(M, (k - 1) * G + g);
+                if (k < CPG) break;            // (a later group's words wait for this one's)
+                if (!finished) {
+                    Cacc = Lw;
+                    Cmin = Mw;
+                    base += CPG;
+                    unsigned long long w = pack2(Cacc, Cmin);
+                    if (w >= kCarryStopped) w = kCarryStopped - 1;          // (a NaN pair that looks like one of the two)
+                    if (lane < G) st_relaxed(&carry[(size_t)(base / CPG) * G + g], stop_end > 0 ? kCarryStopped : w);
+                }
+            }
+        }
+        if (walked == before) {
             // Nothing new.  While the wait lasts, tell the readers if other streams have closed meanwhile, which
             // widens this one's window.
             if (++looks > kFoldPatience) {
@@ -266,43 +310,26 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
             if (closed_now != seen) { seen = closed_now; looks = 0; }
             if (closed_now != closed && walked > 0) {
                 closed = closed_now;
-                if (lane == 0) st_relaxed(&ctl->key_progress, progress_word(stopped, lim_now, granted(window, S, closed), walked));
+                if (lane == 0) st_relaxed(&ctl->key_progress, progress_word(lim_now, granted(window, S, closed), walked));
             }
             __builtin_amdgcn_s_sleep(8);
             continue;
         }
         closed = closed_now;
-        float L = __uint_as_float((uint32_t)(v & 0xffffffffull)), M = __uint_as_float((uint32_t)(v >> 32));
-        // (a chunk's blocks' values follow its words by a store round trip: if this look came in between, it is not `ready`)
-        const int j = fold_group<G, kScan>(L, M, Cacc, Cmin, stop, (int)ready, base, walked - base, k, N, m, KU, eps, finished,
-                                           [&](int b, int i) { return ld_relaxed(&block_lse[(size_t)b * G + i]); });
-        if (base + j == walked && !finished) {
-            if (++looks > kFoldPatience) {
-                if (lane == 0) set_error(ws.header, PSA_DEVERR_STALLED);
-                break;
-            }
-            continue;
-        }
-        walked = base + j;
         looks = 0;
-        if (walked >= nch) finished = true;
         if (finished) break;
-        // my head's state at the frontier (for stop_bound), and the carry once the whole group is folded
-        const float Lw = j == 0 ? Cacc : __shfl(L, (j - 1) * G + g), Mw = j == 0 ? Cmin : __shfl(M, (j - 1) * G + g);
-        if (j == CPG) { Cacc = Lw; Cmin = Mw; base += CPG; }
         // The frontier opens the window for waiting workgroups; the limit tells them how far the stream can still go.
         // The window: the launch's total of chunks in flight is shared by the streams still open, so the last,
         // deepest streams are read as wide as the whole batch was (a window sized for all streams leaves the
         // machine idle once most of them have closed).
-        const int lim = min(nch, stop_bound<G>(Lw, Mw, stop, walked * KU, N, m, KU, odds));
-        lim_now = lim;
-        publish_stops();
-        if (lane == 0) st_relaxed(&ctl->key_progress, progress_word(stopped, lim, granted(window, S, closed), walked));
+        lim_now = min(nch, stop_bound<G>(Lw, Mw, stop_end, walked * KU, N, m, KU, odds));
+        if (lane == 0) st_relaxed(&ctl->key_progress, progress_word(lim_now, granted(window, S, closed), walked));
     }
-    // every head has stopped, or the blocks ran out: close the stream (limit = frontier)
-    publish_stops();
+    // every head has stopped, or the blocks ran out: close the stream (limit = frontier).  A fixed budget is the one position
+    // tested, so the stops are known here, and its chunks have nothing to settle.
+    if (budget > 0 && lane < G && stop_end > 0) ctl->stop[lane] = stop_word(nlim, P_end);
     if (lane == 0) {
-        st_relaxed(&ctl->key_progress, progress_word(stopped, walked, 0, walked));
+        st_relaxed(&ctl->key_progress, progress_word(walked, 0, walked));
         atomicAdd(&ws.header[kClosedStreams], 1);
     }
 }
@@ -346,16 +373,19 @@ __device__ __forceinline__ void load_queries(SelectShared<G, MAXB> &sh, const Kv
 // Key work of one workgroup: chunk c of stream s.  Ends with the chunk published (wave 0 stores the chunk's
 // words, which the stream's folding wave is looking at).
 // =================================================================================================
+// What a chunk publishes, per head, in every lane of wave 0 (head lane % G): (log-sum-exp, minimum) of its L_b, and the
+// same up to its last tested position where that is not its end.
+struct Published { float L, M, LT, MT; };
+
 template <int DT, int G, int MAXB>
-__device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const uint8_t *__restrict__ q,
-                              const DecodeWs &ws, float eps, int m, int CB, int budget, int s, int c) {
+__device__ Published process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const uint8_t *__restrict__ q,
+                              const DecodeWs &ws, int m, int CB, int budget, int s, int c) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = s % kv.num_kv_heads;
     const int ctx = stream_ctx(kv, s);
     const int N = (ctx + kPage - 1) / kPage;
     const int start = c * CB;
     const int nblk = min(CB, N - start);
-    const size_t row0 = (size_t)s * kv.max_blocks + start;
     // (the chunk's pages and valid-token counts are in LDS already: stage_pages)
     // B operand of the QK^T product (see load_queries): the same for every chunk of the stream
     const int n = lane & 15, kq = lane >> 4;
@@ -403,27 +433,98 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
     // ---- the blocks' log-sum-exp L_b per head, from the logits in LDS, all threads of the workgroup at once ----------
     rows_lse<G, kSelectThreads>(&sh.lg[0][0][0], &sh.Lb[0][0], nblk * G, tid);
     lds_barrier();
-    if (wave != 0) return;
+    if (wave != 0) return Published{};
 
     // ---- publish: the chunk's (log-sum-exp, minimum) of its blocks' L_b per head ------------------------------------
-    float aggL, aggMin;
-    chunk_aggregate<G>(&sh.Lb[0][0], nblk, lane, aggL, aggMin);
-    unsigned long long w = pack2(aggL, aggMin);
+    Published own;
+    chunk_aggregate<G>(&sh.Lb[0][0], nblk, lane, own.L, own.M);
+    unsigned long long w = pack2(own.L, own.M);
     if (w == kAggSentinel) w = kAggSentinel - 1;     // a NaN pair that happens to look like "not published"
-    // The G words need no order among themselves: the fold takes a chunk only when it sees all of them.
+    own.LT = -INFINITY;
+    own.MT = INFINITY;
+    if (split_words(CB, m, budget)) {                // the same up to the chunk's last tested position, in memory before the word
+        chunk_aggregate<G>(&sh.Lb[0][0], last_test(start, min(start + nblk, blocks_that_count(N, budget)), m, N) - start, lane, own.LT, own.MT);
+        float2 *t = ws.agg_tested + ((size_t)s * ws.max_chunks + c) * G + lane;
+        if (lane < G) { st_relaxed(&t->x, own.LT); st_relaxed(&t->y, own.MT); }
+        stores_done();
+    }
+    // The G words need no order among themselves: a chunk counts as published when all of them are there.
     if (lane < G) st_relaxed(&ws.agg[((size_t)s * ws.max_chunks + c) * G + lane], w);
-    // The blocks' L_b follow, and a bit that says they are there: the fold needs them only in a chunk in which a head
-    // stops, so the frontier does not wait for these stores to complete (1 to 3 us while the memory system is busy).
-    for (int idx = lane; idx < nblk * G; idx += 64) st_relaxed(&ws.block_lse[row0 * G + idx], sh.Lb[idx / G][idx % G]);
-    stores_done();
-    if (lane == 0)
-        __hip_atomic_fetch_or(lse_ready_word(&ws.ctl[s], c), 1u << (c & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return own;
+}
+
+// (No fixed budget.)  How many of chunk c's blocks every head uses (sh.cnt), and the stops of the heads that stop in it: wave 0 waits for the
+// words of the group's chunks before this one and for the group's carry, and finds what the fold finds.  `own`: what the
+// chunk published.  Nobody needs the chunk if every head stops before it, which the words or the closed stream say.
+template <int G, int MAXB>
+__device__ void settle_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, const Published &own, float eps, int m,
+                             int CB, int s, int c) {
+    constexpr int CPG = 64 / G, kScan = (MAXB * G + 63) / 64;
+    const int lane = threadIdx.x & 63, g = lane % G, jl = lane / G;
+    const unsigned long long head_lanes = (~0ull / ((1ull << G) - 1ull)) << g;
+    const int N = (stream_ctx(kv, s) + kPage - 1) / kPage;
+    const int group = c / CPG, base = group * CPG, cj = c - base, start = c * CB, end = min(start + CB, N);
+    const unsigned long long *agg = ws.agg + ((size_t)s * ws.max_chunks + base) * G;
+    const float2 *tested = ws.agg_tested + ((size_t)s * ws.max_chunks + base) * G;
+    const unsigned long long *carry = ws.carry + ((size_t)s * ws.max_groups + group) * G;
+    unsigned long long v = 0, cw = 0;
+    bool close = group == 0;
+    for (int looks = 0, seen = -1;; ++looks) {
+        const unsigned long long kp = ld_relaxed(&ws.ctl[s].key_progress);
+        if (jl < cj && close) v = ld_relaxed(&agg[lane]);
+        if (group > 0 && close) cw = ld_relaxed(&carry[g]);
+        if (close && __ballot(v == kAggSentinel || cw == kAggSentinel) == 0ull) break;
+        const int fr = uniform(progress_frontier(kp)), lim = uniform(progress_limit(kp));
+        if (fr != seen) { seen = fr; looks = 0; }
+        const bool stalled = looks > kFoldPatience;
+        if (stalled && lane == 0) set_error(ws.header, PSA_DEVERR_STALLED);
+        if (c >= lim || stalled) {
+            if (lane < G) sh.cnt[lane] = -1;
+            return;
+        }
+        // Until the fold has come to the group, one word says so; then the words themselves.
+        const bool was = close;
+        close = fr >= base;
+        if (close && !was) continue;
+        // a fifth of a microsecond, and the same again for every eight chunks the fold has to go: the pollers of one stream
+        // share cache lines
+        for (int i = c - fr; i >= 0; i -= 8) __builtin_amdgcn_s_sleep(8);
+    }
+    float L = jl == cj ? own.L : (jl < cj ? __uint_as_float((uint32_t)(v & 0xffffffffull)) : -INFINITY);
+    float M = jl == cj ? own.M : (jl < cj ? __uint_as_float((uint32_t)(v >> 32)) : INFINITY);
+    const bool split = split_words(CB, m, 0);
+    float LT = own.LT, MT = own.MT;
+    if (split && jl < cj) {
+        LT = ld_relaxed(&tested[lane].x);
+        MT = ld_relaxed(&tested[lane].y);
+    }
+    const float Cacc = group > 0 ? __uint_as_float((uint32_t)(cw & 0xffffffffull)) : -INFINITY;
+    const float Cmin = group > 0 ? __uint_as_float((uint32_t)(cw >> 32)) : INFINITY;
+    float E, F, P;
+    group_states<G>(L, M, Cacc, Cmin, E, F, lane);
+    const int b0 = (base + jl) * CB;
+    const bool passes = jl <= cj && chunk_passes(L, M, E, F, split, LT, MT, b0, min(b0 + CB, N), N, m, eps, P);
+    const unsigned long long mine = __ballot(passes) & head_lanes;
+    const int first = mine != 0ull ? (__ffsll((long long)mine) - 1) / G : CPG;
+    const bool gone = first < cj || (group > 0 && cw == kCarryStopped), here = !gone && first == cj;
+    int cnt = gone ? 0 : end - start;
+    if (__ballot(here) != 0ull) {
+        const int src = cj * G + g;
+        int n;
+        float Ps;
+        stop_in_chunk<G, kScan>(start, end, __shfl(E, src), __shfl(F, src), __shfl(P, src), N, m, eps,
+                                [&](int i) { return (&sh.Lb[0][0])[i]; }, n, Ps, lane);
+        if (here) {
+            cnt = n - start;
+            if (lane < G) ws.ctl[s].stop[lane] = stop_word(n, Ps);      // (for the final merge)
+        }
+    }
+    if (lane < G) sh.cnt[lane] = cnt;
 }
 
 // =================================================================================================
-// The chunk's values (lines 10-12), by the workgroup that holds its logits, once the fold has passed the chunk: the heads
-// that are still open use all of it, and those that stop in it their stop's share.  (A fixed budget says how much beforehand,
-// so nothing is waited for.)  The four waves stream independently: wave w takes blocks w, w+4, ... of the chunk, and
+// The chunk's values (lines 10-12), by the workgroup that holds its logits: the heads that are still open use all of it, and
+// those that stop in it their stop's share (sh.cnt).  The four waves stream independently: wave w takes blocks w, w+4, ... of the chunk, and
 // nothing is shared until the sums at the end.
 //   weights   p = exp(logit - L), L = per head the largest log-sum-exp of a block the head uses: a reference every wave
 //             knows beforehand, so nothing is rescaled on the way and the four waves' sums simply add up.  (p <= 1, and
@@ -437,36 +538,10 @@ __device__ void process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const
 // =================================================================================================
 constexpr int kWholeChunk = 32;      // blocks of a chunk in the default plan: the size with a fixed schedule
 template <int DT, int G, int MAXB>
-__device__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int CB, int budget, int s, int c) {
+__device__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int s, int c) {
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), rg = lane >> 4, cl = lane & 15;
-    const int ctx = stream_ctx(kv, s), N = (ctx + kPage - 1) / kPage;
-    const int h = s % kv.num_kv_heads, start = c * CB, nblk = min(CB, N - start);
-    int mycnt = nblk;                                          // blocks of the chunk that head lane % G uses
-    if (budget > 0) {
-        mycnt = min(nblk, budget - start);
-    } else {
-        if (tid == 0) {
-            unsigned long long kp;
-            for (int looks = 0, seen = -1;; ++looks) {
-                kp = ld_relaxed(&ws.ctl[s].key_progress);
-                const int fr = progress_frontier(kp);
-                if (c < fr || c >= progress_limit(kp)) break;
-                if (fr != seen) { seen = fr; looks = 0; }
-                if (looks > kFoldPatience) { set_error(ws.header, PSA_DEVERR_STALLED); kp = 0; break; }   // (as good as closed)
-                // a fifth of a microsecond, and the same again for every four chunks the fold has to go: the pollers of
-                // one stream share a cache line
-                for (int i = c - fr; i >= 0; i -= 4) __builtin_amdgcn_s_sleep(8);
-            }
-            sh.kp0 = kp;
-        }
-        lds_barrier();
-        const unsigned long long kp = sh.kp0;
-        if (c >= progress_frontier(kp)) return;                // closed before this chunk
-        if (progress_stopped(kp) != 0) {                       // (the stops of the bits that are set are in memory)
-            const unsigned long long stop = ld_relaxed(&ws.ctl[s].stop[lane % G]);
-            if (stop != ~0ull) mycnt = min(nblk, max(0, (int)(stop >> 32) - start));
-        }
-    }
+    const int h = s % kv.num_kv_heads;
+    const int mycnt = sh.cnt[lane % G];                        // blocks of the chunk that head lane % G uses
     int maxcnt = mycnt;
 #pragma unroll
     for (int d = 1; d < G; d <<= 1) maxcnt = max(maxcnt, __shfl_xor(maxcnt, d));
@@ -564,7 +639,7 @@ __global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select
     const int folders = min((S + 3) / 4, kMaxFoldGroups);
     if ((int)blockIdx.x < folders) {
         for (int fs = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6); fs < S; fs += 4 * folders)
-            fold_stream<G, MAXB>(kv, ws, fs, eps, m, CB, budget, window > 0 ? window : 1);
+            fold_stream<G>(kv, ws, fs, eps, m, CB, budget, window > 0 ? window : 1);
         return;
     }
     // Workgroups go to the chip's eight partitions by index, round robin.  With the streams in the same order in
@@ -624,8 +699,14 @@ __global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select
     lds_barrier();
     if (!sh.go) return;
     if (threadIdx.x == 0) atomicAdd(&ws.ctl[s].k_blocks, min(CB, N - c * CB));     // traffic accounting
-    process_chunk<DT, G, MAXB>(sh, kv, q, ws, eps, m, CB, budget, s, c);
-    attend_chunk<DT, G, MAXB>(sh, kv, ws, CB, budget, s, c);
+    const Published own = process_chunk<DT, G, MAXB>(sh, kv, q, ws, m, CB, budget, s, c);
+    if (budget > 0) {                          // used by every head: the values wait for nothing
+        if (threadIdx.x < G) sh.cnt[threadIdx.x] = min(CB, min(N, budget) - c * CB);
+    } else if (threadIdx.x < 64) {
+        settle_chunk<G, MAXB>(sh, kv, ws, own, eps, m, CB, s, c);
+    }
+    lds_barrier();
+    attend_chunk<DT, G, MAXB>(sh, kv, ws, s, c);
 }
 
 template <int DT, int G>

@@ -37,6 +37,7 @@ struct SoloShared {
     float l[kSoloWaves][G];
     float Lb[kSoloBlocks][G];                              // per ranked block: log2-sum-exp2
     float aggL[kSoloUnits][G], aggMin[kSoloUnits][G];      // per chunk
+    float testL[kSoloUnits][G], testMin[kSoloUnits][G];    // the same up to the last tested position (see last_test)
     __attribute__((aligned(16))) uint32_t key[kSoloBlocks];   // ranking key by logical block
     int page[kSoloBlocks];                                 // by logical block
     int order[kSoloBlocks];                                // logical block by rank
@@ -221,17 +222,15 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
     float *logits = ws.logits + (size_t)s * kv.max_blocks * (kPage * G);
     int nread = 0;                                             // key slices read (traffic accounting)
     if (nch > 0) {
-        uint4 qb[4];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) qb[kk] = sh.qb[kk][lane];
-        unsigned long long stop = ~0ull;                       // wave 0: lane = (chunk, head)
         int walked = 0;
         for (int b0 = 0; b0 < min(N, nch * kSoloChunk); b0 += kSoloStep) {
             const int nblk = min(kSoloStep, min(N, nch * kSoloChunk) - b0);
             nread = b0 + nblk;
             {
-                uint4 ka[4][4];
+                uint4 ka[4][4], qb[4];                         // (qb from LDS every step: registers are short here)
                 int blk[4];
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) qb[kk] = sh.qb[kk][lane];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     blk[u] = sh.order[b0 + min(wave + kSoloWaves * u, nblk - 1)];      // (clamped: no branch around a load)
@@ -259,17 +258,26 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
                 const int c = b0 / kSoloChunk + wave;
                 chunk_aggregate<G>(&sh.Lb[c * kSoloChunk][0], min(kSoloChunk, nblk - wave * kSoloChunk), lane, aggL, aggMin);
                 if (lane < G) { sh.aggL[c][lane] = aggL; sh.aggMin[c][lane] = aggMin; }
+                if (split_words(kSoloChunk, m, budget)) {
+                    const int c0 = c * kSoloChunk;
+                    chunk_aggregate<G>(&sh.Lb[c0][0], last_test(c0, min(c0 + kSoloChunk, nlim), m, N) - c0, lane, aggL, aggMin);
+                    if (lane < G) { sh.testL[c][lane] = aggL; sh.testMin[c][lane] = aggMin; }
+                }
             }
             lds_barrier();
             if (wave == 0) {
-                const int g = lane % G, jl = lane / G, k = (b0 + nblk + kSoloChunk - 1) / kSoloChunk;
-                float L = jl < k ? sh.aggL[jl][g] : -INFINITY, M = jl < k ? sh.aggMin[jl][g] : INFINITY;
+                int ln = lane;                                 // (opaque: what derives from it is not kept in registers from before the loop)
+                asm volatile("" : "+v"(ln));
+                const int g = ln % G, jl = ln / G, k = (b0 + nblk + kSoloChunk - 1) / kSoloChunk;
+                const float L = jl < k ? sh.aggL[jl][g] : -INFINITY, M = jl < k ? sh.aggMin[jl][g] : INFINITY;
+                const bool split = split_words(kSoloChunk, m, budget) && jl < k;
+                const float LT = split ? sh.testL[jl][g] : -INFINITY, MT = split ? sh.testMin[jl][g] : INFINITY;
+                unsigned long long stop = sh.stop[g];          // lane = (chunk, head)
                 bool all = false;
-                walked = fold_group<G, (kSoloChunk * G + 63) / 64>(L, M, -INFINITY, INFINITY, stop, 1, 0, walked, k, N, m,
-                                                                    kSoloChunk, eps, all,
-                                                                    [&](int b, int i) { return (&sh.Lb[b][0])[i]; });
-                if (lane < G) sh.stop[lane] = stop;
-                if (lane == 0) sh.finished = all || walked >= nch;
+                walked = fold_group<G, (kSoloChunk * G + 63) / 64>(L, M, LT, MT, stop, walked, k, N, m, kSoloChunk, budget, eps, all,
+                                                                    [&](int b, int i) { return (&sh.Lb[b][0])[i]; }, ln);
+                if (ln < G) sh.stop[ln] = stop;
+                if (ln == 0) sh.finished = all || walked >= nch;
             }
             lds_barrier();
             if (sh.finished) break;
