@@ -111,9 +111,11 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
 
 // psa_score.hip, psa_order.hip, psa_select.hip, psa_values.hip: the kernels of one decode call
 // Whether the scores of such a call are formed on the matrix cores (see psa_score.hip).  Another order of sums can swap two
-// blocks whose scores nearly tie, so every path of a call has to form them in the same way.
-inline bool score_on_matrix_cores(int G, int num_kv_heads, int scorer) {
-    return G >= 8 && scorer != 2 && !(num_kv_heads > 1 && 16 % num_kv_heads == 0);
+// blocks whose scores nearly tie, so every path of a call has to form them in the same way.  Up to 128 blocks (one launch,
+// unless tuned) packed dots are as good where they read whole pages' records: two requests of 36 blocks 15.5 us, 15.9 on the
+// matrix cores.
+inline bool score_on_matrix_cores(int G, int num_kv_heads, int scorer, int max_blocks) {
+    return G >= 8 && scorer != 2 && (max_blocks > 128 || !(num_kv_heads > 1 && 16 % num_kv_heads == 0));
 }
 hipError_t launch_score(const KvView &kv, int dtype, int G, int scorer, const void *q, const void *meta,
                         const DecodeWs &ws, float *scores_out, hipStream_t st);

@@ -4,8 +4,13 @@
 
 namespace psa {
 
-constexpr int kScoreBlocks = 64;   // blocks per workgroup and round: 16 per wave (the matrix version: per workgroup)
-constexpr int kMaxRounds = 4;      // rounds a workgroup of score_kernel makes at most
+constexpr int kScoreBlocks = 64;   // blocks per workgroup and round, 16 per wave (score_kernel, score_mfma_kernel)
+constexpr int kMaxRounds = 4;      // rounds at most (the same two kernels)
+
+// Workgroups go to the chip's eight partitions by index, round robin: with a multiple of eight in x, the early blocks of all
+// rows would go to one partition and the late ones, which short requests do not have, to another.  So x rotates by row
+// (six requests of 2.7K to 29K tokens, 32 KV heads: 102 -> 95.7 us a call).
+__device__ __forceinline__ int rotated_x() { return (int)((blockIdx.x + blockIdx.y) % gridDim.x); }
 
 // =================================================================================================
 // Scoring.  Upper bound (CENTER = 0):
@@ -34,7 +39,7 @@ __global__ __launch_bounds__(256) void score_kernel(KvView kv, const uint8_t *__
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 2) header[kClosedStreams] = 0;
     const int ctx = ctx_clamped_quiet(kv, r);
     const int N = (ctx + kPage - 1) / kPage;
-    const int base = (blockIdx.x * 4 + wave) * 16 * rounds;      // the wave's first block
+    const int base = (rotated_x() * 4 + wave) * 16 * rounds;      // the wave's first block
     if (base >= N) return;
     const int mine = min(16 * rounds, N - base);                 // blocks of this wave
 
@@ -126,7 +131,7 @@ __global__ __launch_bounds__(256) void score_pages_kernel(KvView kv, const uint8
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 2) header[kClosedStreams] = 0;
     const int ctx = ctx_clamped_quiet(kv, r);
     const int N = (ctx + kPage - 1) / kPage;
-    const int base = blockIdx.x * nb;
+    const int base = rotated_x() * nb;
     if (base >= N) return;
     const int mine = min(nb, N - base);                 // blocks of this workgroup
     const int32_t *table = kv.block_table + (size_t)r * kv.max_blocks;
@@ -194,71 +199,95 @@ __global__ __launch_bounds__(256) void score_pages_kernel(KvView kv, const uint8
 }
 
 // =================================================================================================
-// Scoring on the matrix cores (used at G = 8 when the KV-head count does not allow the page-by-page kernel above:
-// the stream-by-stream packed-dot kernel is bound by its arithmetic there).  Upper bound (CENTER = 0):
+// Scoring on the matrix cores, at G = 8 (with packed dots the vector ALUs were busy 58 % of the time and more: 64 ragged
+// requests of up to 128K tokens 1376 -> 1347 us a call, 34 of 41K with a budget 94.6 -> 87.4).  Upper bound
+// (CENTER = 0):
 //   UB[g][b] = (1/sqrt d) sum_c max(q_c kmin_c, q_c kmax_c) = (1/sqrt d) (q- . kmin + q+ . kmax)
 //   with q+ = max(q,0), q- = min(q,0).
 // Cuboid centre (CENTER = 1): (1/sqrt d) q . (kmin + kmax)/2 = (1/(2 sqrt d)) (q . kmin + q . kmax).
 // Either way CS[b] = max over the heads g of the group.
 // Both are one matrix product over the 256 numbers of a block's record [min(128) | max(128)]:
 //   D[block][head] = sum_e record[block][e] * qq[e][head],  qq = (q- | q+) or (q | q),
-// done as eight 16x16x32 steps on the matrix cores: 16 blocks per wave, row = block, the record's 512
-// contiguous bytes are the k dimension; columns beyond G are zero and left out of the maximum.
-// grid (ceil(max_blocks/64), S), 256 threads: wave w takes blocks 64*blockIdx.x + 16*w .. +15.
+// done as eight 16x16x32 steps: 16 blocks of one KV head, row = block, the record's 512 contiguous bytes are the k
+// dimension; columns beyond G are zero and left out of the maximum.
+// A wave takes such a unit of 16 blocks (8 KiB), or up to kMaxRounds of them of one head, two in flight.  Loaded in the
+// operand's layout a load instruction would touch half a cache line of sixteen records, which made this kernel slower than
+// the packed dots; so a record is loaded whole (32 lanes, two records to an instruction) and turned into the operand's
+// layout through the wave's own patch of LDS (rows 33 16-byte words apart: no bank conflicts).
+// grid (ceil(units / 4), batch), 256 threads: wave w takes unit 4 * blockIdx.x + w = (16 * rounds blocks, KV head), heads
+// varying fastest, so that the records of a page, which are contiguous, are read at about the same time.
 // =================================================================================================
 template <int DT, int G, int CENTER>
 __global__ __launch_bounds__(256) void score_mfma_kernel(KvView kv, const uint8_t *__restrict__ q,
                                                     const uint8_t *__restrict__ meta,
                                                     float *__restrict__ scores,
-                                                    float *__restrict__ scores_out, int32_t *header) {
-    const int s = blockIdx.y, r = s / kv.num_kv_heads, h = s % kv.num_kv_heads;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4, n = lane & 15;
+                                                    float *__restrict__ scores_out, int32_t *header, int rounds) {
+    __shared__ uint4 patch[4][16 * 33];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4, n = lane & 15, H = kv.num_kv_heads;
+    const int r = blockIdx.y, unit = __builtin_amdgcn_readfirstlane(rotated_x() * 4 + wave), h = unit % H;
     // first kernel of a decode call: it clears the sticky error word and clamps silently; the
     // ranking kernel, which sees the same table entries and contexts, reports them
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) header[threadIdx.x] = 0;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 2) header[kClosedStreams] = 0;
     const int ctx = ctx_clamped_quiet(kv, r);
     const int N = (ctx + kPage - 1) / kPage;
-    const int base = blockIdx.x * kScoreBlocks + wave * 16;
-    if (base >= N) return;
-
-    // A operand: row n = block base + n; step kk holds bytes 64*kk + 16*kq .. +15 of its record
+    const int base = unit / H * 16 * rounds;
+    if (base >= N) return;                                       // (the whole wave; there is no barrier)
+    const int mine = min(16 * rounds, N - base), s = r * H + h;
     const int32_t *table = kv.block_table + (size_t)r * kv.max_blocks;
-    const int page = clamp_page_quiet(table[min(base + n, N - 1)], kv.num_pages);
-    const uint8_t *mp = meta + ((size_t)page * kv.num_kv_heads + h) * kMetaBytes + kq * 16;
-    uint4 a[8];
+    const int page_of_lane = clamp_page_quiet(table[base + min(lane, mine - 1)], kv.num_pages);   // lane = block
+    uint4 qw[4];                                                 // the lane's part of the B operand: head n
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) a[kk] = ld16(mp + kk * 64);      // (half a cache line per record and load: the other half is the next load's, so not marked read-once)
-    // B operand: column n = head n; the same 8 numbers of the record's index range, taken from q with the
-    // entries of the wrong sign zeroed (steps 0-3 meet the minima, 4-7 the maxima)
-    f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-        uint4 b = make_uint4(0, 0, 0, 0);
-        if (n < G) {
-            const int ch = (32 * kk + 8 * kq) & 127;
-            b = ld16(q + ((size_t)(r * kv.num_q_heads + h * G + n) * kHeadDim + ch) * 2);
-            if (!CENTER) {
-                uint32_t w[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t neg = ((w[j] >> 15) & 0x00010001u) * 0xFFFFu;
-                    w[j] &= (kk >= 4) ? ~neg : neg;
-                }
-                b = make_uint4(w[0], w[1], w[2], w[3]);
-            }
-        }
-        d = mfma_16x16x32<DT>(a[kk], b, d);
+    for (int kk = 0; kk < 4; ++kk) {
+        qw[kk] = ld16(q + ((size_t)(r * kv.num_q_heads + h * G + min(n, G - 1)) * kHeadDim + (4 * kk + kq) * 8) * 2);
+        if (n >= G) qw[kk] = make_uint4(0, 0, 0, 0);
     }
-    // lane (kq, n): head n of blocks base + 4kq .. + 4kq+3; the maximum over the heads of the group
+    uint4 rec[2][8];
+    auto fetch = [&](int rd, uint4 (&dst)[8]) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float v = n < G ? d[j] : -INFINITY;
-        v = row_max16(v) * (CENTER ? 0.5f * kScale : kScale);
-        const int b2 = base + 4 * kq + j;
-        if (n == 0 && b2 < N) {
-            scores[(size_t)s * kv.max_blocks + b2] = v;
-            if (scores_out) scores_out[(size_t)s * kv.max_blocks + b2] = v;
+        for (int i = 0; i < 8; ++i) {
+            const int j = min(16 * rd + 2 * i + (lane >> 5), mine - 1);     // (clamped: the loads need no branch)
+            dst[i] = ld16_stream(meta + ((size_t)__shfl(page_of_lane, j) * H + h) * kMetaBytes + (lane & 31) * 16);
+        }
+    };
+    auto reduce = [&](int rd, const uint4 (&src)[8]) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) patch[wave][(2 * i + (lane >> 5)) * 33 + (lane & 31)] = src[i];
+        lds_wave_sync();
+        f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            uint32_t w[4] = {qw[kk & 3].x, qw[kk & 3].y, qw[kk & 3].z, qw[kk & 3].w};
+            if constexpr (CENTER == 0) {                         // (steps 0-3 meet the minima, 4-7 the maxima)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const uint32_t neg = ((w[x] >> 15) & 0x00010001u) * 0xFFFFu;
+                    w[x] &= kk >= 4 ? ~neg : neg;
+                }
+            }
+            d = mfma_16x16x32<DT>(patch[wave][n * 33 + 4 * kk + kq], make_uint4(w[0], w[1], w[2], w[3]), d);
+        }
+        lds_wave_sync();
+        // lane (kq, n): head n of blocks 4 kq .. 4 kq + 3; the maximum over the heads of the group, lane n < 4 stores block n's
+        float cs = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float v = row_max16(n < G ? d[j] : -INFINITY) * (CENTER ? 0.5f * kScale : kScale);
+            if (n == j) cs = v;
+        }
+        const int b = 16 * rd + 4 * kq + n;
+        if (n < 4 && b < mine) {
+            scores[(size_t)s * kv.max_blocks + base + b] = cs;
+            if (scores_out) scores_out[(size_t)s * kv.max_blocks + base + b] = cs;
+        }
+    };
+    const int nr = (mine + 15) / 16;
+    fetch(0, rec[0]);
+#pragma unroll
+    for (int rd = 0; rd < kMaxRounds; ++rd) {
+        if (rd < nr) {
+            if (rd + 1 < nr) fetch(rd + 1, rec[(rd + 1) & 1]);
+            reduce(rd, rec[rd & 1]);
         }
     }
 }
@@ -267,8 +296,7 @@ template <int DT, int G>
 static hipError_t launch_score_t(const KvView &kv, int scorer, const void *q, const void *meta, const DecodeWs &ws,
                                  float *scores_out, hipStream_t st) {
     const int S = kv.batch * kv.num_kv_heads;
-    const dim3 grid((kv.max_blocks + kScoreBlocks - 1) / kScoreBlocks, S);
-    // rounds per workgroup of score_kernel: as many (up to kMaxRounds) as still leave four workgroups per compute unit
+    // rounds per workgroup: as many as still leave four workgroups per compute unit
     long long per = ((long long)S * kv.max_blocks) / (4ll * compute_units() * kScoreBlocks);
     const int rounds = per < 1 ? 1 : (per > kMaxRounds ? kMaxRounds : (int)per);
     const dim3 grid_r((kv.max_blocks + kScoreBlocks * rounds - 1) / (kScoreBlocks * rounds), S);
@@ -277,22 +305,23 @@ static hipError_t launch_score_t(const KvView &kv, int scorer, const void *q, co
                                                        scores_out, ws.header, rounds);
         return hipGetLastError();
     }
-    if constexpr (G >= 8) {
-        if (score_on_matrix_cores(G, kv.num_kv_heads, scorer)) {
-            if (scorer == 1)
-                score_mfma_kernel<DT, G, 1><<<grid, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
-                                                                  scores_out, ws.header);
-            else
-                score_mfma_kernel<DT, G, 0><<<grid, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
-                                                                  scores_out, ws.header);
-            return hipGetLastError();
-        }
+    if constexpr (G >= 8) if (score_on_matrix_cores(G, kv.num_kv_heads, scorer, kv.max_blocks)) {
+        const int units = (kv.max_blocks + 16 * rounds - 1) / (16 * rounds) * kv.num_kv_heads;
+        const dim3 grid_u((units + 3) / 4, kv.batch);
+        if (scorer == 1)
+            score_mfma_kernel<DT, G, 1><<<grid_u, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
+                                                                scores_out, ws.header, rounds);
+        else
+            score_mfma_kernel<DT, G, 0><<<grid_u, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
+                                                                scores_out, ws.header, rounds);
+        return hipGetLastError();
     }
     if (kv.num_kv_heads > 1 && 16 % kv.num_kv_heads == 0) {
-        // all KV heads of a page together; blocks per workgroup: as many (up to 64) as still leave four
-        // workgroups per compute unit, in whole rounds of four steps
+        // all KV heads of a page together; blocks per workgroup: as many (up to 64) as still leave eight
+        // workgroups per compute unit, in whole rounds of four steps (with four, ragged batches leave the chip idle: 24 requests of
+        // 513 to 16K tokens took 79.7 us a call instead of 77.3; equal lengths make no difference)
         const int round_blocks = 4 * (16 / kv.num_kv_heads);
-        long long want = ((long long)kv.batch * kv.max_blocks) / (4ll * compute_units());
+        long long want = ((long long)kv.batch * kv.max_blocks) / (8ll * compute_units());
         int nb = (int)(want / round_blocks) * round_blocks;
         nb = nb < round_blocks ? round_blocks : (nb > 64 ? 64 : nb);
         const dim3 grid_p((kv.max_blocks + nb - 1) / nb, kv.batch);

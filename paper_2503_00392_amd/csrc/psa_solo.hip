@@ -124,23 +124,33 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
             if (scores_out) scores_out[(size_t)s * kv.max_blocks + blk] = cs;
         };
         if constexpr (MFMA) {
-            // one product over the blocks' records, row = block, as score_mfma_kernel forms it
-            const uint8_t *mp = meta + ((size_t)page_of_lane * kv.num_kv_heads + h) * kMetaBytes + rg * 16;
+            // one product over the blocks' records, row = block, as score_mfma_kernel forms it: whole rows are loaded (four
+            // to an instruction) and turned into the operand's layout through the wave's patch, the minima first
             uint4 a[8];
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk) a[kk] = ld16(mp + kk * 64);
+            for (int i = 0; i < 8; ++i) {
+                const int j = min(4 * (i & 3) + rg, N - 1 - 16 * wave);     // (clamped: the loads need no branch)
+                a[i] = ld16_stream(meta + ((size_t)__shfl(page_of_lane, j) * kv.num_kv_heads + h) * kMetaBytes + (i >> 2) * 256 + cl * 16);
+            }
             f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk) {
-                uint32_t w[4] = {qw[kk & 3].x, qw[kk & 3].y, qw[kk & 3].z, qw[kk & 3].w};
-                if constexpr (SCORER == 0) {
+            for (int half = 0; half < 2; ++half) {
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        const uint32_t neg = ((w[x] >> 15) & 0x00010001u) * 0xFFFFu;
-                        w[x] &= kk >= 4 ? ~neg : neg;
+                for (int i = 0; i < 4; ++i) sh.stage[wave][(4 * i + rg) * 17 + cl] = a[4 * half + i];
+                lds_wave_sync();
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) {
+                    uint32_t w[4] = {qw[kk].x, qw[kk].y, qw[kk].z, qw[kk].w};
+                    if constexpr (SCORER == 0) {
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            const uint32_t neg = ((w[x] >> 15) & 0x00010001u) * 0xFFFFu;
+                            w[x] &= half ? ~neg : neg;
+                        }
                     }
+                    d = mfma_16x16x32<DT>(sh.stage[wave][cl * 17 + 4 * kk + rg], make_uint4(w[0], w[1], w[2], w[3]), d);
                 }
-                d = mfma_16x16x32<DT>(a[kk], make_uint4(w[0], w[1], w[2], w[3]), d);
+                lds_wave_sync();
             }
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
@@ -401,7 +411,7 @@ static hipError_t launch_solo_t(const KvView &kv, const DecodeArgs &a, const Dec
 template <int DT, int G>
 static hipError_t launch_solo_g(const KvView &kv, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st) {
     if constexpr (G >= 8) {
-        if (score_on_matrix_cores(G, kv.num_kv_heads, a.scorer))
+        if (score_on_matrix_cores(G, kv.num_kv_heads, a.scorer, kv.max_blocks))
             return a.scorer == 1 ? launch_solo_t<DT, G, 1, true>(kv, a, ws, st) : launch_solo_t<DT, G, 0, true>(kv, a, ws, st);
     }
     return a.scorer == 2 ? launch_solo_t<DT, G, 2>(kv, a, ws, st)
