@@ -1,6 +1,7 @@
 // Dense control: exact paged decode attention (softmax(q K^T / sqrt d) V over every block),
 // split over the context, with fp32 online softmax; a second kernel merges the splits.
 #include "psa_attend.h"
+#include "psa_fold.h"
 #include "psa_host.h"
 
 namespace psa {
@@ -10,16 +11,21 @@ constexpr int kDenseStride = 132;  // M, l, error bits (head 0), pad, acc[128]
 
 // grid (nsplit, S); 256 threads.  Wave w of the workgroup takes blocks b0+w, b0+w+4, ... and carries its own
 // online softmax over them, both products on the matrix cores:
-//   logits  D[token][head] = K[token][channel] Q[channel][head]: four 16x16x32 steps.  Row r of the A operand
-//           stands for token 4*(r%4) + r/4, so that lane (kq, n) = (lane/16, lane%16) ends up with the logits
-//           of head n/2 for tokens kq, 4+kq, 8+kq, 12+kq -- the token rows its value loads fetch;
+//   logits  D[token][head] = K[token][channel] Q[channel][head]: four 16x16x32 steps (see block_logits); lane (kq, n) =
+//           (lane/16, lane%16) ends up with the logits of head n/2 for tokens kq, 4+kq, 8+kq, 12+kq -- the token rows its
+//           value loads fetch;
 //   values  D[head][channel] += P[head][token] V[token][channel]: eight 16x16x16 products per block (one per
 //           channel of the lane's eight), the weights split into two 16-bit halves in neighbouring rows (see
 //           add_weighted); lane (kq, cl) accumulates heads 2kq and 2kq+1 of channels 8cl..8cl+7.
 // The running maximum of a head is shared by the wave (two exchanges per block); the four waves are merged
 // once at the end.
+// Bound by memory: 5.9 -> 6.1 TB/s on 6 ragged requests of up to 64K tokens (147.5 -> 143.0 us a call), 256 requests of up to
+// 2048 143 -> 128 us, 8 of up to 30000 29.2 -> 27.0.  Whole rows of keys are loaded and turned into the operand's layout in
+// LDS, which alone gave 145.5, 134.5 and 28.4: loaded in that layout, an instruction touched half a cache line of sixteen
+// tokens and could not be marked read-once.  The next block's keys are under way while a block is worked on, with three workgroups
+// to a compute unit: with two (as many registers as the compiler likes) 140.6, 129.5 and 30.0, with four 144.7 on the first.
 template <int DT, int G>
-__global__ __launch_bounds__(256) void dense_split_kernel(KvView kv, const uint8_t *__restrict__ q,
+__global__ __launch_bounds__(256, 3) void dense_split_kernel(KvView kv, const uint8_t *__restrict__ q,
                                                           float *__restrict__ partial,
                                                           int blocks_per_split, int32_t *header) {
     const int s = blockIdx.y, split = blockIdx.x, nsplit = gridDim.x;
@@ -45,35 +51,37 @@ __global__ __launch_bounds__(256) void dense_split_kernel(KvView kv, const uint8
         qb[kk] = make_uint4(0, 0, 0, 0);
         if (hd < G) qb[kk] = ld16(q + ((size_t)(r * kv.num_q_heads + h * G + hd) * kHeadDim + (4 * kk + rg) * 8) * 2);
     }
-    const int row_token = 4 * (cl & 3) + (cl >> 2);      // the token this lane's row of the A operand stands for
+    __shared__ uint4 stage[4][16 * 17];                  // per wave: a key slice on its way into the operand's layout
     float m = -INFINITY, l = 0.0f;                       // head hd: running maximum (whole wave), exp-sum (this row group)
     f32x4_t acc[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int32_t *table = kv.block_table + (size_t)r * kv.max_blocks;
-    int pages = 0;                                       // lane j: page of the wave's block j of the next 64
-    for (int b = b0 + wave, i = 0; b < b1; b += 4, ++i) {
+    int pages = 0;                                       // lane j: page of the wave's block j of 64
+    auto slice_of = [&](int b, int i) __attribute__((always_inline)) {      // where block b, the wave's i-th, lies in the pools
         if ((i & 63) == 0) {
             const int bl = b + 4 * lane, page = table[min(bl, b1 - 1)];
             pages = clamp_page_quiet(page, kv.num_pages);
             if (pages != page) err |= PSA_DEVERR_PAGE_RANGE;
         }
-        const int page = __builtin_amdgcn_readlane(pages, i & 63);
-        const size_t off = ((size_t)page * kv.num_kv_heads + h) * kSliceBytes;
-        const uint8_t *kp = kv.k_pool + off + row_token * kRowBytes + rg * 16;
-        uint4 ka[4];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) ka[kk] = ld16(kp + kk * 64);     // (operand layout: half a cache line per row and load, the
-                                                                         // next load takes the other half -- not marked read-once)
+        return ((size_t)__builtin_amdgcn_readlane(pages, i & 63) * kv.num_kv_heads + h) * kSliceBytes;
+    };
+    size_t off = 0;
+    Slice k;
+    if (b0 + wave < b1) {
+        off = slice_of(b0 + wave, 0);
+        k = load_slice(kv.k_pool + off, lane);
+    }
+    for (int b = b0 + wave, i = 0; b < b1; b += 4, ++i) {
+        const Slice kc = k;
         Slice v = load_slice(kv.v_pool + off, lane);
+        if (b + 4 < b1) {                                // (the next keys are under way while these are worked on)
+            off = slice_of(b + 4, i + 1);
+            k = load_slice(kv.k_pool + off, lane);
+        }
         const int valid = min(kPage, ctx - b * kPage);
-        f32x4_t s4 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) s4 = mfma_16x16x32<DT>(ka[kk], qb[kk], s4);
-        float sc[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sc[j] = (4 * j + rg < valid) ? s4[j] * kScaleLog2 : -INFINITY;
+        const f32x4_t sc = block_logits<DT>(kc.r, qb, stage[wave], lane, valid);
         if (valid < kPage) zero_invalid_rows(v, rg, valid);
         float bm = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
         bm = fmaxf(bm, __shfl_xor(bm, 16));
