@@ -199,6 +199,13 @@ __device__ __forceinline__ f32x4_t mfma_16x16x32(const uint4 &a, const uint4 &b,
     }
 }
 
+// Sum of a record's eight products (0-3 the minima, 4-7 the maxima of the same channels), as a tree that begins with what
+// cancels.  One chain of eight accumulations loses more: the error of a bound's score against binary64 is 9.0e-8 of its size
+// that way, 5.5e-8 this way and with packed dots.
+__device__ __forceinline__ f32x4_t sum_tree(const f32x4_t (&d)[8]) {
+    return ((d[0] + d[4]) + (d[1] + d[5])) + ((d[2] + d[6]) + (d[3] + d[7]));
+}
+
 template <int DT>
 __device__ __forceinline__ float cvt_lo(uint32_t w) {
     if constexpr (DT == 0) {

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void score_pages_kernel(KvView kv, const uint8
 }
 
 // =================================================================================================
-// Scoring on the matrix cores, at G = 8 (with packed dots the vector ALUs were busy 58 % of the time and more: 64 ragged
+// Scoring on the matrix cores, at G = 8, where score_on_matrix_cores says so (with packed dots the vector ALUs were busy 58 % of the time and more: 64 ragged
 // requests of up to 128K tokens 1376 -> 1347 us a call, 34 of 41K with a budget 94.6 -> 87.4).  Upper bound
 // (CENTER = 0):
 //   UB[g][b] = (1/sqrt d) sum_c max(q_c kmin_c, q_c kmax_c) = (1/sqrt d) (q- . kmin + q+ . kmax)
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void score_pages_kernel(KvView kv, const uint8
 // Either way CS[b] = max over the heads g of the group.
 // Both are one matrix product over the 256 numbers of a block's record [min(128) | max(128)]:
 //   D[block][head] = sum_e record[block][e] * qq[e][head],  qq = (q- | q+) or (q | q),
-// done as eight 16x16x32 steps: 16 blocks of one KV head, row = block, the record's 512 contiguous bytes are the k
+// done as eight 16x16x32 products and a tree of sums: 16 blocks of one KV head, row = block, the record's 512 contiguous bytes are the k
 // dimension; columns beyond G are zero and left out of the maximum.
 // A wave takes such a unit of 16 blocks (8 KiB), or up to kMaxRounds of them of one head, two in flight.  Loaded in the
 // operand's layout a load instruction would touch half a cache line of sixteen records, which made this kernel slower than
@@ -254,7 +254,8 @@ __global__ __launch_bounds__(256) void score_mfma_kernel(KvView kv, const uint8_
 #pragma unroll
         for (int i = 0; i < 8; ++i) patch[wave][(2 * i + (lane >> 5)) * 33 + (lane & 31)] = src[i];
         lds_wave_sync();
-        f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
+        const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        f32x4_t part[8];
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
             uint32_t w[4] = {qw[kk & 3].x, qw[kk & 3].y, qw[kk & 3].z, qw[kk & 3].w};
@@ -265,8 +266,9 @@ __global__ __launch_bounds__(256) void score_mfma_kernel(KvView kv, const uint8_
                     w[x] &= kk >= 4 ? ~neg : neg;
                 }
             }
-            d = mfma_16x16x32<DT>(patch[wave][n * 33 + 4 * kk + kq], make_uint4(w[0], w[1], w[2], w[3]), d);
+            part[kk] = mfma_16x16x32<DT>(patch[wave][n * 33 + 4 * kk + kq], make_uint4(w[0], w[1], w[2], w[3]), zero);
         }
+        const f32x4_t d = sum_tree(part);
         lds_wave_sync();
         // lane (kq, n): head n of blocks 4 kq .. 4 kq + 3; the maximum over the heads of the group, lane n < 4 stores block n's
         float cs = 0.0f;

@@ -132,7 +132,8 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
                 const int j = min(4 * (i & 3) + rg, N - 1 - 16 * wave);     // (clamped: the loads need no branch)
                 a[i] = ld16_stream(meta + ((size_t)__shfl(page_of_lane, j) * kv.num_kv_heads + h) * kMetaBytes + (i >> 2) * 256 + cl * 16);
             }
-            f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
+            const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+            f32x4_t part[8];
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
 #pragma unroll
@@ -148,10 +149,11 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
                             w[x] &= half ? ~neg : neg;
                         }
                     }
-                    d = mfma_16x16x32<DT>(sh.stage[wave][cl * 17 + 4 * kk + rg], make_uint4(w[0], w[1], w[2], w[3]), d);
+                    part[4 * half + kk] = mfma_16x16x32<DT>(sh.stage[wave][cl * 17 + 4 * kk + rg], make_uint4(w[0], w[1], w[2], w[3]), zero);
                 }
                 lds_wave_sync();
             }
+            const f32x4_t d = sum_tree(part);
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
                 const float cs = row_max16(cl < G ? d[x] : -INFINITY) * (SCORER == 1 ? 0.5f * kScale : kScale);
