@@ -46,6 +46,9 @@ DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t) {
     // 30 against 28 with 8, 35 against 31 with 32 (at 1536 tokens the two are even there).  Above 128 blocks a stream that selects nearly all its blocks wants more than one unit, unless
     // there are streams for most of the chip: at 256 blocks 63 us against 32 with 8 streams, 99 against 103 with 192; at
     // 192 blocks 53 against 53 with 128.  Hence three streams for four blocks.
+    // (The chain was five kernels then.  With four, G = 4, 2048 tokens: little selected 16 us against 24 with 8 streams, 22 against
+    // 27 with 32, 24 against 33 with 128; all selected 25 against 24, 35 against 26, 39 against 39; 256 blocks, 192 streams 56
+    // against 55 and 97 against 93.  A stream's share is not known beforehand, so the line stays.)
     // Whoever tunes the general path, times its phases or brings a second tier gets the general path.  So does a call of more
     // streams than one grid of workgroups of 1024 threads can have (fewer than 2^32 threads).
     const bool tuned = t && (t->window_chunks > 0 || t->spin_limit > 0 || t->force_bitonic || t->phase_events ||

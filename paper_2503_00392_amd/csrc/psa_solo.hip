@@ -295,7 +295,7 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
             if (sh.finished) break;
         }
     }
-    // ---- values (lines 10-12): four waves to a unit of 32 ranked blocks, as the general path's value kernel -------
+    // ---- values (lines 10-12): four waves to a unit of 32 ranked blocks, as in the general path's chunks ----------
     const unsigned long long my_stop = sh.stop[lane % G];      // head lane % G's
     const int n_mine = (my_stop != ~0ull && (int)(my_stop >> 32) <= N) ? (int)(my_stop >> 32) : N;
     int nmax = n_mine;
