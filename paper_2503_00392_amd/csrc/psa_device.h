@@ -77,29 +77,27 @@ __device__ __forceinline__ const uint8_t *value_slice(const KvView &kv, int loc,
 }
 
 // A wave that has just read the key slice of (page, KV head h) from host memory -- lane l holds bytes 16 l .. 16 l + 15
-// of each of its four 1 KiB rows -- leaves a copy in the staging buffer, for the tier update that follows the call;
-// the wave that later reads the value slice adds it to the same entry.  Entries beyond the buffer's capacity are
-// not made (the update fetches those slices itself).
-__device__ __forceinline__ void stage_key_slice(const KvView &kv, int page, int h, const uint4 (&rows)[4], int lane) {
+// of each of its four 1 KiB rows -- leaves a copy in the staging buffer, for the tier update that follows the call.
+// Returns the entry (uniform), or -1 beyond the buffer's capacity (the update fetches those slices itself).
+__device__ __forceinline__ int stage_key_slice(const KvView &kv, int page, int h, const uint4 (&rows)[4], int lane) {
     int entry = 0;
     if (lane == 0) entry = (int)atomicAdd(staging_count(kv.staging), 1u);
     entry = __builtin_amdgcn_readfirstlane(entry);
-    if (entry < 0 || entry >= kv.staging_cap) return;
+    if (entry < 0 || entry >= kv.staging_cap) return -1;
     uint8_t *e = staging_entry(kv.staging, kv.staging_cap, entry) + lane * 16;
 #pragma unroll
     for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4 *>(e + i * 1024) = rows[i];
-    if (lane == 0) {
-        const long long id = kv.slice_base + (long long)page * kv.num_kv_heads + h;
-        staging_ids(kv.staging)[entry] = (int)id;
-        kv.staged_at[id] = entry;
-    }
+    if (lane == 0) staging_ids(kv.staging)[entry] = (int)(kv.slice_base + (long long)page * kv.num_kv_heads + h);
+    return entry;
 }
-__device__ __forceinline__ void stage_value_slice(const KvView &kv, int page, int h, const uint4 (&rows)[4], int lane) {
-    const int entry = kv.staged_at[kv.slice_base + (long long)page * kv.num_kv_heads + h];
-    if (entry < 0 || entry >= kv.staging_cap) return;
+// The same wave adds the value slice to the entry it got for the keys, and only then names the entry in staged_at.  Two streams may
+// read one slice (a page that two requests share, a bad table entry taken for page 0); each fills an entry of its own, and an
+// entry whose values are never read -- keys read ahead of the stop -- is never named, so whichever is named is whole.
+__device__ __forceinline__ void stage_value_slice(const KvView &kv, int entry, int page, int h, const uint4 (&rows)[4], int lane) {
     uint8_t *e = staging_entry(kv.staging, kv.staging_cap, entry) + kSliceBytes + lane * 16;
 #pragma unroll
     for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4 *>(e + i * 1024) = rows[i];
+    if (lane == 0) kv.staged_at[kv.slice_base + (long long)page * kv.num_kv_heads + h] = entry;
 }
 
 // ---- workspace of psa_decode_attention -----------------------------------------------------

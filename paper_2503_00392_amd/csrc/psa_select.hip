@@ -141,6 +141,7 @@ struct SelectShared {
     float Lb[MAXB][G];                     // per-block log2-sum-exp2
     int page[MAXB];
     int valid[MAXB];
+    int entry[MAXB];                       // second tier: the block's entry in the staging buffer, -1 = none (its wave's own)
     int go;                                // after the wait for the window: 1 = read the chunk, 0 = the stream closed
     unsigned long long kp0;                // the stream's progress word as the workgroup first saw it, later as it saw it last
     uint4 stage[kSelectThreads / 64][16 * 17];   // per wave: one key slice, rows padded to 272 bytes; later its numerators
@@ -401,7 +402,10 @@ __device__ Published process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, 
     };
     auto consume = [&](int i, const uint4 (&k)[4]) {
         // (second tier with a staging buffer: a slice that came over the host link is kept for the update)
-        if (kv.staging != nullptr && sh.page[i] >= 0) stage_key_slice(kv, sh.page[i], h, k, lane);
+        if (kv.staging != nullptr) {
+            const int entry = sh.page[i] >= 0 ? stage_key_slice(kv, sh.page[i], h, k, lane) : -1;
+            if (lane == 0) sh.entry[i] = entry;
+        }
         const f32x4_t sc = block_logits<DT>(k, qb, sh.stage[wave], lane, sh.valid[i]);
         if (n < G) *reinterpret_cast<f32x4_t *>(&sh.lg[i][n][4 * kq]) = sc;
     };
@@ -569,9 +573,9 @@ __device__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const 
     auto consume = [&](int j, auto slot) __attribute__((always_inline)) {
         constexpr int u = decltype(slot)::value;
         const int blk = wave + 4 * j;
-        if (kv.staging != nullptr) {                           // (second tier: see stage_key_slice; the entry is this wave's own)
-            const int loc = uniform(sh.page[blk]);
-            if (loc >= 0) stage_value_slice(kv, loc, h, v[u].r, lane);
+        if (kv.staging != nullptr) {                           // (second tier: see stage_value_slice)
+            const int entry = uniform(sh.entry[blk]);
+            if (entry >= 0) stage_value_slice(kv, entry, uniform(sh.page[blk]), h, v[u].r, lane);
         }
         const int valid = uniform(sh.valid[blk]);
         if (valid < kPage) zero_invalid_rows(v[u], rg, valid);

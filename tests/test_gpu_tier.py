@@ -354,3 +354,35 @@ def test_updates_on_a_second_stream_beside_the_next_layer(psa):
         assert got_stats[k][4] == want.promoted, f"update {k}: every slice placed comes from the staging buffer"
     _check_tables(tier, model, layers)
     assert got_stats[:, 3].sum() > 0, "the pool was meant to be too small"
+
+
+@pytest.mark.parametrize("hinted", [False, True])
+def test_a_slice_that_two_streams_read_is_staged_whole(psa, hinted):
+    """One long request whose keys are read ahead of its stop, and 31 requests of one block each, all of it a page that the
+    long one reads ahead and does not use: both stage the slice's keys, only one ever stages its values.  What the update
+    places is the bytes in host memory."""
+    cfg = get_config(3).scaled(batch=32, ctx=4096, num_q_heads=4, num_kv_heads=1, layers=1)
+    li = generate_layer(cfg, layer=5, device="cuda")
+    li.ctx_lens[1:] = 16
+    n_slices = li.k_pool.shape[0]
+    first = Layer(psa, li, psa.Tier(n_slices, 1), 0)
+    for eps in (0.3, 0.4, 0.5, 0.6, 0.7, 0.8, 0.85, 0.9, 0.93, 0.95, 0.97):
+        one = psa.decode_attention(first.dev, li.q, first.meta_dev, eps, 1, want_order=True)
+        if 32 < int(one.blocks_read[0, 0]) <= 64:
+            break
+    assert 32 < int(one.blocks_read[0, 0]) <= 64          # stops in its second chunk: the third is read for nothing
+    li.block_table[1:, 0] = li.block_table[0][one.order[0, 0, 64:95].long()]
+    for _ in range(8):
+        tier = psa.Tier(n_slices, n_slices)
+        model = TierModel(n_slices, n_slices)
+        L = Layer(psa, li, tier, 0)
+        L.host.staging = psa.Tier.staging_buffer(1 << 10)
+        hint = torch.full((32, 1), 96, dtype=torch.int32, device="cuda")
+        got = psa.decode_attention(L.host, li.q, L.meta_host, eps, 1, want_order=True,
+                                   tuning=psa.Tuning(depth_hint=hint) if hinted else None)
+        torch.cuda.synchronize()
+        assert psa.read_device_error(got._workspace) == 0
+        assert torch.equal(got.order[0], one.order[0]) and int(got.blocks_read[0, 0]) == int(one.blocks_read[0, 0])
+        st = _update(psa, L, got, tier, model)
+        assert st.misses == st.promoted == st.from_staging == int(one.blocks_read[0, 0]) + 31
+        _check_tables(tier, model, [L])
