@@ -137,7 +137,9 @@ typedef struct {
                                call divided by those not yet finished, at most 256 (default: 96 MiB of
                                keys over all pairs, 2 to 24 chunks)                                    */
     int32_t spin_limit;     /* looks (about a microsecond apart) a workgroup takes at the window before it
-                               reads its chunk regardless (default 1<<14); the wait only limits read-ahead  */
+                               reads its chunk regardless, and at the chunks before its own, while none of them
+                               comes, before it reads those as well (default 1<<14); costs reading, never
+                               correctness                                                            */
     int32_t force_bitonic;  /* 1: always rank with the bitonic network (testing); 0: automatic        */
     const int32_t *depth_hint; /* device pointer or NULL: [batch][num_kv_heads] blocks each (request, KV head)
                                is expected to need, e.g. blocks_read of the previous decode step of the

@@ -138,7 +138,7 @@ struct DecodeWs {
     float2 *agg_tested;     // [S][max_chunks][G]  the same up to the chunk's last tested position, where that can be another
                             // than its end; written before the chunk's words in agg
     unsigned long long *carry;  // [S][max_groups][G]  (L_acc, L_min) of the head before the group of chunks, kCarryStopped, or
-                            // kAggSentinel (the fold has not come there)
+                            // kAggSentinel (the last chunk of the group before is not settled)
     float *logits;          // [S][max_blocks][G][16]  short contexts only: scaled logits (log2 units) by ranked block;
                             // position 4*r + j of a (block, head) row holds token 4*j + r
     float *partial;         // [S][max_chunks][G][kPartialStride]

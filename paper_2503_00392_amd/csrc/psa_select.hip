@@ -25,7 +25,7 @@
 //   4. publishes the chunk's (log-sum-exp, minimum) of L_b per head as one 64-bit word per head;
 //   5. waits for the words of the chunks before it and finds how many of its blocks every head uses -- a head stops in the
 //      first chunk at whose last tested position P_acc exceeds the threshold, and if that is this one, at a block that a
-//      prefix scan over the chunk's L_b finds;
+//      prefix scan over the chunk's L_b finds (words that do not come, it makes itself: see settle_chunk);
 //   6. reads those value slices, and leaves the chunk's part of the output (reference, sum of weights, numerator) for the
 //      final merge.
 // Keys and values in one kernel: the logits stay in LDS.  In a kernel of its own the value pass had them written to memory
@@ -40,17 +40,21 @@
 // From the last key to the published word a chunk takes 0.9 us, and 3.2 us from its first load on an idle chip; with
 // the reduction inside the loop over the slices, and the words after all stores, these were 1.0 us (3 us under load)
 // and 4.6 us.  A call at 32K tokens, batch 8, went from 112.5 to 109.7 us, at 4K, batch 31, from 58.1 to 54.1.
-// The wait of step 2 is a courtesy: when the looks run out the workgroup simply reads its chunk.  The wait of step 5 is for the words of
-// chunks of the same stream that come before, whose workgroups have smaller indexes and publish before they wait for those
-// before them: the hardware starts workgroups in the order of their indexes (within each of the chip's partitions), so the
-// one with the smallest index that is not done never waits for one that has not started.  It is bounded all the same.
+// The wait of step 2 is a courtesy: when the looks run out the workgroup simply reads its chunk.  The wait of step 5 is for the
+// words of chunks of the same stream that come before, whose workgroups have smaller indexes.  Within one launch those have
+// always started: the hardware starts workgroups in the order of their indexes (within each of the chip's partitions), so the
+// one with the smallest index that is not done waits for none that has not.  Beside another launch that does not hold: the
+// waiting workgroups of one call can fill a partition while the next chunk of the other is queued behind them, and the other
+// way round.  So nobody relies on it: when the looks of step 5 run out, the workgroup reads the missing chunks itself and makes
+// their words and, at the end of a group, the carry.  Every workgroup that has started then ends without any that has not, in
+// whatever order they are started.
 // THE FOLD applies lines 12-17 chunk by chunk, strictly in rank order, to steer the reading: AS_acc, AS_min and P_acc at
 // the last tested position of each published chunk after the frontier say in which chunk every head stops.  One wave per
 // stream does it, in workgroups of its own at the head of the grid (so they start first): it looks at the words of the next
 // chunks, folds what is published, moves the frontier, tells the readers how far the stream can still go (stop_bound),
 // and looks again.  Once every head has stopped (or the blocks ran out) it closes the stream: the chunks beyond what it used
-// are never read.  Chunks are folded in groups (see fold_stream); the state at the start of a group goes into a carry word,
-// from which the group's workgroups go on by themselves in step 5.  They had waited for the fold to pass their chunk and to
+// are never read.  Chunks are folded in groups (see fold_stream); the workgroup of a group's last chunk leaves the state after it in
+// a carry word per head, from which the next group's workgroups go on by themselves in step 5.  They had waited for the fold to pass their chunk and to
 // hand out the stops before, which it found from the L_b in memory: a chunk's way from its word to its values was then the
 // fold's look, its arithmetic, a load of the L_b, two stores one after the other, and the workgroup's look and load of the
 // stops -- 3.7 to 5.2 us on an idle chip and 7.5 in the median of a busy one.  One request of 4K tokens 29.0 -> 25.9 us a call,
@@ -112,7 +116,7 @@ __device__ __forceinline__ unsigned long long shfl_u64(unsigned long long v, int
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 
-constexpr int kBatch = 4;            // key slices a wave keeps in flight
+constexpr int kKeyDepth = 4;         // key slices a wave keeps in flight
 constexpr int kValueDepth = 2;       // value slices a wave keeps in flight
 constexpr int kSelectThreads = 256;  // 4 waves; four such workgroups fit a CU (registers, LDS at G = 8)
 
@@ -143,11 +147,12 @@ struct SelectShared {
     int valid[MAXB];
     int entry[MAXB];                       // second tier: the block's entry in the staging buffer, -1 = none (its wave's own)
     int go;                                // after the wait for the window: 1 = read the chunk, 0 = the stream closed
-    unsigned long long kp0;                // the stream's progress word as the workgroup first saw it, later as it saw it last
+    unsigned long long kp0;                // the stream's progress word as the workgroup first saw it
     uint4 stage[kSelectThreads / 64][16 * 17];   // per wave: one key slice, rows padded to 272 bytes; later its numerators
     // the chunk's logits: position 4 r + j of a (block, head) row holds token 4 j + r
     __attribute__((aligned(16))) float lg[MAXB][G][kPage];
     int cnt[G];                                      // blocks of the chunk each head uses (-1: nobody needs the chunk)
+    int next;                                        // the chunk to read next (see settle_chunk), -1 = none
     float st_l[kSelectThreads / 64][G], st_ref[G];   // value phase: per wave the sum of its weights, the reference
 };
 
@@ -204,8 +209,8 @@ __device__ __forceinline__ int granted(int window, int S, int closed) {
 // The expression that gives the state after a chunk is fixed by the chunk's place in its group (see group_states): the
 // fold is reproducible bit for bit although its timing is not, and the chunks' own workgroups find the same bits.
 //
-// The wave waits for nothing but chunks whose workgroups are in this kernel's grid and never wait for anything but
-// chunks before them and, a bounded number of looks, for the window; so it always ends.  A count of looks bounds it all the same
+// The wave waits for nothing but chunks whose workgroups are in this kernel's grid, and those end without it: they wait for
+// the window and for chunks before them, each a bounded number of looks; so it always ends.  A count of looks bounds it all the same
 // (kFoldPatience: about half a second in which neither this stream moves nor another one closes), after which the stream
 // is closed as it stands and PSA_DEVERR_STALLED is raised.  With more streams than folding waves (4 * kMaxFoldGroups) a
 // wave folds several streams, one after the other, and the grid hands out the chunks in the same order: all chunks of the
@@ -227,7 +232,6 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
     const int N = (stream_ctx(kv, s) + kPage - 1) / kPage;
     const unsigned long long *agg = ws.agg + (size_t)s * ws.max_chunks * G;
     const float2 *tested = ws.agg_tested + (size_t)s * ws.max_chunks * G;
-    unsigned long long *carry = ws.carry + (size_t)s * ws.max_groups * G;
     const bool split = split_words(KU, m, budget);
     // chunks that may ever be folded: all of them, or those a fixed budget of blocks covers (the limit in the
     // progress word is for the readers of keys and may be tighter: see stop_bound)
@@ -295,9 +299,6 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
                     Cacc = Lw;
                     Cmin = Mw;
                     base += CPG;
-                    unsigned long long w = pack2(Cacc, Cmin);
-                    if (w >= kCarryStopped) w = kCarryStopped - 1;          // (a NaN pair that looks like one of the two)
-                    if (lane < G) st_relaxed(&carry[(size_t)(base / CPG) * G + g], stop_end > 0 ? kCarryStopped : w);
                 }
             }
         }
@@ -339,8 +340,7 @@ __device__ void fold_stream(const KvView &kv, const DecodeWs &ws, int s, float e
 // the workgroup looks at the window, so that the loads overlap its wait.
 template <int G, int MAXB>
 __device__ __forceinline__ void stage_pages(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int CB,
-                                            int s, int c) {
-    const int tid = threadIdx.x;
+                                            int s, int c, int tid) {
     const int ctx = stream_ctx(kv, s);
     const int N = (ctx + kPage - 1) / kPage;
     const int nblk = min(CB, N - c * CB);
@@ -378,10 +378,11 @@ __device__ __forceinline__ void load_queries(SelectShared<G, MAXB> &sh, const Kv
 // same up to its last tested position where that is not its end.
 struct Published { float L, M, LT, MT; };
 
-template <int DT, int G, int MAXB>
-__device__ Published process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const uint8_t *__restrict__ q,
-                              const DecodeWs &ws, int m, int CB, int budget, int s, int c) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// kBatch: key slices a wave keeps in flight.
+template <int DT, int G, int MAXB, int kBatch>
+__device__ __forceinline__ Published process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int m, int CB,
+                                                   int budget, int s, int c, int tid) {
+    const int lane = tid & 63, wave = tid >> 6;
     const int h = s % kv.num_kv_heads;
     const int ctx = stream_ctx(kv, s);
     const int N = (ctx + kPage - 1) / kPage;
@@ -410,7 +411,7 @@ __device__ Published process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, 
         if (n < G) *reinterpret_cast<f32x4_t *>(&sh.lg[i][n][4 * kq]) = sc;
     };
     constexpr int kWaves = kSelectThreads / 64;
-    if (nblk == 32) {
+    if (kBatch > 1 && nblk == 32) {
         // A whole chunk of 32 blocks, eight per wave: a rolling window.  kBatch slices are in flight; the oldest is
         // worked on and its registers go to the next load at once, so the wave never stands with nothing in
         // flight between rounds.
@@ -457,42 +458,73 @@ __device__ Published process_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, 
     return own;
 }
 
-// (No fixed budget.)  How many of chunk c's blocks every head uses (sh.cnt), and the stops of the heads that stop in it: wave 0 waits for the
-// words of the group's chunks before this one and for the group's carry, and finds what the fold finds.  `own`: what the
-// chunk published.  Nobody needs the chunk if every head stops before it, which the words or the closed stream say.
+// The first of chunks from .. to - 1 whose words (agg: the stream's) are not all there, -1 if they are.  One wave.
+template <int G>
+__device__ __forceinline__ int first_unpublished(const unsigned long long *agg, int from, int to, int lane) {
+    for (int i0 = from * G; i0 < to * G; i0 += 64) {
+        const unsigned long long w = i0 + lane < to * G ? ld_relaxed(&agg[i0 + lane]) : 0;
+        const unsigned long long missing = __ballot(w == kAggSentinel);
+        if (missing != 0ull) return (i0 + __ffsll((long long)missing) - 1) / G;
+    }
+    return -1;
+}
+
+// Looks (about a microsecond each) at a frontier that stands still before a workgroup reads what is missing: spin_limit, and no
+// more than this many unless slices come over the host link, where a chunk can take milliseconds.  A launch that has the chip to
+// itself reads nothing twice even with 64; launches beside others, of 2 to 4 streams, read no more than one after the
+// other (8 requests of 32K tokens on each of 3 streams: 203 us a round, 264 in turn).
+constexpr int kPatience = 1 << 10;
+
+// (No fixed budget.)  How many of chunk c's blocks every head uses (sh.cnt), and the stops of the heads that stop in it: wave
+// 0 waits for the words of the group's chunks before this one and for the group's carry, and finds what the fold finds; the
+// group's last chunk leaves the next group's carry.  `own`: what the chunk published.  Nobody needs the workgroup's own chunk, `mine`, if every
+// head stops before it, which the words or the closed stream say.
+// sh.next: -1 once `mine` is settled, else the chunk this workgroup is to read next.  When the looks have brought nothing, the workgroup reads the chunks before its own whose words are missing, the first one first, settles each
+// (c < mine until then), and comes back to its own.  Whatever a chunk leaves in memory is the same bits whoever works on it,
+// so it does not matter that the chunk's own workgroup is under way, or comes later.
 template <int G, int MAXB>
-__device__ void settle_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, const Published &own, float eps, int m,
-                             int CB, int s, int c) {
+__device__ __forceinline__ void settle_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, const Published &own,
+                                             float eps, int m, int CB, int spin_limit, int s, int c, int mine, int lane) {
     constexpr int CPG = 64 / G, kScan = (MAXB * G + 63) / 64;
-    const int lane = threadIdx.x & 63, g = lane % G, jl = lane / G;
+    const int g = lane % G, jl = lane / G;
     const unsigned long long head_lanes = (~0ull / ((1ull << G) - 1ull)) << g;
     const int N = (stream_ctx(kv, s) + kPage - 1) / kPage;
     const int group = c / CPG, base = group * CPG, cj = c - base, start = c * CB, end = min(start + CB, N);
-    const unsigned long long *agg = ws.agg + ((size_t)s * ws.max_chunks + base) * G;
+    const unsigned long long *words = ws.agg + (size_t)s * ws.max_chunks * G, *agg = words + base * G;
     const float2 *tested = ws.agg_tested + ((size_t)s * ws.max_chunks + base) * G;
-    const unsigned long long *carry = ws.carry + ((size_t)s * ws.max_groups + group) * G;
+    unsigned long long *carry = ws.carry + ((size_t)s * ws.max_groups + group) * G;
+    const int patience = kv.slot_pool != nullptr ? spin_limit : min(spin_limit, kPatience);
     unsigned long long v = 0, cw = 0;
     bool close = group == 0;
-    for (int looks = 0, seen = -1;; ++looks) {
+    for (int looks = 0, seen = -1;;) {
         const unsigned long long kp = ld_relaxed(&ws.ctl[s].key_progress);
         if (jl < cj && close) v = ld_relaxed(&agg[lane]);
         if (group > 0 && close) cw = ld_relaxed(&carry[g]);
         if (close && __ballot(v == kAggSentinel || cw == kAggSentinel) == 0ull) break;
         const int fr = uniform(progress_frontier(kp)), lim = uniform(progress_limit(kp));
-        if (fr != seen) { seen = fr; looks = 0; }
-        const bool stalled = looks > kFoldPatience;
-        if (stalled && lane == 0) set_error(ws.header, PSA_DEVERR_STALLED);
-        if (c >= lim || stalled) {
+        if (mine >= lim) {
             if (lane < G) sh.cnt[lane] = -1;
+            if (lane == 0) sh.next = -1;
             return;
+        }
+        if (fr != seen) { seen = fr; looks = 0; }
+        const bool tired = looks > patience;
+        if (tired) {
+            const int missing = first_unpublished<G>(words, fr, c, lane);
+            if (missing >= 0) {
+                if (lane == 0) sh.next = missing;
+                return;
+            }
+            looks = 0;
         }
         // Until the fold has come to the group, one word says so; then the words themselves.
         const bool was = close;
-        close = fr >= base;
+        close = fr >= base || tired;
         if (close && !was) continue;
         // a fifth of a microsecond, and the same again for every eight chunks the fold has to go: the pollers of one stream
         // share cache lines
         for (int i = c - fr; i >= 0; i -= 8) __builtin_amdgcn_s_sleep(8);
+        looks += 1 + (max(0, c - fr) >> 3);
     }
     float L = jl == cj ? own.L : (jl < cj ? __uint_as_float((uint32_t)(v & 0xffffffffull)) : -INFINITY);
     float M = jl == cj ? own.M : (jl < cj ? __uint_as_float((uint32_t)(v >> 32)) : INFINITY);
@@ -508,8 +540,8 @@ __device__ void settle_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const 
     group_states<G>(L, M, Cacc, Cmin, E, F, lane);
     const int b0 = (base + jl) * CB;
     const bool passes = jl <= cj && chunk_passes(L, M, E, F, split, LT, MT, b0, min(b0 + CB, N), N, m, eps, P);
-    const unsigned long long mine = __ballot(passes) & head_lanes;
-    const int first = mine != 0ull ? (__ffsll((long long)mine) - 1) / G : CPG;
+    const unsigned long long hits = __ballot(passes) & head_lanes;
+    const int first = hits != 0ull ? (__ffsll((long long)hits) - 1) / G : CPG;
     const bool gone = first < cj || (group > 0 && cw == kCarryStopped), here = !gone && first == cj;
     int cnt = gone ? 0 : end - start;
     if (__ballot(here) != 0ull) {
@@ -523,7 +555,14 @@ __device__ void settle_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const 
             if (lane < G) ws.ctl[s].stop[lane] = stop_word(n, Ps);      // (for the final merge)
         }
     }
+    if (cj == CPG - 1 && end < N && jl == cj) {                         // the lanes that hold the state after the group
+        unsigned long long w = pack2(L, M);
+        if (w >= kCarryStopped) w = kCarryStopped - 1;                  // (a NaN pair that looks like one of the two)
+        st_relaxed(&carry[G + g], gone || here ? kCarryStopped : w);
+    }
     if (lane < G) sh.cnt[lane] = cnt;
+    const int missing = c < mine ? first_unpublished<G>(words, c + 1, mine, lane) : -1;
+    if (lane == 0) sh.next = c == mine ? -1 : (missing >= 0 ? missing : mine);
 }
 
 // =================================================================================================
@@ -542,8 +581,8 @@ __device__ void settle_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const 
 // =================================================================================================
 constexpr int kWholeChunk = 32;      // blocks of a chunk in the default plan: the size with a fixed schedule
 template <int DT, int G, int MAXB>
-__device__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int s, int c) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6), rg = lane >> 4, cl = lane & 15;
+__device__ __forceinline__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int s, int c, int tid) {
+    const int lane = tid & 63, wave = uniform(tid >> 6), rg = lane >> 4, cl = lane & 15;
     const int h = s % kv.num_kv_heads;
     const int mycnt = sh.cnt[lane % G];                        // blocks of the chunk that head lane % G uses
     int maxcnt = mycnt;
@@ -627,6 +666,42 @@ __device__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const 
     }
 }
 
+struct SelectArgs {
+    KvView kv;
+    const uint8_t *q;
+    DecodeWs ws;
+    float eps;
+    int m, CB, budget, window, spin_limit;
+    const int32_t *depth_hint;
+};
+
+// The workgroup's chunk, c, is not settled (see settle_chunk): reads the chunks that are asked for until it is.  Hardly ever
+// needed, so nothing of it may cost the way that all others take: it has the kernel's arguments anew from where they were
+// passed, and the thread's index anew, or their values and what derives from them would be kept in registers, which are short.
+template <int DT, int G, int MAXB>
+__device__ __forceinline__ void catch_up(SelectShared<G, MAXB> &sh, int s, int c) {
+    typedef const __attribute__((address_space(4))) uint32_t *Words;
+    Words from = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+    int tid = threadIdx.x;
+    asm volatile("" : "+s"(from), "+v"(tid));
+    uint32_t copy[sizeof(SelectArgs) / 4];
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(SelectArgs) / 4; ++i) copy[i] = from[i];
+    SelectArgs a;
+    __builtin_memcpy(&a, copy, sizeof(a));
+    const int N = (stream_ctx(a.kv, s) + kPage - 1) / kPage;
+    for (int at = uniform(sh.next); at >= 0;) {
+        lds_barrier();                          // (everyone has read sh.next, and is done with the chunk before)
+        stage_pages<G, MAXB>(sh, a.kv, a.ws, a.CB, s, at, tid);
+        if (tid == 0) atomicAdd(&a.ws.ctl[s].k_blocks, min(a.CB, N - at * a.CB));
+        lds_barrier();
+        const Published own = process_chunk<DT, G, MAXB, 1>(sh, a.kv, a.ws, a.m, a.CB, a.budget, s, at, tid);
+        if (tid < 64) settle_chunk<G, MAXB>(sh, a.kv, a.ws, own, a.eps, a.m, a.CB, a.spin_limit, s, at, c, tid);
+        lds_barrier();
+        at = uniform(sh.next);
+    }
+}
+
 // =================================================================================================
 // grid = folders + S * max_chunks workgroups of 256 threads.  The first `folders` = min(ceil(S / 4), kMaxFoldGroups)
 // workgroups are the folds, one wave per stream (they start first and stay until their streams close); then one
@@ -634,10 +709,13 @@ __device__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const 
 // those waves after the other.
 // =================================================================================================
 template <int DT, int G, int MAXB>
-__global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select_kernel(KvView kv, const uint8_t *__restrict__ q,
-                                                                DecodeWs ws, float eps, int m, int CB, int budget,
-                                                                int window, int spin_limit,
-                                                                const int32_t *depth_hint) {
+__global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select_kernel(SelectArgs args) {
+    const KvView &kv = args.kv;
+    const DecodeWs &ws = args.ws;
+    const uint8_t *__restrict__ q = args.q;
+    const int32_t *depth_hint = args.depth_hint;
+    const float eps = args.eps;
+    const int m = args.m, CB = args.CB, budget = args.budget, window = args.window, spin_limit = args.spin_limit;
     __shared__ SelectShared<G, MAXB> sh;
     const int S = kv.batch * kv.num_kv_heads;
     const int folders = min((S + 3) / 4, kMaxFoldGroups);
@@ -668,7 +746,7 @@ __global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select
     const int N = (stream_ctx(kv, s) + kPage - 1) / kPage;
     if (c * CB >= N) return;
     load_queries<G, MAXB>(sh, kv, q, s);
-    stage_pages<G, MAXB>(sh, kv, ws, CB, s, c);
+    stage_pages<G, MAXB>(sh, kv, ws, CB, s, c, threadIdx.x);
     if (threadIdx.x == 0) sh.kp0 = kp_first;
     lds_barrier();
     if (c >= progress_limit(sh.kp0)) return;          // closed, out of reach, or beyond a block budget
@@ -703,14 +781,16 @@ __global__ __launch_bounds__(kSelectThreads, G * MAXB > 256 ? 2 : 4) void select
     lds_barrier();
     if (!sh.go) return;
     if (threadIdx.x == 0) atomicAdd(&ws.ctl[s].k_blocks, min(CB, N - c * CB));     // traffic accounting
-    const Published own = process_chunk<DT, G, MAXB>(sh, kv, q, ws, m, CB, budget, s, c);
+    const Published own = process_chunk<DT, G, MAXB, kKeyDepth>(sh, kv, ws, m, CB, budget, s, c, threadIdx.x);
     if (budget > 0) {                          // used by every head: the values wait for nothing
         if (threadIdx.x < G) sh.cnt[threadIdx.x] = min(CB, min(N, budget) - c * CB);
+        if (threadIdx.x == 0) sh.next = -1;
     } else if (threadIdx.x < 64) {
-        settle_chunk<G, MAXB>(sh, kv, ws, own, eps, m, CB, s, c);
+        settle_chunk<G, MAXB>(sh, kv, ws, own, eps, m, CB, spin_limit, s, c, c, threadIdx.x);
     }
     lds_barrier();
-    attend_chunk<DT, G, MAXB>(sh, kv, ws, s, c);
+    if (__builtin_expect(sh.next >= 0, 0)) catch_up<DT, G, MAXB>(sh, s, c);
+    attend_chunk<DT, G, MAXB>(sh, kv, ws, s, c, threadIdx.x);
 }
 
 template <int DT, int G>
@@ -719,12 +799,12 @@ static hipError_t launch_select_t(const KvView &kv, const void *q, const DecodeW
     const unsigned S = (unsigned)(kv.batch * kv.num_kv_heads);
     const unsigned folders = (S + 3) / 4 < (unsigned)kMaxFoldGroups ? (S + 3) / 4 : (unsigned)kMaxFoldGroups;
     const unsigned grid = folders + S * (unsigned)plan.max_chunks;
+    const SelectArgs args = {kv, (const uint8_t *)q, ws, eps, m, plan.chunk_blocks, budget, plan.window_chunks, plan.spin_limit,
+                             plan.depth_hint};
     if (plan.chunk_blocks <= 32)
-        select_kernel<DT, G, 32><<<grid, kSelectThreads, 0, st>>>(kv, (const uint8_t *)q, ws, eps, m, plan.chunk_blocks,
-                                                         budget, plan.window_chunks, plan.spin_limit, plan.depth_hint);
+        select_kernel<DT, G, 32><<<grid, kSelectThreads, 0, st>>>(args);
     else
-        select_kernel<DT, G, kMaxChunkBlocks><<<grid, kSelectThreads, 0, st>>>(kv, (const uint8_t *)q, ws, eps, m, plan.chunk_blocks,
-                                                          budget, plan.window_chunks, plan.spin_limit, plan.depth_hint);
+        select_kernel<DT, G, kMaxChunkBlocks><<<grid, kSelectThreads, 0, st>>>(args);
     return hipGetLastError();
 }
 
