@@ -31,9 +31,12 @@ __global__ __launch_bounds__(512) void finalize_kernel(KvView kv, DecodeWs ws, i
     const int N = (ctx + kPage - 1) / kPage;
     const StreamCtl *ctl = &ws.ctl[s];
     const unsigned long long st = ctl->stop[g];
-    int n = N;
+    // Blocks the fold has gone over: all that any head uses, unless it gave up (PSA_DEVERR_STALLED); beyond them the chunks'
+    // outputs may be another call's.
+    const int folded = min(N, (int)(ctl->key_progress & 0xffffull) * VU);
+    int n = folded;
     float P = N > 0 ? 1.0f : 0.0f;
-    if (st != ~0ull && (int)(st >> 32) <= N) { n = (int)(st >> 32); P = __uint_as_float((uint32_t)st); }
+    if (st != ~0ull && (int)(st >> 32) <= folded) { n = (int)(st >> 32); P = __uint_as_float((uint32_t)st); }
     const int nun = (n + VU - 1) / VU;
     const float *src = ws.partial + ((size_t)s * ws.max_units * G + g) * kPartialStride;
     const size_t stride = (size_t)G * kPartialStride;
@@ -95,7 +98,7 @@ __global__ __launch_bounds__(512) void finalize_kernel(KvView kv, DecodeWs ws, i
                 int mx = 0;
                 for (int x = 0; x < G; ++x) {
                     const unsigned long long sx = ctl->stop[x];
-                    const int nx = (sx != ~0ull && (int)(sx >> 32) <= N) ? (int)(sx >> 32) : N;
+                    const int nx = (sx != ~0ull && (int)(sx >> 32) <= folded) ? (int)(sx >> 32) : folded;
                     mx = max(mx, nx);
                 }
                 if (blocks_read) blocks_read[s] = mx;
