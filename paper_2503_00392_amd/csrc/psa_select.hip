@@ -675,30 +675,42 @@ struct SelectArgs {
     const int32_t *depth_hint;
 };
 
-// The workgroup's chunk, c, is not settled (see settle_chunk): reads the chunks that are asked for until it is.  Hardly ever
-// needed, so nothing of it may cost the way that all others take: it has the kernel's arguments anew from where they were
-// passed, and the thread's index anew, or their values and what derives from them would be kept in registers, which are short.
-template <int DT, int G, int MAXB>
-__device__ __forceinline__ void catch_up(SelectShared<G, MAXB> &sh, int s, int c) {
+// The kernel's arguments, anew from where they were passed.
+__device__ __forceinline__ SelectArgs args_anew() {
     typedef const __attribute__((address_space(4))) uint32_t *Words;
     Words from = (Words)__builtin_amdgcn_kernarg_segment_ptr();
-    int tid = threadIdx.x;
-    asm volatile("" : "+s"(from), "+v"(tid));
+    asm volatile("" : "+s"(from));
     uint32_t copy[sizeof(SelectArgs) / 4];
 #pragma unroll
     for (unsigned i = 0; i < sizeof(SelectArgs) / 4; ++i) copy[i] = from[i];
     SelectArgs a;
     __builtin_memcpy(&a, copy, sizeof(a));
-    const int N = (stream_ctx(a.kv, s) + kPage - 1) / kPage;
-    for (int at = uniform(sh.next); at >= 0;) {
+    return a;
+}
+
+// The workgroup's chunk, c, is not settled (see settle_chunk): reads the chunks that are asked for until it is.  Hardly ever
+// needed, so nothing of it may cost the way that all others take: it has the kernel's arguments anew, for every step, and the
+// thread's index, or their values and what derives from them would be kept in registers, which are short.
+template <int DT, int G, int MAXB>
+__device__ __forceinline__ void catch_up(SelectShared<G, MAXB> &sh, int s, int c) {
+    for (int at = uniform(sh.next); at >= 0; at = uniform(sh.next)) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
         lds_barrier();                          // (everyone has read sh.next, and is done with the chunk before)
-        stage_pages<G, MAXB>(sh, a.kv, a.ws, a.CB, s, at, tid);
-        if (tid == 0) atomicAdd(&a.ws.ctl[s].k_blocks, min(a.CB, N - at * a.CB));
+        Published own;
+        {
+            const SelectArgs a = args_anew();
+            const int N = (stream_ctx(a.kv, s) + kPage - 1) / kPage;
+            stage_pages<G, MAXB>(sh, a.kv, a.ws, a.CB, s, at, tid);
+            if (tid == 0) atomicAdd(&a.ws.ctl[s].k_blocks, min(a.CB, N - at * a.CB));
+            lds_barrier();
+            own = process_chunk<DT, G, MAXB, 1>(sh, a.kv, a.ws, a.m, a.CB, a.budget, s, at, tid);
+        }
+        {
+            const SelectArgs a = args_anew();
+            if (tid < 64) settle_chunk<G, MAXB>(sh, a.kv, a.ws, own, a.eps, a.m, a.CB, a.spin_limit, s, at, c, tid);
+        }
         lds_barrier();
-        const Published own = process_chunk<DT, G, MAXB, 1>(sh, a.kv, a.ws, a.m, a.CB, a.budget, s, at, tid);
-        if (tid < 64) settle_chunk<G, MAXB>(sh, a.kv, a.ws, own, a.eps, a.m, a.CB, a.spin_limit, s, at, c, tid);
-        lds_barrier();
-        at = uniform(sh.next);
     }
 }
 
