@@ -111,13 +111,16 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
 
 // psa_score.hip, psa_order.hip, psa_select.hip, psa_values.hip: the kernels of one decode call
 // Whether the scores of such a call are formed on the matrix cores (see psa_score.hip).  Another order of sums can swap two
-// blocks whose scores nearly tie, so every path of a call has to form them in the same way.  Up to 128 blocks (one launch,
-// unless tuned) packed dots are as good where they read whole pages' records: two requests of 36 blocks 15.5 us, 15.9 on the
-// matrix cores.  Nor does the centre's score leave them there: minima and maxima cancel in it lane by lane, which keeps its
-// error against binary64 at 4.6e-8 of its size, 5.5e-8 on the matrix cores (the bound's is 5.5e-8 either way).
-inline bool score_on_matrix_cores(int G, int num_kv_heads, int scorer, int max_blocks) {
+// blocks whose scores nearly tie, so every path of a call has to form them in the same way, and the width of the block table
+// must not enter: it is that of the batch's longest request, on whom another's scores must not hang.  (Up to 128 blocks, in
+// one launch, packed dots and the matrix cores take as long: one request of 300 to 1024 tokens and 8 KV heads 14.1 to 16.5 us
+// with dots, 14.2 to 16.8 with products; 32 of up to 1500 23.6 and 23.1; 64 of up to 2048 53.1 and 52.5.)
+// The centre's score stays with packed dots where they read whole pages' records: minima and maxima cancel in it lane
+// by lane, which keeps its error against binary64 at 4.6e-8 of its size, 5.5e-8 on the matrix cores (the bound's is 5.5e-8
+// either way).
+inline bool score_on_matrix_cores(int G, int num_kv_heads, int scorer) {
     const bool by_pages = num_kv_heads > 1 && 16 % num_kv_heads == 0;
-    return G >= 8 && scorer != 2 && (!by_pages || (scorer == 0 && max_blocks > 128));
+    return G >= 8 && (scorer == 0 || (scorer == 1 && !by_pages));
 }
 hipError_t launch_score(const KvView &kv, int dtype, int G, int scorer, const void *q, const void *meta,
                         const DecodeWs &ws, float *scores_out, hipStream_t st);

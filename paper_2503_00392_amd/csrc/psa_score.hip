@@ -199,17 +199,17 @@ __global__ __launch_bounds__(256) void score_pages_kernel(KvView kv, const uint8
 }
 
 // =================================================================================================
-// Scoring on the matrix cores, at G = 8, where score_on_matrix_cores says so (with packed dots the vector ALUs were busy 58 % of the time and more: 64 ragged
-// requests of up to 128K tokens 1376 -> 1347 us a call, 34 of 41K with a budget 94.6 -> 87.4).  Upper bound
-// (CENTER = 0):
+// Scoring on the matrix cores, at G = 8, where score_on_matrix_cores says so (with packed dots the vector ALUs were busy
+// 58 % of the time and more: 64 ragged requests of up to 128K tokens 1376 -> 1347 us a call, 34 of 41K with a budget
+// 94.6 -> 87.4).  Upper bound (CENTER = 0):
 //   UB[g][b] = (1/sqrt d) sum_c max(q_c kmin_c, q_c kmax_c) = (1/sqrt d) (q- . kmin + q+ . kmax)
 //   with q+ = max(q,0), q- = min(q,0).
 // Cuboid centre (CENTER = 1): (1/sqrt d) q . (kmin + kmax)/2 = (1/(2 sqrt d)) (q . kmin + q . kmax).
 // Either way CS[b] = max over the heads g of the group.
 // Both are one matrix product over the 256 numbers of a block's record [min(128) | max(128)]:
 //   D[block][head] = sum_e record[block][e] * qq[e][head],  qq = (q- | q+) or (q | q),
-// done as eight 16x16x32 products and a tree of sums: 16 blocks of one KV head, row = block, the record's 512 contiguous bytes are the k
-// dimension; columns beyond G are zero and left out of the maximum.
+// done as eight 16x16x32 products and a tree of sums: 16 blocks of one KV head, row = block, the record's 512 contiguous
+// bytes are the k dimension; columns beyond G are zero and left out of the maximum.
 // A wave takes such a unit of 16 blocks (8 KiB), or up to kMaxRounds of them of one head, two in flight.  Loaded in the
 // operand's layout a load instruction would touch half a cache line of sixteen records, which made this kernel slower than
 // the packed dots; so a record is loaded whole (32 lanes, two records to an instruction) and turned into the operand's
@@ -307,7 +307,7 @@ static hipError_t launch_score_t(const KvView &kv, int scorer, const void *q, co
                                                        scores_out, ws.header, rounds);
         return hipGetLastError();
     }
-    if constexpr (G >= 8) if (score_on_matrix_cores(G, kv.num_kv_heads, scorer, kv.max_blocks)) {
+    if constexpr (G >= 8) if (score_on_matrix_cores(G, kv.num_kv_heads, scorer)) {
         const int units = (kv.max_blocks + 16 * rounds - 1) / (16 * rounds) * kv.num_kv_heads;
         const dim3 grid_u((units + 3) / 4, kv.batch);
         if (scorer == 1)
@@ -330,7 +330,7 @@ static hipError_t launch_score_t(const KvView &kv, int scorer, const void *q, co
         if (scorer == 1)
             score_pages_kernel<DT, G, 1><<<grid_p, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
                                                                  scores_out, ws.header, nb);
-        else
+        else if constexpr (G < 8)
             score_pages_kernel<DT, G, 0><<<grid_p, 256, 0, st>>>(kv, (const uint8_t *)q, (const uint8_t *)meta, ws.scores,
                                                                  scores_out, ws.header, nb);
     } else if constexpr (G < 8) {

@@ -413,11 +413,12 @@ static hipError_t launch_solo_t(const KvView &kv, const DecodeArgs &a, const Dec
 template <int DT, int G>
 static hipError_t launch_solo_g(const KvView &kv, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st) {
     if constexpr (G >= 8) {
-        if (score_on_matrix_cores(G, kv.num_kv_heads, a.scorer, kv.max_blocks))
+        if (score_on_matrix_cores(G, kv.num_kv_heads, a.scorer))
             return a.scorer == 1 ? launch_solo_t<DT, G, 1, true>(kv, a, ws, st) : launch_solo_t<DT, G, 0, true>(kv, a, ws, st);
+    } else if (a.scorer == 0) {
+        return launch_solo_t<DT, G, 0>(kv, a, ws, st);
     }
-    return a.scorer == 2 ? launch_solo_t<DT, G, 2>(kv, a, ws, st)
-                         : (a.scorer == 1 ? launch_solo_t<DT, G, 1>(kv, a, ws, st) : launch_solo_t<DT, G, 0>(kv, a, ws, st));
+    return a.scorer == 2 ? launch_solo_t<DT, G, 2>(kv, a, ws, st) : launch_solo_t<DT, G, 1>(kv, a, ws, st);
 }
 
 hipError_t launch_solo(const KvView &kv, int dtype, int G, const DecodeArgs &a, const DecodeWs &ws, hipStream_t st) {

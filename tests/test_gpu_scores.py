@@ -49,3 +49,30 @@ def test_scores_against_their_definition(psa, G, H, batch, max_blocks, scorer, d
             want = torch.matmul((a + b).permute(1, 0, 2), x) / 2
         want = want.amax(dim=2) / 128 ** 0.5                                    # [H][n]
         assert (out.scores[r, :, :n].double() - want).abs().max() <= gc.SCORE_ERR, r
+
+
+@pytest.mark.parametrize("G,H", [(8, 1), (8, 2), (8, 3), (8, 8), (8, 16), (4, 8), (2, 5), (1, 32)])
+@pytest.mark.parametrize("scorer,dtype", [(0, torch.bfloat16), (1, torch.float16)])
+def test_scores_do_not_depend_on_the_other_requests(psa, G, H, scorer, dtype):
+    """The width of the block table is that of the batch's longest request.  The same requests in tables of other widths, and
+    beside a longer request, get the same bits: scores, ranking, stops and outputs."""
+    gen = torch.Generator(device="cuda").manual_seed(G * 100 + H)
+    pages, lens = 400, [1, 37, 16 * 61, 16 * 90 + 5]
+    k, v = (torch.randn((pages, H, 16, 128), generator=gen, device="cuda").to(dtype) for _ in range(2))
+    q = torch.randn((5, G * H, 128), generator=gen, device="cuda").to(dtype)
+    rows = torch.randint(0, pages, (5, 1100), generator=gen, device="cuda", dtype=torch.int32)
+    want = None
+    for longest in (0, 128, 129, 200, 257, 1100):
+        n = 5 if longest else 4
+        kv = psa.KvCache(k, v, rows[:n, :max(longest, 91)].contiguous(),
+                         torch.tensor((lens + [16 * longest])[:n], dtype=torch.int32, device="cuda"), G * H)
+        meta = psa.build_block_metadata(kv, page_fill=torch.full((pages,), 16, dtype=torch.int32, device="cuda"))
+        out = psa.decode_attention(kv, q[:n].contiguous(), meta, 0.9, 1, want_order=True, want_scores=True, scorer=scorer)
+        torch.cuda.synchronize()
+        assert psa.read_device_error(out._workspace) == 0
+        got = [x[:4] for x in (out.out, out.n_selected, out.mass_est, out.lse)] + [
+            x[r, :, :(lens[r] + 15) // 16] for x in (out.scores, out.order) for r in range(4)]
+        if want is None:
+            want = [x.clone() for x in got]
+        for a, b in zip(got, want):
+            assert torch.equal(a.contiguous().view(torch.int32), b.contiguous().view(torch.int32)), longest
