@@ -21,7 +21,8 @@
  *     What the host can see is checked there (null required pointer, shapes, threshold outside
  *     [0,1] or NaN, check_granularity < 1, workspace too small).  What only the device can see
  *     (a block-table entry outside [0,num_pages), a context longer than max_blocks_per_seq pages,
- *     a negative context length) is clamped by the kernels, which set a sticky bit in the workspace that psa_read_device_error returns.
+ *     a negative context length) is clamped by the kernels, which set a sticky bit in the workspace
+ *     that psa_read_device_error returns.
  *   - Element type of Q, K, V and metadata: IEEE binary16 or bfloat16, 2 bytes.
  *   - Supported shapes: head_dim == 128, page_size == 16, num_q_heads / num_kv_heads in
  *     {1, 2, 4, 8}, max_blocks_per_seq <= 8192 for psa_decode_attention (128K tokens).
@@ -258,8 +259,8 @@ psa_status psa_decode_attention(const psa_kv_desc *desc, const void *q, const vo
  *                     PSA_DEVERR_* bits, 0 = none) -- there is no workspace pointer to hand to
  *                     psa_read_device_error
  * Errors: those of psa_decode_attention; PSA_ERR_WORKSPACE_TOO_SMALL if this descriptor and tuning need more
- * than PSA_STATIC_SCRATCH_BYTES (psa_decode_workspace_bytes tells how much: about 43 MiB for 8 requests x 8
- * KV heads x 32K tokens with 4 query heads per KV head); PSA_ERR_UNSUPPORTED with a second tier.
+ * than PSA_STATIC_SCRATCH_BYTES (psa_decode_workspace_bytes tells how much, an upper bound: about 43 MiB for 8
+ * requests x 8 KV heads x 32K tokens with 4 query heads per KV head); PSA_ERR_UNSUPPORTED with a second tier.
  * All calls on one GPU share that GPU's array, whatever their streams: two calls whose kernels may overlap
  * in time race and give wrong results.  Order them (one stream, or events).  Nothing needs clearing between
  * calls: every call initialises what it reads.

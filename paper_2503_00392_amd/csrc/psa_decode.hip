@@ -39,16 +39,17 @@ DecodePlan make_plan(const psa_kv_desc *d, const psa_tuning *t) {
     p.force_bitonic = t ? t->force_bitonic : 0;
     p.depth_hint = t ? t->depth_hint : nullptr;
     p.events = t ? static_cast<hipEvent_t *>(t->phase_events) : nullptr;
-    // One launch for short contexts, where the chain of launches is what a call costs (psa_solo.hip).  One compute unit
-    // does a stream's work there.  Up to 128 blocks that is the better bargain with any number of streams (one launch
-    // against the chain, 2048 tokens, G = 4): where the rule selects little, 17 us against 26 to 30 with 1 to 8 streams, 31
-    // against 52 with 256; where nearly everything is selected, 61 against 77 with 256 streams, but 32 against 26 with one,
-    // 30 against 28 with 8, 35 against 31 with 32 (at 1536 tokens the two are even there).  Above 128 blocks a stream that selects nearly all its blocks wants more than one unit, unless
-    // there are streams for most of the chip: at 256 blocks 63 us against 32 with 8 streams, 99 against 103 with 192; at
-    // 192 blocks 53 against 53 with 128.  Hence three streams for four blocks.
-    // (The chain was five kernels then.  With four, G = 4, 2048 tokens: little selected 16 us against 24 with 8 streams, 22 against
-    // 27 with 32, 24 against 33 with 128; all selected 25 against 24, 35 against 26, 39 against 39; 256 blocks, 192 streams 56
-    // against 55 and 97 against 93.  A stream's share is not known beforehand, so the line stays.)
+    // One launch for short contexts, where the chain of launches is what a call costs (psa_solo.hip).  One compute unit does
+    // a stream's work there.  Up to 128 blocks that is the better bargain with any number of streams (one launch against the
+    // chain, 2048 tokens, G = 4): where the rule selects little, 17 us against 26 to 30 with 1 to 8 streams, 31 against 52
+    // with 256; where nearly everything is selected, 61 against 77 with 256 streams, but 32 against 26 with one, 30 against
+    // 28 with 8, 35 against 31 with 32 (at 1536 tokens the two are even there).  Above 128 blocks a stream that selects
+    // nearly all its blocks wants more than one unit, unless there are streams for most of the chip: at 256 blocks 63 us
+    // against 32 with 8 streams, 99 against 103 with 192; at 192 blocks 53 against 53 with 128.  Hence three streams for
+    // four blocks.
+    // (The chain was five kernels then.  With four, G = 4, 2048 tokens: little selected 16 us against 24 with 8 streams, 22
+    // against 27 with 32, 24 against 33 with 128; all selected 25 against 24, 35 against 26, 39 against 39; 256 blocks, 192
+    // streams 56 against 55 and 97 against 93.  A stream's share is not known beforehand, so the line stays.)
     // Whoever tunes the general path, times its phases or brings a second tier gets the general path.  So does a call of more
     // streams than one grid of workgroups of 1024 threads can have (fewer than 2^32 threads).
     const bool tuned = t && (t->window_chunks > 0 || t->spin_limit > 0 || t->force_bitonic || t->phase_events ||
@@ -79,8 +80,8 @@ static WsLayout layout(const psa_kv_desc *d, const DecodePlan &p) {
     L.logits = at;
     L.agg_tested = at;
     L.carry = align_up(at + S * p.max_chunks * G * 8, 256);
-    // The size is part of the interface (callers keep buffers of it, and what fits the static array is drawn in it), so it
-    // stays what it was when every path kept its logits here, block by block sums beside them, and had a work list.
+    // The size is what it was when every path kept its logits here, block by block sums beside them, and had a work list: what
+    // fits the static array is drawn in it, and calls that were refused there for their size stay refused.
     at = align_up(at + S * MB * kPage * G * 4, 256);
     at = align_up(at + S * MB * G * 4, 256);
     L.total = align_up(at + S * p.max_chunks * 4, 256);
@@ -148,7 +149,6 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     ws.carry = reinterpret_cast<unsigned long long *>(base + L.carry);
     ws.partial = reinterpret_cast<float *>(base + L.partial);
     ws.max_chunks = plan.max_chunks;
-    ws.max_units = plan.max_chunks;
     const int G = d->num_q_heads / d->num_kv_heads;
     ws.max_groups = (plan.max_chunks * G + 63) / 64;
     if (kv.batch == 0) return hipSuccess;
@@ -164,7 +164,8 @@ hipError_t launch_decode(const psa_kv_desc *d, const DecodeArgs &a, const Decode
     if (ev) (void)hipEventRecord(ev[0], st);
     if ((e = launch_score(kv, d->dtype, G, a.scorer, a.q, a.meta, ws, a.scores_out, st)) != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[1], st);
-    if ((e = launch_order(kv, ws, G, plan, a.budget_blocks, d->tier ? make_tier_view(d->tier).slot_of : nullptr, a.order_out, st)) != hipSuccess) return e;
+    const int32_t *slot_of = d->tier ? make_tier_view(d->tier).slot_of : nullptr;
+    if ((e = launch_order(kv, ws, G, plan, a.budget_blocks, slot_of, a.order_out, st)) != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[2], st);
     if ((e = launch_select(kv, d->dtype, G, a.q, ws, a.threshold, a.check_granularity, a.budget_blocks, plan, st)) != hipSuccess)
         return e;

@@ -19,11 +19,12 @@ constexpr int kDenseStride = 132;  // M, l, error bits (head 0), pad, acc[128]
 //           add_weighted); lane (kq, cl) accumulates heads 2kq and 2kq+1 of channels 8cl..8cl+7.
 // The running maximum of a head is shared by the wave (two exchanges per block); the four waves are merged
 // once at the end.
-// Bound by memory: 5.9 -> 6.1 TB/s on 6 ragged requests of up to 64K tokens (147.5 -> 143.0 us a call), 256 requests of up to
-// 2048 143 -> 128 us, 8 of up to 30000 29.2 -> 27.0.  Whole rows of keys are loaded and turned into the operand's layout in
-// LDS, which alone gave 145.5, 134.5 and 28.4: loaded in that layout, an instruction touched half a cache line of sixteen
-// tokens and could not be marked read-once.  The next block's keys are under way while a block is worked on, with three workgroups
-// to a compute unit: with two (as many registers as the compiler likes) 140.6, 129.5 and 30.0, with four 144.7 on the first.
+// Bound by memory: 5.9 -> 6.1 TB/s on 6 ragged requests of up to 64K tokens (146.6 -> 141.7 us a call, each time within
+// 0.1), 256 requests of up to 2048 143 -> 128 us, 8 of up to 30000 29.2 -> 27.0.  Whole rows of keys are loaded and turned
+// into the operand's layout in LDS, which alone gave 145.5, 134.5 and 28.4: loaded in that layout, an instruction touched
+// half a cache line of sixteen tokens and could not be marked read-once.  The next block's keys are under way while a block
+// is worked on, with three workgroups to a compute unit: with two (as many registers as the compiler likes) 140.6, 129.5 and
+// 30.0, with four 144.7 on the first.
 template <int DT, int G>
 __global__ __launch_bounds__(256, 3) void dense_split_kernel(KvView kv, const uint8_t *__restrict__ q,
                                                           float *__restrict__ partial,

@@ -143,7 +143,6 @@ struct DecodeWs {
                             // position 4*r + j of a (block, head) row holds token 4*j + r
     float *partial;         // [S][max_chunks][G][kPartialStride]
     int32_t max_chunks;     // chunks per stream at most
-    int32_t max_units;      // = max_chunks (stride of `partial`)
     int32_t max_groups;     // groups of 64 / G chunks per stream at most
 };
 constexpr int kPartialStride = 132;  // M, l, pad, pad, acc[128]
@@ -179,13 +178,6 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float acc) {
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-// Four floats written once and read once, by a later kernel, and four such floats read (see ld16_stream).
-__device__ __forceinline__ void store_stream(float *p, f32x4_t v) {
-    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t *>(p));
-}
-__device__ __forceinline__ f32x4_t load_stream(const float *p) {
-    return __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(p));
-}
 template <int DT>
 __device__ __forceinline__ f32x4_t mfma_16x16x32(const uint4 &a, const uint4 &b, f32x4_t c) {
     if constexpr (DT == 0) {
@@ -324,9 +316,9 @@ __device__ __forceinline__ void lds_wave_sync() {
 // 16-byte global load of 8 packed 16-bit values.
 __device__ __forceinline__ uint4 ld16(const uint8_t *p) { return *reinterpret_cast<const uint4 *>(p); }
 
-// The same for data that is read once (key and value slices, metadata records, the stored logits): marked
-// non-temporal, so that hundreds of megabytes streaming through a launch do not push out of the caches what is
-// used again -- queries, page lists, control words, the logits on their way to the next kernel.
+// The same for data that is read once (key and value slices, metadata records): marked non-temporal, so that hundreds
+// of megabytes streaming through a launch do not push out of the caches what is used again -- queries, page lists,
+// control words.
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 ld16_stream(const uint8_t *p) {
     const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));

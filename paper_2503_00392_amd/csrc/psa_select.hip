@@ -31,12 +31,13 @@
 // Keys and values in one kernel: the logits stay in LDS.  In a kernel of its own the value pass had them written to memory
 // and read back (6 % of the keys' bytes at G = 4, 12 % at G = 8, and writes cost this kernel several times their bytes), and
 // it could not begin before the last stream's fold had ended, nor the launch gap be hidden; here the values of the streams
-// that stop early are read while the deep ones are still folding.  Two kernels -> one: 32K tokens, batch 8 102.5 -> 89.2 us a
-// call, four layers at 128K 767 -> 679, 64 ragged requests at G = 8 1610 -> 1399, everything selected (64K, batch 16)
-// 862 -> 773, one request of 4K tokens 32.6 -> 29.0.  A slot is held while a workgroup waits for the fold, which is why this
-// lost in an earlier form with fewer resident workgroups: four fit a compute unit with two value slices in flight per wave
-// (128 registers); three with four slices were 4 % slower at G = 8, and no faster elsewhere.  Value slices asked for before the
-// fold's answer, where the stream was likely to need them, made no difference.
+// that stop early are read while the deep ones are still folding.  Two kernels -> one (median of repeated calls, all builds
+// in turn on one machine, here and below): 32K tokens, batch 8 103.2 -> 88.4 us a call, four layers at 128K 758 -> 684, 64
+// ragged requests at G = 8 1555 -> 1361, everything selected (64K, batch 16) 848 -> 761, one request of 4K tokens 32.1 ->
+// 29.0.  A slot is held while a workgroup waits for the fold, which is why this lost in an earlier form with fewer resident
+// workgroups: four fit a compute unit with two value slices in flight per wave (128 registers); three with four slices were
+// 4 % slower at G = 8, and no faster elsewhere.  Value slices asked for before the fold's answer, where the stream was
+// likely to need them, made no difference.
 // From the last key to the published word a chunk takes 0.9 us, and 3.2 us from its first load on an idle chip; with
 // the reduction inside the loop over the slices, and the words after all stores, these were 1.0 us (3 us under load)
 // and 4.6 us.  A call at 32K tokens, batch 8, went from 112.5 to 109.7 us, at 4K, batch 31, from 58.1 to 54.1.
@@ -48,19 +49,20 @@
 // way round.  So nobody relies on it: when the looks of step 5 run out, the workgroup reads the missing chunks itself and makes
 // their words and, at the end of a group, the carry.  Every workgroup that has started then ends without any that has not, in
 // whatever order they are started.
-// THE FOLD applies lines 12-17 chunk by chunk, strictly in rank order, to steer the reading: AS_acc, AS_min and P_acc at
-// the last tested position of each published chunk after the frontier say in which chunk every head stops.  One wave per
-// stream does it, in workgroups of its own at the head of the grid (so they start first): it looks at the words of the next
-// chunks, folds what is published, moves the frontier, tells the readers how far the stream can still go (stop_bound),
-// and looks again.  Once every head has stopped (or the blocks ran out) it closes the stream: the chunks beyond what it used
-// are never read.  Chunks are folded in groups (see fold_stream); the workgroup of a group's last chunk leaves the state after it in
-// a carry word per head, from which the next group's workgroups go on by themselves in step 5.  They had waited for the fold to pass their chunk and to
-// hand out the stops before, which it found from the L_b in memory: a chunk's way from its word to its values was then the
-// fold's look, its arithmetic, a load of the L_b, two stores one after the other, and the workgroup's look and load of the
-// stops -- 3.7 to 5.2 us on an idle chip and 7.5 in the median of a busy one.  One request of 4K tokens 29.0 -> 25.9 us a call,
-// 32K tokens, batch 8 89.2 -> 86.1, four layers at 128K 681 -> 669, 64 ragged requests at G = 8 1401 -> 1366, two tiers 353 ->
-// 335.  (With every waiting workgroup looking at its group's words all the time, instead of at one word until the fold has come
-// to the group, everything selected at 64K, batch 16, took 820 us instead of 766.)
+// THE FOLD applies lines 12-17 chunk by chunk, strictly in rank order, to steer the reading: AS_acc, AS_min and P_acc at the
+// last tested position of each published chunk after the frontier say in which chunk every head stops.  One wave per stream
+// does it, in workgroups of its own at the head of the grid (so they start first): it looks at the words of the next chunks,
+// folds what is published, moves the frontier, tells the readers how far the stream can still go (stop_bound), and looks
+// again.  Once every head has stopped (or the blocks ran out) it closes the stream: the chunks beyond what it used are never
+// read.  Chunks are folded in groups (see fold_stream); the workgroup of a group's last chunk leaves the state after it in a
+// carry word per head, from which the next group's workgroups go on by themselves in step 5.  They had waited for the fold
+// to pass their chunk and to hand out the stops before, which it found from the L_b in memory: a chunk's way from its word
+// to its values was then the fold's look, its arithmetic, a load of the L_b, two stores one after the other, and the
+// workgroup's look and load of the stops -- 3.7 to 5.2 us on an idle chip and 7.5 in the median of a busy one.  One request
+// of 4K tokens 29.0 -> 26.8 us a call, 32K tokens, batch 8 88.4 -> 84.7, four layers at 128K 684 -> 672, 64 ragged requests
+// at G = 8 1361 -> 1331, two tiers 522 -> 502.  (With every waiting workgroup looking at its group's words all the time,
+// instead of at one word until the fold has come to the group, everything selected at 64K, batch 16, took 820 us instead of
+// 766.)
 //
 // Communication between workgroups: every shared word is read and written with relaxed agent-scope
 // atomics (coherent accesses); a writer waits for its data stores to complete before it stores the
@@ -84,14 +86,8 @@ __device__ __forceinline__ int ld_relaxed(const int32_t *p) {
 __device__ __forceinline__ unsigned long long ld_relaxed(const unsigned long long *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint32_t ld_relaxed(const uint32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ float ld_relaxed(const float *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_relaxed(int32_t *p, int v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_relaxed(unsigned long long *p, unsigned long long v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -107,11 +103,6 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 
 __device__ __forceinline__ unsigned long long pack2(float a, float b) {
     return ((unsigned long long)__float_as_uint(b) << 32) | __float_as_uint(a);
-}
-__device__ __forceinline__ unsigned long long shfl_u64(unsigned long long v, int src) {
-    const int lo = __shfl((int)(v & 0xffffffffull), src);
-    const int hi = __shfl((int)(v >> 32), src);
-    return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
 }
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -156,12 +147,12 @@ struct SelectShared {
     float st_l[kSelectThreads / 64][G], st_ref[G];   // value phase: per wave the sum of its weights, the reference
 };
 
-// How far a stream can still go, in chunks, given what the fold knows after n blocks.  AS_acc only grows and
-// AS_min only shrinks as more blocks are folded, so for any n* >= n
+// How far a stream can still go, in chunks, given what the fold knows after n blocks.  AS_acc only grows and AS_min only
+// shrinks as more blocks are folded, so for any n* >= n
 //     P_acc(n*) >= AS_acc(n) / (AS_acc(n) + AS_min(n) (N - n*)),
-// and the right-hand side exceeds eps as soon as N - n* < (AS_acc(n) / AS_min(n)) (1 - eps) / eps: the head stops at
-// the first tested position from there on, whatever the blocks in between hold.  Lane g < G carries head g
-// (stop_end > 0: it has stopped in the chunk that ends there; lanes >= G need nothing); the result, the largest need of the group plus one chunk
+// and the right-hand side exceeds eps as soon as N - n* < (AS_acc(n) / AS_min(n)) (1 - eps) / eps: the head stops at the
+// first tested position from there on, whatever the blocks in between hold.  Lane g < G carries head g (stop_end > 0: it has
+// stopped in the chunk that ends there; lanes >= G need nothing); the result, the largest need of the group plus one chunk
 // to spare against rounding, is the same in every lane.  Keys beyond it are never worth reading.
 template <int G>
 __device__ __forceinline__ int stop_bound(float Lacc, float Lmin, int stop_end, int n, int N, int m, int KU, float odds) {
@@ -210,13 +201,13 @@ __device__ __forceinline__ int granted(int window, int S, int closed) {
 // fold is reproducible bit for bit although its timing is not, and the chunks' own workgroups find the same bits.
 //
 // The wave waits for nothing but chunks whose workgroups are in this kernel's grid, and those end without it: they wait for
-// the window and for chunks before them, each a bounded number of looks; so it always ends.  A count of looks bounds it all the same
-// (kFoldPatience: about half a second in which neither this stream moves nor another one closes), after which the stream
-// is closed as it stands and PSA_DEVERR_STALLED is raised.  With more streams than folding waves (4 * kMaxFoldGroups) a
-// wave folds several streams, one after the other, and the grid hands out the chunks in the same order: all chunks of the
+// the window and for chunks before them, each a bounded number of looks; so it always ends.  A count of looks bounds it all
+// the same (kFoldPatience: about half a second in which neither this stream moves nor another one closes), after which the
+// stream is closed as it stands and PSA_DEVERR_STALLED is raised.  With more streams than folding waves (4 * kMaxFoldGroups)
+// a wave folds several streams, one after the other, and the grid hands out the chunks in the same order: all chunks of the
 // streams that are folded first, then those of the next.  A chunk whose fold has not begun would otherwise hold its slot
-// until its looks run out, thousands of them all slots there are, while the chunks the folds wait for have not started
-// (4096 streams of 512 blocks, all selected: 860 ms and PSA_DEVERR_STALLED).
+// until its looks run out, thousands of them all slots there are, while the chunks the folds wait for have not started (4096
+// streams of 512 blocks, all selected: 860 ms and PSA_DEVERR_STALLED).
 // =================================================================================================
 constexpr int kFoldPatience = 1 << 19;
 constexpr int kMaxFoldGroups = 128;            // workgroups of four folding waves at most: they must leave the
@@ -448,7 +439,8 @@ __device__ __forceinline__ Published process_chunk(SelectShared<G, MAXB> &sh, co
     own.LT = -INFINITY;
     own.MT = INFINITY;
     if (split_words(CB, m, budget)) {                // the same up to the chunk's last tested position, in memory before the word
-        chunk_aggregate<G>(&sh.Lb[0][0], last_test(start, min(start + nblk, blocks_that_count(N, budget)), m, N) - start, lane, own.LT, own.MT);
+        const int upto = last_test(start, min(start + nblk, blocks_that_count(N, budget)), m, N) - start;
+        chunk_aggregate<G>(&sh.Lb[0][0], upto, lane, own.LT, own.MT);
         float2 *t = ws.agg_tested + ((size_t)s * ws.max_chunks + c) * G + lane;
         if (lane < G) { st_relaxed(&t->x, own.LT); st_relaxed(&t->y, own.MT); }
         stores_done();
@@ -475,13 +467,14 @@ __device__ __forceinline__ int first_unpublished(const unsigned long long *agg, 
 // other (8 requests of 32K tokens on each of 3 streams: 203 us a round, 264 in turn).
 constexpr int kPatience = 1 << 10;
 
-// (No fixed budget.)  How many of chunk c's blocks every head uses (sh.cnt), and the stops of the heads that stop in it: wave
-// 0 waits for the words of the group's chunks before this one and for the group's carry, and finds what the fold finds; the
-// group's last chunk leaves the next group's carry.  `own`: what the chunk published.  Nobody needs the workgroup's own chunk, `mine`, if every
-// head stops before it, which the words or the closed stream say.
-// sh.next: -1 once `mine` is settled, else the chunk this workgroup is to read next.  When the looks have brought nothing, the workgroup reads the chunks before its own whose words are missing, the first one first, settles each
-// (c < mine until then), and comes back to its own.  Whatever a chunk leaves in memory is the same bits whoever works on it,
-// so it does not matter that the chunk's own workgroup is under way, or comes later.
+// (No fixed budget.)  How many of chunk c's blocks every head uses (sh.cnt), and the stops of the heads that stop in it:
+// wave 0 waits for the words of the group's chunks before this one and for the group's carry, and finds what the fold finds;
+// the group's last chunk leaves the next group's carry.  `own`: what the chunk published.  Nobody needs the workgroup's own
+// chunk, `mine`, if every head stops before it, which the words or the closed stream say.
+// sh.next: -1 once `mine` is settled, else the chunk this workgroup is to read next.  When the looks have brought nothing,
+// the workgroup reads the chunks before its own whose words are missing, the first one first, settles each (c < mine until
+// then), and comes back to its own.  Whatever a chunk leaves in memory is the same bits whoever works on it, so it does not
+// matter that the chunk's own workgroup is under way, or comes later.
 template <int G, int MAXB>
 __device__ __forceinline__ void settle_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, const Published &own,
                                              float eps, int m, int CB, int spin_limit, int s, int c, int mine, int lane) {
@@ -567,8 +560,8 @@ __device__ __forceinline__ void settle_chunk(SelectShared<G, MAXB> &sh, const Kv
 
 // =================================================================================================
 // The chunk's values (lines 10-12), by the workgroup that holds its logits: the heads that are still open use all of it, and
-// those that stop in it their stop's share (sh.cnt).  The four waves stream independently: wave w takes blocks w, w+4, ... of the chunk, and
-// nothing is shared until the sums at the end.
+// those that stop in it their stop's share (sh.cnt).  The four waves stream independently: wave w takes blocks w, w+4, ...
+// of the chunk, and nothing is shared until the sums at the end.
 //   weights   p = exp(logit - L), L = per head the largest log-sum-exp of a block the head uses: a reference every wave
 //             knows beforehand, so nothing is rescaled on the way and the four waves' sums simply add up.  (p <= 1, and
 //             the largest weight is at least 1/16: the weights keep their precision as 16-bit halves.)
@@ -581,7 +574,8 @@ __device__ __forceinline__ void settle_chunk(SelectShared<G, MAXB> &sh, const Kv
 // =================================================================================================
 constexpr int kWholeChunk = 32;      // blocks of a chunk in the default plan: the size with a fixed schedule
 template <int DT, int G, int MAXB>
-__device__ __forceinline__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int s, int c, int tid) {
+__device__ __forceinline__ void attend_chunk(SelectShared<G, MAXB> &sh, const KvView &kv, const DecodeWs &ws, int s, int c,
+                                             int tid) {
     const int lane = tid & 63, wave = uniform(tid >> 6), rg = lane >> 4, cl = lane & 15;
     const int h = s % kv.num_kv_heads;
     const int mycnt = sh.cnt[lane % G];                        // blocks of the chunk that head lane % G uses
@@ -654,7 +648,7 @@ __device__ __forceinline__ void attend_chunk(SelectShared<G, MAXB> &sh, const Kv
         if (wave == 0) sh.st_ref[hd] = Lc;
     }
     lds_barrier();
-    float *dst = ws.partial + ((size_t)s * ws.max_units + c) * G * kPartialStride;
+    float *dst = ws.partial + ((size_t)s * ws.max_chunks + c) * G * kPartialStride;
     for (int idx = tid; idx < G * kHeadDim; idx += 256) {
         const int g = idx / kHeadDim, ch = idx % kHeadDim;
         dst[g * kPartialStride + 4 + ch] =

@@ -130,7 +130,8 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int j = min(4 * (i & 3) + rg, N - 1 - 16 * wave);     // (clamped: the loads need no branch)
-                a[i] = ld16_stream(meta + ((size_t)__shfl(page_of_lane, j) * kv.num_kv_heads + h) * kMetaBytes + (i >> 2) * 256 + cl * 16);
+                const size_t record = (size_t)__shfl(page_of_lane, j) * kv.num_kv_heads + h;
+                a[i] = ld16_stream(meta + record * kMetaBytes + (i >> 2) * 256 + cl * 16);
             }
             const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
             f32x4_t part[8];
@@ -149,7 +150,8 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
                             w[x] &= half ? ~neg : neg;
                         }
                     }
-                    part[4 * half + kk] = mfma_16x16x32<DT>(sh.stage[wave][cl * 17 + 4 * kk + rg], make_uint4(w[0], w[1], w[2], w[3]), zero);
+                    part[4 * half + kk] = mfma_16x16x32<DT>(sh.stage[wave][cl * 17 + 4 * kk + rg],
+                                                            make_uint4(w[0], w[1], w[2], w[3]), zero);
                 }
                 lds_wave_sync();
             }
@@ -278,7 +280,7 @@ __global__ __launch_bounds__(kSoloThreads) void solo_kernel(KvView kv, DecodeWs 
             }
             lds_barrier();
             if (wave == 0) {
-                int ln = lane;                                 // (opaque: what derives from it is not kept in registers from before the loop)
+                int ln = lane;                                 // (opaque: what derives from it is not kept from before the loop)
                 asm volatile("" : "+v"(ln));
                 const int g = ln % G, jl = ln / G, k = (b0 + nblk + kSoloChunk - 1) / kSoloChunk;
                 const float L = jl < k ? sh.aggL[jl][g] : -INFINITY, M = jl < k ? sh.aggMin[jl][g] : INFINITY;

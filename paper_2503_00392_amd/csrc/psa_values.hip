@@ -38,7 +38,7 @@ __global__ __launch_bounds__(512) void finalize_kernel(KvView kv, DecodeWs ws, i
     float P = N > 0 ? 1.0f : 0.0f;
     if (st != ~0ull && (int)(st >> 32) <= folded) { n = (int)(st >> 32); P = __uint_as_float((uint32_t)st); }
     const int nun = (n + VU - 1) / VU;
-    const float *src = ws.partial + ((size_t)s * ws.max_units * G + g) * kPartialStride;
+    const float *src = ws.partial + ((size_t)s * ws.max_chunks * G + g) * kPartialStride;
     const size_t stride = (size_t)G * kPartialStride;
 
     // reference maximum over the units

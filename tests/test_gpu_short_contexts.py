@@ -1,4 +1,4 @@
-"""Requests that fit one workgroup take one launch instead of five kernels.  Both paths form the same sums in the
+"""Requests that fit one workgroup take one launch instead of four kernels.  Both paths form the same sums in the
 same order, so every output has to agree bit for bit; any tuning of the general path selects that path.  Sizes: the
 edges of a chunk (32 ranked blocks), of a step of key reads (64) and of the path itself (128 blocks, or up to 256 with
 three streams for four blocks)."""
