@@ -7,7 +7,7 @@
 // One workgroup of sixteen waves has no one to wait for: a barrier replaces a launch, LDS replaces the workspace.
 // 1024 tokens, 8 streams, G = 4: 28.0 -> 14.4 us; 256 streams: 38.2 -> 19.7; 2048 tokens: 30.8 -> 18.4 and 47.9 -> 28.1;
 // 4096 tokens, 256 streams: 60.4 -> 44.0.  What bounds it then is what one compute unit can have in flight between the
-// barriers: with 8 streams its waves wait for 57 to 70 % of their time and its vector ALUs are busy 27 to 41 % (by counters).
+// barriers: with 8 streams its waves wait for 58 to 70 % of their time and its vector ALUs are busy 27 to 37 % (by counters).
 // Reading keys a step ahead, or four value slices instead of two, ran out of registers and was 5 to 20 % slower.
 //
 // The results are bit for bit those of the general path: the same products (scores on the matrix cores where that forms
